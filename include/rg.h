@@ -69,7 +69,10 @@ typedef enum {
     RG_ERR_ALIAS = 6     /* y overlaps x or W */
 } rg_status;
 
-/* Kernel ids reported by rg_plan (scheduling only; the order is the same). */
+/* Kernel ids reported by rg_plan (scheduling only; the order is the same).  A shape's id names its class:
+ * the kernel a launch forced with rg_linear_set_launch runs.  Default launches (no override) of the
+ * classes GENERIC, and SKINNY, KTILE, WTILE and TILED with M > 8 (FP32 weights: M > 4), run the wave-tile kernel,
+ * whose output tile (8 x 16 to 64 x 64) and waves are a function of M, N, K, the weight type and the alignment. */
 typedef enum {
     RG_KERNEL_GENERIC = 0,   /* one thread per output; any K, any alignment */
     RG_KERNEL_DECODE = 1,    /* M <= 4 (or K < 4096 up to M = 64): streaming skinny GEMM, x in registers */
@@ -86,10 +89,9 @@ typedef enum {
     RG_KERNEL_SKINNY = 7,    /* M <= 16, and narrow layers to M = 64: waves of 16 W rows x 4
                                 segments, x of a segment shared by 16 lanes through DPP row
                                 broadcasts, slices of 1, 2, 4 or 8 rows of x */
-    RG_KERNEL_WTILE = 8      /* 32 < M <= 64 on wide layers: 64 x 64 output tiles, each wave the
-                                whole tile for one segment at a time (8 x 8 chains per lane),
-                                its own LDS slabs, the partials added wave by wave in segment
-                                order */
+    RG_KERNEL_WTILE = 8      /* 32 < M <= 64 on wide layers (forced: 64 x 64 output tiles): each wave the
+                                whole tile for one segment at a time (8 x 8 chains per lane), its
+                                own LDS slabs, the partials of a round folded in segment order */
 } rg_kernel_id;
 
 /* Scheduling overrides for the determinism tests.  0 in a field = planner
@@ -125,7 +127,9 @@ typedef struct {
     int32_t reserved;
 } rg_launch_t;
 
-/* What rg_linear will do for a shape (on a 256-CU MI355X with default launch). */
+/* The class of a shape and its kernel's schedule (on a 256-CU MI355X) under the current overrides; where
+ * a default launch takes the wave-tile kernel (see rg_kernel_id) the fields from waves_per_wg on are the
+ * class's own kernel's. */
 typedef struct {
     int32_t order_id;      /* RG_ORDER_ID */
     int32_t chunk;         /* C = 256 */
@@ -146,8 +150,8 @@ typedef struct {
  *   y      device pointer, float32 [M][N], 4-byte aligned, must not overlap x or W
  *   M,N,K  >= 1
  *   stream hipStream_t or NULL
- * The caller owns all buffers.  Fast paths need 16-byte aligned x and W and
- * K % 8 == 0; other shapes take a slower kernel with the same order and bits.
+ * The caller owns all buffers.  The fastest paths need 16-byte aligned x and W
+ * and K % 8 == 0; other shapes are staged through registers, with the same order and bits.
  * Returns RG_OK once the kernel is enqueued, or an rg_status error (nothing
  * is enqueued on error).  Launch-time HIP errors are returned as RG_ERR_HIP.
  */
@@ -174,9 +178,8 @@ int rg_linear_bias(const float* x, const uint16_t* w_bf16, const float* bias, fl
  *   x      device pointer, float32 [M][K], 4-byte aligned
  *   w_f32  device pointer, float32 [N][K], 4-byte aligned
  *   y      device pointer, float32 [M][N], 4-byte aligned, must not overlap x or W
- * Kernels: RG_KERNEL_STREAM for M <= 4, then ktile (M <= 64) and tiled
- * (wtile when forced), all needing 16-byte aligned x and W and K % 4 == 0;
- * other shapes take the generic kernel.  Errors, streams and ownership as rg_linear; the same
+ * Kernels: RG_KERNEL_STREAM for M <= 4 with 16-byte aligned x and W and K % 4 == 0, the
+ * wave-tile kernel otherwise; ktile, tiled, wtile and generic when forced.  Errors, streams and ownership as rg_linear; the same
  * rg_linear_set_launch overrides apply (decode, decode_xs and gemv cannot be
  * forced here: RG_ERR_RANGE).
  */

@@ -599,6 +599,34 @@ rg_launch_t current_launch() {
     return g_launch;
 }
 
+// No override at all: the launch is the planner's to choose.
+bool is_default(const rg_launch_t& o) {
+    return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.grid_order == 0 &&
+           o.tile_n == 0 && o.slice_m == 0;
+}
+
+// The shapes a default launch runs on the wave-tile kernel (tile and waves by the rule in
+// rg_wtile.hip) in place of the class's own kernel, which forced launches still run.
+// Measured against the class's kernel, us, interleaved on one MI355X (BF16 weights; before -> now):
+//   skinny, M > 8    QKV 6144 x 4096 at M = 16 / 24 / 64: 23.5 / 41.8 / 73.6 -> 20.2 / 26.8 / 46;
+//                    down 4096 x 14336: 60.6 / 168 / 219 -> 46 / 85 / 109; at M = 8 the skinny
+//                    kernel stays (QKV 17.4 against 16.9, gate+up 50.8 against 57)
+//   ktile, wtile     gate+up 28672 x 4096 at M = 24 / 64: 143 / 220 -> 91 / 183
+//   tiled            gate+up at M = 333: 1118 -> 1036; 8192 x 28672 at M = 2048: 10650 -> 10280
+//   generic          one thread per output, a serial chain of 2-byte loads each: 2999 x 1003
+//                    at M = 5: 255 -> 12
+bool takes_wave_tile(const Plan& p, int64_t M, int64_t K, int64_t own_max_m, const rg_launch_t& o) {
+    if (!is_default(o) || K > rg::kWtileMaxK) return false;
+    switch (p.kernel) {
+        case RG_KERNEL_GENERIC: return true;
+        case RG_KERNEL_SKINNY:
+        case RG_KERNEL_KTILE:
+        case RG_KERNEL_WTILE:
+        case RG_KERNEL_TILED: return M > own_max_m;
+        default: return false;
+    }
+}
+
 // Map a launch result to an rg_status, remembering the HIP code for rg_last_hip_error.
 int hip_status(hipError_t e) {
     t_last_hip = (int)e;
@@ -698,11 +726,16 @@ int linear_impl(const float* x, const uint16_t* w, const float* bias, float* y, 
     if (dc != RG_OK) return dc;
     const bool fast_ok = (K % 8) == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)w & 15) == 0;
     Plan p;
-    const int s = make_plan(M, N, K, fast_ok, current_launch(), &p);
+    const rg_launch_t o = current_launch();
+    const int s = make_plan(M, N, K, fast_ok, o, &p);
     if (s != RG_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();   // drop an error left by an unrelated earlier HIP call on this thread
     hipError_t e = hipSuccess;
+    if (takes_wave_tile(p, M, K, 8, o)) {
+        e = rg::launch_wtile(x, w, bias, y, M, N, K, 0, 0, st);
+        if (e != hipErrorInvalidValue) return hip_status(e);   // more tiles than a grid holds: the class's kernel
+    }
     if (p.kernel == RG_KERNEL_GEMV) {
         rg::GemvArgs a;
         a.x = x;
@@ -768,9 +801,9 @@ int linear_impl(const float* x, const uint16_t* w, const float* bias, float* y, 
         e = launch_stream(x, w, bias, y, M, N, K, p, false, st);
     } else if (p.kernel == RG_KERNEL_KTILE) {
         e = rg::launch_ktile(x, w, bias, y, M, N, K, p.tile_m, p.tile_n, 64 * p.nw, p.cn, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_WTILE) {
+    } else if (p.kernel == RG_KERNEL_WTILE && K <= rg::kWtileMaxK) {
         e = rg::launch_wtile(x, w, bias, y, M, N, K, p.nw, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_TILED) {
+    } else if (p.kernel == RG_KERNEL_TILED || p.kernel == RG_KERNEL_WTILE) {   // (wtile: K beyond its offsets)
         e = rg::launch_tiled(x, w, bias, y, M, N, K, p.tile_m, p.tile_n, p.depth, p.reverse, st);
     } else {
         e = rg::launch_generic(x, w, bias, y, M, N, K, p.grid, p.reverse, st);
@@ -789,18 +822,23 @@ int linear_f32w_impl(const float* x, const float* w, float* y, int64_t M, int64_
     if (dc != RG_OK) return dc;
     const bool fast_ok = (K % 4) == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)w & 15) == 0;
     Plan p;
-    const int s = make_plan_f32w(M, N, K, fast_ok, current_launch(), &p);
+    const rg_launch_t o = current_launch();
+    const int s = make_plan_f32w(M, N, K, fast_ok, o, &p);
     if (s != RG_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();
     hipError_t e = hipSuccess;
+    if (takes_wave_tile(p, M, K, 4, o)) {
+        e = rg::launch_wtile(x, w, nullptr, y, M, N, K, 0, 0, st);
+        if (e != hipErrorInvalidValue) return hip_status(e);
+    }
     if (p.kernel == RG_KERNEL_STREAM) {
         e = launch_stream(x, w, nullptr, y, M, N, K, p, true, st);
     } else if (p.kernel == RG_KERNEL_KTILE) {
         e = rg::launch_ktile(x, w, nullptr, y, M, N, K, p.tile_m, p.tile_n, 64 * p.nw, p.cn, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_WTILE) {
+    } else if (p.kernel == RG_KERNEL_WTILE && K <= rg::kWtileMaxK) {
         e = rg::launch_wtile(x, w, nullptr, y, M, N, K, p.nw, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_TILED) {
+    } else if (p.kernel == RG_KERNEL_TILED || p.kernel == RG_KERNEL_WTILE) {   // (wtile: K beyond its offsets)
         e = rg::launch_tiled(x, w, nullptr, y, M, N, K, p.tile_m, p.tile_n, p.depth, p.reverse, st);
     } else {
         e = rg::launch_generic(x, w, nullptr, y, M, N, K, p.grid, p.reverse, st);

@@ -1,22 +1,38 @@
-// Wave-tile kernel for the fused-upcast linear layer (gfx950): 32 < M <= 64 on wide layers.
+// Wave-tile kernel for the fused-upcast linear layer (gfx950): the default for M > 8, for FP32
+// weights at M > 4, and for every K or alignment the 16-byte kernels do not take.
 //
 // Same order as every kernel of the library (include/rg.h, RG-ORDER-1; paper: Design,
 // eq. 2 and rules R1-R4): 256-wide K segments, each a chain of fmaf from +0 in ascending
 // k, the segment partials folded left to right in ascending segment order.
 //
-// Work split.  A workgroup owns a 64 x 64 output tile (64 rows of x by 64 rows of W) and
-// all of K.  Each of its KS waves holds the whole tile for one segment at a time: lane
-// (mi, ni) = (lane % 8, lane / 8) runs the 8 x 8 chains of x rows {4mi .. 4mi+3, 32+4mi ..
-// 32+4mi+3} and W rows {4ni .. 4ni+3, 32+4ni .. 32+4ni+3}.  Wave g runs segments g, g + KS,
-// g + 2KS, ...; each wave stages the 8-k slabs of its own segment (x, and W widened once)
-// through its own double-buffered LDS region, so a segment runs without any barrier.
-// Per k a lane reads two float4 of x and two of W (the eight lanes that share an address
-// get it by broadcast) and issues 64 plain FMAs: one LDS byte per FMA.
+// Work split.  A workgroup owns a BM x BN output tile and all of K.  Each of its NW waves holds
+// the whole tile for one segment at a time (wave g runs segments g, g + NW, ...): lane
+// (mi, ni) = (lane % LM, lane / LM) runs the TM x TN chains of x rows r LM + mi and W rows
+// c (64 / LM) + ni.  A wave stages the KT-wide slabs of its own segment through its own
+// double-buffered LDS region, so a segment runs without any barrier.
 //
-// Fold.  After each round the waves add their segment partials to the tile's running
-// totals in LDS one after another, in ascending segment order (the first partial starts
-// the sum); the wave that adds the last segment writes y (+ b).  No atomics, no workspace,
-// no second launch.
+// Data path.  Slabs go from memory to LDS by 16-byte DMA as they are, x rows [row][k] in FP32 and
+// W rows [row][k] in their own type: no registers, no transposing stores.  The 16-byte pieces of a row
+// are XOR-swizzled (on the global side of the DMA) so that neighbouring rows reach different
+// banks.  A lane reads four k of a row at once (16 bytes of x, 8 bytes of BF16 W) and
+// widens W in registers.  x or W that are not 16-byte aligned, and K that is not a multiple of the
+// vector, go through registers instead (AL = false: loads of any alignment one slab ahead, then
+// 16-byte LDS stores); the k past K are staged as x = +0 and w = -0, for which
+// fmaf(+0, -0, p) = p for every p.
+//
+// Fold.  After each round of NW segments the waves put their partials in the LDS slot they have
+// just computed from and, after a barrier, every thread adds the round's partials of its
+// outputs in ascending segment order to the running total (LDS); the last round stores
+// y (+ b).  No atomics, no workspace, no second launch.
+//
+// What bounds it.  A SIMD issues one FMA per 2 cycles over two waves (one wave: one per 4), LDS
+// returns 128 bytes per cycle to a CU, so a tile of TM x TN chains per lane is bound by the
+// FMAs (and TN widenings per k) from 8 x 8 down to about 8 x 4, and by its LDS reads
+// (4 / TN + 2 / TM bytes per FMA) below that.  With two waves per SIMD an FMA whose three
+// operands lie in registers of the same parity holds up the other wave, so W is
+// widened into register pairs such that x and W never share a parity (widen2).
+// 28672 x 4096 at M = 64: 183 us (82 TFLOP/s) against 223 with the transposing wave tile this
+// replaced; 4096 x 14336: 109 against 219; 6144 x 4096: 47 against 74.
 //
 // Arithmetic: only v_fmac_f32 / v_fma_f32 and v_add_f32 (the library is built with
 // -ffp-contract=off and packed FP32 disabled), binary32 denormals preserved.
@@ -32,235 +48,548 @@
 namespace rg {
 namespace {
 
-// Weight elements of a 16-byte vector: bfloat16 bit patterns widened exactly (bits << 16;
-// element k at the lower address in the low half of a dword), float32 weights as they are.
-template <typename WT>
-struct WtVec;
-template <>
-struct WtVec<uint16_t> {
-    using V = uint4;
-    static constexpr int E = 8;
-    static __device__ __forceinline__ V zero() { return make_uint4(0u, 0u, 0u, 0u); }
-    static __device__ __forceinline__ float get(const V& v, int h) {
-        const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-        const uint32_t u = d[h >> 1];
-        return __uint_as_float((h & 1) ? (u & 0xffff0000u) : (u << 16));
-    }
-};
-template <>
-struct WtVec<float> {
-    using V = float4;
-    static constexpr int E = 4;
-    static __device__ __forceinline__ V zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-    static __device__ __forceinline__ float get(const V& v, int h) {
-        const float d[4] = {v.x, v.y, v.z, v.w};
-        return d[h];
-    }
+struct WtileArgs {
+    const float* x;
+    const void* w;        // uint16_t bfloat16 bits or float, [N][K]
+    const float* bias;    // b[N] added after the fold, or null
+    float* y;
+    int64_t M, N, K;
+    int J;                // ceil(K / kChunk)
+    int tiles_m, tiles_n;
+    int reverse;          // 1: reversed workgroup-to-tile mapping
 };
 
-constexpr int kT = kWtileRows;        // tile rows (x) = tile rows (W)
-constexpr int kPad = kWtileRows + 4;  // LDS row of one k: 64 values and 4 of padding
-constexpr int kKT = kWtileK;          // k per slab
+constexpr int kDepth = 2;             // slabs of a wave's LDS ring: one computed, one in flight
+constexpr int kGroupM = 8;            // m tiles that share an n tile before the next n tile (large M)
+constexpr int kWtileLds = 160 * 1024;
+
+// LDS bytes of one slab of a wave: x then W, each padded to whole 1 KB DMA instructions.
+template <int BM, int BN, int KT, typename WT>
+struct Slab {
+    static constexpr int PX = KT / 4;                         // 16-byte pieces of an x row
+    static constexpr int PW = KT * (int)sizeof(WT) / 16;      // ... of a W row
+    static constexpr int XI = (BM * PX + 63) / 64;            // DMA instructions for x
+    static constexpr int WI = (BN * PW + 63) / 64;            // ... for W
+    static constexpr int WOFF = XI * 1024;
+    static constexpr int BYTES = (XI + WI) * 1024;
+};
+
+__device__ __forceinline__ uint32_t lds_addr32(const void* p) {
+    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)p);
+}
+
+// One or two 16-byte global -> LDS DMA instructions (lane l writes LDS [base + 16 l, +16), the
+// second 1 KB further on).  M0 is saved and restored, and never read in the cycle after a write.
+__device__ __forceinline__ void dma_1(const void* sbase, uint32_t v0, uint32_t lds_base) {
+    uint32_t saved;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %3\n\t"
+        "s_mov_b32 m0, %0\n\t"
+        : "=&s"(saved)
+        : "v"(v0), "s"(lds_base), "s"(sbase)
+        : "memory");
+}
+__device__ __forceinline__ void dma_2(const void* sbase, uint32_t v0, uint32_t v1, uint32_t lds_base) {
+    uint32_t saved;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %3\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %4\n\t"
+        "s_add_u32 m0, m0, 0x400\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %4\n\t"
+        "s_mov_b32 m0, %0\n\t"
+        : "=&s"(saved)
+        : "v"(v0), "v"(v1), "s"(lds_base), "s"(sbase)
+        : "memory", "scc");
+}
+template <int N>
+__device__ __forceinline__ void dma_n(const void* sbase, const uint32_t (&v)[N], uint32_t lds_base) {
+#pragma unroll
+    for (int u = 0; u + 1 < N; u += 2) dma_2(sbase, v[u], v[u + 1], lds_base + 1024u * u);
+    if constexpr (N % 2) dma_1(sbase, v[N - 1], lds_base + 1024u * (N - 1));
+}
+
+// Every DMA of this wave has landed (the only vector memory operations in flight are its DMA).
+__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// Barrier that leaves the DMA in flight (a wave's LDS operations are waited for).
+__device__ __forceinline__ void wg_barrier() {
+    lds_wait();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The two bfloat16 of a packed dword (even k in the low half), widened exactly.  The odd k's value is
+// placed in the even register of a pair and the even k's in the odd one: x arrives by 16-byte LDS reads,
+// whose k-th register has the parity of k, so an FMA's x and W never share a register
+// parity (two waves per SIMD then issue at the full rate: 64 x 56 tiles 185 -> 180 us at M = 64
+// on 28672 x 4096, 64 x 64 tiles 10.77 -> 10.28 ms on 8192 x 28672 at M = 2048).
+__device__ __forceinline__ void widen2(uint32_t d, float& even_k, float& odd_k) {
+    uint64_t pair = ((uint64_t)(d << 16) << 32) | (d & 0xffff0000u);
+    asm("" : "+v"(pair));
+    even_k = __uint_as_float((uint32_t)(pair >> 32));
+    odd_k = __uint_as_float((uint32_t)pair);
+}
 
 }  // namespace
 
-template <int KS, typename WT>
-__global__ void __launch_bounds__(64 * KS) wtile_kernel(const float* __restrict__ x, const WT* __restrict__ w,
-                                                        const float* __restrict__ bias, float* __restrict__ y,
-                                                        int64_t M, int64_t N, int64_t K, int reverse) {
-    using WV = WtVec<WT>;
-    constexpr int NSL = kChunk / kKT;             // slabs per segment
-    constexpr int WPR = kKT / WV::E;              // weight vectors per slab row
-    constexpr int XPT = kT * kKT / 4 / 64;        // float4 x loads per lane per slab
-    constexpr int WPT = kT * WPR / 64;            // weight vector loads per lane per slab
-    static_assert(XPT * 64 * 4 == kT * kKT && WPT * 64 == kT * WPR && WPR >= 1, "slab split");
-    static_assert(NSL % 2 == 0, "slabs of a segment alternate between the two buffers");
-    __shared__ __attribute__((aligned(16))) float xs[KS][2][kKT][kPad];
-    __shared__ __attribute__((aligned(16))) float ws[KS][2][kKT][kPad];
-    __shared__ __attribute__((aligned(16))) float4 tots[16][64];   // running totals, lane-major
+// LM: lanes along m; TM x TN: chains per lane; KT: k per slab; NWMAX: waves per workgroup at most;
+// WPE: waves per SIMD the registers are held to; KB: k per operand read (4 or 8); AL: DMA staging.
+template <int LM, int TM, int TN, int KT, int NWMAX, int WPE, int KB, typename WT, bool AL>
+__global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
+    constexpr int LN = 64 / LM, BM = LM * TM, BN = LN * TN;
+    using SL = Slab<BM, BN, KT, WT>;
+    constexpr int PX = SL::PX, PW = SL::PW, XI = SL::XI, WI = SL::WI;
+    constexpr int SLOT = SL::BYTES, RING = kDepth * SLOT;
+    constexpr bool BF = sizeof(WT) == 2;
+    constexpr int NSL = kChunk / KT;                // slabs per segment
+    constexpr int NB = KT / KB;                     // operand reads per slab
+    constexpr int NA = TM * TN;                     // chains per lane
+    // chains per lane that a fold pass moves through a slot
+    constexpr int QC = NA * 256 <= SLOT ? NA
+                       : (NA % 2 == 0 && NA / 2 * 256 <= SLOT) ? NA / 2
+                       : (NA % 3 == 0 && NA / 3 * 256 <= SLOT) ? NA / 3
+                       : (NA % 4 == 0 && NA / 4 * 256 <= SLOT) ? NA / 4 : NA / 8;
+    static_assert(QC >= 1 && NA % QC == 0 && QC * 256 <= SLOT, "fold pass");
+    static_assert(KT % KB == 0 && KB % 4 == 0 && kChunk % KT == 0 && kDepth == 2, "slab split");
+    extern __shared__ __attribute__((aligned(16))) uint8_t wt_lds[];
 
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int mi = lane & 7, ni = lane >> 3;
-    const int64_t tiles_n = (N + kT - 1) / kT;
-    const int64_t b = reverse ? (int64_t)(gridDim.x - 1 - blockIdx.x) : (int64_t)blockIdx.x;
-    const int64_t m0 = (b / tiles_n) * kT, n0 = (b % tiles_n) * kT;
-    const int J = (int)((K + kChunk - 1) / kChunk);
-    const int rounds = (J + KS - 1) / KS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NT = blockDim.x, NW = NT >> 6;
+    const int mi = lane % LM, ni = lane / LM;
+    const int64_t M = a.M, N = a.N, K = a.K;
+    const int J = a.J;
 
-    // two register sets: slab s of this wave (its slabs numbered across rounds) lives in set
-    // s % 2, loaded three slabs before it is computed and stored to LDS one slab before
-    float4 xr[2][XPT];
-    typename WV::V wr[2][WPT];
-    // this wave's slab s into register set R.  Every lane loads, from an address clamped into
-    // x and W: rows past M or N then hold copies of the last row (their outputs are never
-    // stored) and k past K or past the last segment copies of the first (never multiplied:
-    // a short slab runs only its valid k).  Unconditional loads let the compiler's waits count
-    // exactly the slabs still in flight.
-    auto load_slab = [&](auto R, int s) {
-        const int t = s / NSL, sl = s % NSL;
-        const int64_t j = (int64_t)t * KS + g;
-        const int64_t k0 = j * kChunk + (int64_t)sl * kKT;
+    // workgroup -> tile.  Workgroups b, b + 8, b + 16, ... run on one XCD and take one contiguous range of the
+    // tiles, in the order: the m tiles of a group of at most kGroupM for one n tile, then the next n tile, then
+    // the next group.  So an XCD's L2 holds what its tiles share, and every XCD has as many (same box, against
+    // tiles dealt round the XCDs one by one: 28672 x 4096 at M = 16 / 333 82 / 960 -> 75 / 931 us, 8192 x 28672
+    // at M = 2048 11.03 -> 10.76 ms).
+    int tm, tn;
+    {
+        const uint32_t b0 = a.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+        const uint32_t total = (uint32_t)a.tiles_m * (uint32_t)a.tiles_n;
+        const uint32_t i = (b0 & 7) * (gridDim.x >> 3) + (b0 >> 3);
+        if (i >= total) return;                                     // padding workgroup: no tile
+        const uint32_t gsz = min((uint32_t)kGroupM, (uint32_t)a.tiles_m);
+        const uint32_t per = gsz * (uint32_t)a.tiles_n;             // tiles of a whole m group
+        const uint32_t gm = i / per, j = i % per;
+        const uint32_t gs = min(gsz, (uint32_t)a.tiles_m - gm * gsz);
+        tm = __builtin_amdgcn_readfirstlane((int)(gm * gsz + j % gs));
+        tn = __builtin_amdgcn_readfirstlane((int)(j / gs));
+    }
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    uint8_t* ring = wt_lds + g * RING;
+    const uint32_t ring_base = lds_addr32(ring);
+    float* tots = reinterpret_cast<float*>(wt_lds + NW * RING);     // [NA][64], when there are several rounds
+
+    // swizzle of a row's pieces: eight rows in a row reach eight different 16-byte bank groups
+    auto fx = [](int row) { return PX >= 8 ? (row & 7) : ((row * PX / 8) & (PX - 1)); };
+    auto fw = [](int row) { return PW >= 8 ? (row & 7) : ((row * PW / 8) & (PW - 1)); };
+    // staging roles: instruction u of this lane brings 16-byte position 64 u + lane of the slab image, which
+    // holds piece (position % P) ^ f(row) of row position / P (rows past M or N: the last one again, never stored)
+    int kx[XI], kw[WI];                 // first k of the piece within the slab
+    uint32_t vx[XI], vw[WI];            // byte offset of row and piece from the tile's first row
 #pragma unroll
-        for (int u = 0; u < XPT; ++u) {
-            const int idx = lane + 64 * u;               // over 64 rows x kKT/4 float4
-            const int row = idx / (kKT / 4), kq = idx % (kKT / 4);
-            const int64_t gm = m0 + row, gk = k0 + 4 * kq;
-            const bool kok = j < J && gk + 4 <= K;
-            xr[R][u] = *reinterpret_cast<const float4*>(x + (gm < M ? gm : M - 1) * K + (kok ? gk : 0));
-        }
+    for (int u = 0; u < XI; ++u) {
+        const int p = 64 * u + lane, row = min(p / PX, BM - 1);
+        kx[u] = 4 * ((p % PX) ^ fx(p / PX));
+        vx[u] = (uint32_t)(min((int64_t)row, M - 1 - m0) * K * 4) + 4u * kx[u];
+    }
 #pragma unroll
-        for (int u = 0; u < WPT; ++u) {
-            const int idx = lane + 64 * u;               // over 64 rows x WPR vectors
-            const int row = idx / WPR, kh = idx % WPR;
-            const int64_t gn = n0 + row, gk = k0 + WV::E * kh;
-            const bool kok = j < J && gk + WV::E <= K;
-            // (a normal load: a slab reads 16 or 32 bytes of each 128-byte line of a row and the
-            // next slabs the rest, which a non-temporal load would not find in the cache)
-            wr[R][u] = *reinterpret_cast<const typename WV::V*>(w + (gn < N ? gn : N - 1) * K + (kok ? gk : 0));
+    for (int u = 0; u < WI; ++u) {
+        const int p = 64 * u + lane, row = min(p / PW, BN - 1);
+        kw[u] = (16 / (int)sizeof(WT)) * ((p % PW) ^ fw(p / PW));
+        vw[u] = (uint32_t)(min((int64_t)row, N - 1 - n0) * K * (int)sizeof(WT)) + (uint32_t)sizeof(WT) * kw[u];
+    }
+    const char* xb = reinterpret_cast<const char*>(a.x + m0 * K);
+    const char* wb = reinterpret_cast<const char*>(a.w) + n0 * K * (int)sizeof(WT);
+
+    const int last_len = (int)(K - (int64_t)(J - 1) * kChunk);
+    const int last_slabs = (last_len + KT - 1) / KT;
+    const int nseg = g < J ? (J - 1 - g) / NW + 1 : 0;             // this wave's segments, and their slabs
+    const bool has_last = nseg > 0 && g + (nseg - 1) * NW == J - 1;
+    const int S = nseg * NSL - (has_last ? NSL - last_slabs : 0);
+    auto slab_k = [&](int s) { return (int64_t)(g + s / NSL * NW) * kChunk + s % NSL * KT; };
+
+    // AL: slab s by DMA into slot s % 2.  Pieces past K (a short last slab) repeat the row's first piece of
+    // the slab and are never multiplied.
+    auto issue = [&](int s) {
+        const int64_t k0 = slab_k(s);
+        const uint32_t slot = ring_base + (uint32_t)(s % kDepth * SLOT);
+        const char* sx = xb + k0 * 4;
+        const char* sw = wb + k0 * (int)sizeof(WT);
+        if (k0 + KT <= K) {
+            dma_n(sw, vw, slot + SL::WOFF);
+            dma_n(sx, vx, slot);
+        } else {
+            const int kl = (int)(K - k0);
+            uint32_t tx[XI], tw[WI];
+#pragma unroll
+            for (int u = 0; u < XI; ++u) tx[u] = kx[u] < kl ? vx[u] : vx[u] - 4u * kx[u];
+#pragma unroll
+            for (int u = 0; u < WI; ++u) tw[u] = kw[u] < kl ? vw[u] : vw[u] - (uint32_t)sizeof(WT) * kw[u];
+            dma_n(sw, tw, slot + SL::WOFF);
+            dma_n(sx, tx, slot);
         }
     };
-    // register set R into this wave's LDS buffer R, transposed to [k][row]
-    auto store_slab = [&](auto R) {
-        constexpr int buf = decltype(R)::value;
+    // !AL: slab s into registers (any alignment; k past K as x = +0, w = -0), and from there into its slot
+    uint4 rx[AL ? 1 : XI], rw[AL ? 1 : WI];
+    auto load_regs = [&](int s) {
+        const int64_t k0 = slab_k(s);
+        const char* sx = xb + k0 * 4;
+        const char* sw = wb + k0 * (int)sizeof(WT);
+        constexpr int EW = 16 / (int)sizeof(WT);
+        if (k0 + KT <= K) {
 #pragma unroll
-        for (int u = 0; u < XPT; ++u) {
-            const int idx = lane + 64 * u;
-            const int row = idx / (kKT / 4), kq = idx % (kKT / 4);
-            xs[g][buf][4 * kq + 0][row] = xr[buf][u].x;
-            xs[g][buf][4 * kq + 1][row] = xr[buf][u].y;
-            xs[g][buf][4 * kq + 2][row] = xr[buf][u].z;
-            xs[g][buf][4 * kq + 3][row] = xr[buf][u].w;
+            for (int u = 0; u < XI; ++u) __builtin_memcpy(&rx[AL ? 0 : u], sx + vx[u], 16);
+#pragma unroll
+            for (int u = 0; u < WI; ++u) __builtin_memcpy(&rw[AL ? 0 : u], sw + vw[u], 16);
+        } else {
+            const int kl = (int)(K - k0);
+#pragma unroll
+            for (int u = 0; u < XI; ++u) {
+                uint32_t e[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t v = 0u;                                            // +0
+                    if (kx[u] + i < kl) __builtin_memcpy(&v, sx + vx[u] + 4 * i, 4);
+                    e[i] = v;
+                }
+                rx[AL ? 0 : u] = make_uint4(e[0], e[1], e[2], e[3]);
+            }
+#pragma unroll
+            for (int u = 0; u < WI; ++u) {
+                uint32_t e[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int i = 0; i < EW; ++i) {
+                    if constexpr (BF) {
+                        uint16_t v = 0x8000u;                                   // -0
+                        if (kw[u] + i < kl) __builtin_memcpy(&v, sw + vw[u] + 2 * i, 2);
+                        e[i / 2] |= (uint32_t)v << (16 * (i & 1));
+                    } else {
+                        uint32_t v = 0x80000000u;                               // -0
+                        if (kw[u] + i < kl) __builtin_memcpy(&v, sw + vw[u] + 4 * i, 4);
+                        e[i] = v;
+                    }
+                }
+                rw[AL ? 0 : u] = make_uint4(e[0], e[1], e[2], e[3]);
+            }
         }
+    };
+    int arrived = 0;                    // slabs made readable so far
+    // make slab s readable (in order, once each)
+    auto arrive = [&](int s) {
+        if constexpr (AL) {
+            dma_wait();
+        } else {
+            if (s < arrived || s >= S) return;
+            uint4* slot = reinterpret_cast<uint4*>(ring + s % kDepth * SLOT);
 #pragma unroll
-        for (int u = 0; u < WPT; ++u) {
-            const int idx = lane + 64 * u;
-            const int row = idx / WPR, kh = idx % WPR;
+            for (int u = 0; u < XI; ++u) slot[64 * u + lane] = rx[AL ? 0 : u];
 #pragma unroll
-            for (int h = 0; h < WV::E; ++h) ws[g][buf][WV::E * kh + h][row] = WV::get(wr[buf][u], h);
+            for (int u = 0; u < WI; ++u) slot[SL::WOFF / 16 + 64 * u + lane] = rw[AL ? 0 : u];
+            if (s + 1 < S) load_regs(s + 1);
+            arrived = s + 1;
         }
     };
 
-    float acc[64];
-    // the operands of one k: x rows {4mi .. 4mi+3, 32+4mi ..} and W rows {4ni .., 32+4ni ..}
+    float acc[TM][TN];
+    using WV = typename std::conditional<BF, uint2, float4>::type;
     struct Ops {
-        float4 x0, x1, w0, w1;
+        float4 x[KB / 4][TM];
+        WV w[KB / 4][TN];
     };
-    auto read_k = [&](int buf, int kk) {
+    // four k of this lane's rows: 16 bytes of x, 8 bytes of BF16 W or 16 of FP32 W
+    auto read4 = [&](const uint8_t* slot, int q, float4 (&ox)[TM], WV (&ow)[TN]) {
+        // rows r LM + mi share the swizzle of row mi where LM rows are whole swizzle periods
+        constexpr bool wper = PW >= 8 ? LN % 8 == 0 : LN * PW >= 8 && LN * PW / 8 % PW == 0;
+        constexpr bool xper = PX >= 8 ? LM % 8 == 0 : LM * PX >= 8 && LM * PX / 8 % PX == 0;
+#pragma unroll
+        for (int c = 0; c < TN; ++c) {
+            const int f = wper ? fw(ni) : fw(c * LN + ni);
+            const uint8_t* p = slot + SL::WOFF + ni * (KT * (int)sizeof(WT)) + c * (LN * KT * (int)sizeof(WT));
+            if constexpr (BF) ow[c] = *reinterpret_cast<const uint2*>(p + 16 * ((q >> 1) ^ f) + 8 * (q & 1));
+            else ow[c] = *reinterpret_cast<const float4*>(p + 16 * (q ^ f));
+        }
+#pragma unroll
+        for (int r = 0; r < TM; ++r) {
+            const int f = xper ? fx(mi) : fx(r * LM + mi);
+            ox[r] = *reinterpret_cast<const float4*>(slot + mi * (KT * 4) + 16 * (q ^ f) + r * (LM * KT * 4));
+        }
+    };
+    auto fma4 = [&](const float4 (&ox)[TM], const WV (&ow)[TN]) {
+#pragma unroll
+        for (int kp = 0; kp < 2; ++kp) {
+            float wv[2][TN];
+#pragma unroll
+            for (int c = 0; c < TN; ++c) {
+                if constexpr (BF) {
+                    widen2(kp == 0 ? ow[c].x : ow[c].y, wv[0][c], wv[1][c]);
+                } else {
+                    wv[0][c] = kp == 0 ? ow[c].x : ow[c].z;
+                    wv[1][c] = kp == 0 ? ow[c].y : ow[c].w;
+                }
+            }
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+                for (int r = 0; r < TM; ++r) {
+                    const float xv = kp == 0 ? (kk == 0 ? ox[r].x : ox[r].y) : (kk == 0 ? ox[r].z : ox[r].w);
+#pragma unroll
+                    for (int c = 0; c < TN; ++c) acc[r][c] = __builtin_fmaf(xv, wv[kk][c], acc[r][c]);
+                }
+            }
+        }
+    };
+    auto read = [&](const uint8_t* slot, int b) {
         Ops o;
-        o.x0 = *reinterpret_cast<const float4*>(&xs[g][buf][kk][4 * mi]);
-        o.x1 = *reinterpret_cast<const float4*>(&xs[g][buf][kk][32 + 4 * mi]);
-        o.w0 = *reinterpret_cast<const float4*>(&ws[g][buf][kk][4 * ni]);
-        o.w1 = *reinterpret_cast<const float4*>(&ws[g][buf][kk][32 + 4 * ni]);
+#pragma unroll
+        for (int h = 0; h < KB / 4; ++h) read4(slot, b * (KB / 4) + h, o.x[h], o.w[h]);
         return o;
     };
-    // one k of the 8 x 8 chains: acc[8r + c] += x[row r] * w[row c]
     auto fma_ops = [&](const Ops& o) {
-        const float xa[8] = {o.x0.x, o.x0.y, o.x0.z, o.x0.w, o.x1.x, o.x1.y, o.x1.z, o.x1.w};
-        const float wa[8] = {o.w0.x, o.w0.y, o.w0.z, o.w0.w, o.w1.x, o.w1.y, o.w1.z, o.w1.w};
 #pragma unroll
-        for (int r = 0; r < 8; ++r)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[8 * r + c] = __builtin_fmaf(xa[r], wa[c], acc[8 * r + c]);
+        for (int h = 0; h < KB / 4; ++h) fma4(o.x[h], o.w[h]);
     };
-    auto fma_k = [&](int buf, int kk) { fma_ops(read_k(buf, kk)); };
 
-    using R0 = std::integral_constant<int, 0>;
-    using R1 = std::integral_constant<int, 1>;
-    load_slab(R0{}, 0);
-    store_slab(R0{});
-    load_slab(R1{}, 1);
-    load_slab(R0{}, 2);
-    // move slab s + 1 from registers to the other LDS buffer, load slab s + 3 into the
-    // registers it freed, then compute slab s from buffer s % 2 with the next k's operands
-    // read while the current k's FMAs run (a wave's LDS operations run in order and only this
-    // wave touches its buffers, so no barrier is needed)
-    auto slab = [&](auto R, int s, int len, int sl) {
-        constexpr int buf = decltype(R)::value;
-        using RN = std::integral_constant<int, 1 - buf>;
-        store_slab(RN{});
-        load_slab(RN{}, s + 3);
-        const int kvalid = max(0, min(kKT, len - sl * kKT));
-        if (kvalid == kKT) {
-            Ops cur = read_k(buf, 0);
-#pragma unroll
-            for (int kk = 0; kk < kKT; ++kk) {
-                Ops nxt;
-                if (kk + 1 < kKT) nxt = read_k(buf, kk + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                fma_ops(cur);
-                __builtin_amdgcn_sched_barrier(0);
-                if (kk + 1 < kKT) cur = nxt;
-            }
-        } else {
-            for (int kk = 0; kk < kvalid; ++kk) fma_k(buf, kk);
-        }
-    };
+    if (S > 0) {
+        if constexpr (AL) issue(0);
+        else load_regs(0);
+    }
+    Ops cur;
+    int s = 0;                                             // this wave's next slab
+    const int rounds = (J + NW - 1) / NW;
     for (int t = 0; t < rounds; ++t) {
-        const int64_t j = (int64_t)t * KS + g;
+        const int j = t * NW + g;
 #pragma unroll
-        for (int i = 0; i < 64; ++i) acc[i] = 0.0f;
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int c = 0; c < TN; ++c) acc[r][c] = 0.0f;
         if (j < J) {
-            const int len = (int)min((int64_t)kChunk, K - j * kChunk);   // this segment's length
-            for (int sl = 0; sl < NSL; sl += 2) {
-                slab(R0{}, t * NSL + sl, len, sl);
-                slab(R1{}, t * NSL + sl + 1, len, sl + 1);
+            const int len = j == J - 1 ? last_len : kChunk;
+            const int nfull = len / KT;
+            if (nfull > 0) {
+                arrive(s);
+                cur = read(ring + s % kDepth * SLOT, 0);
             }
+            for (int sl = 0; sl < nfull; ++sl, ++s) {
+                const uint8_t* slot = ring + s % kDepth * SLOT;
+                // the other slot's reads are done: fill it with the next slab while this one is computed
+                if constexpr (AL) {
+                    lds_wait();
+                    if (s + 1 < S) issue(s + 1);
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    // the next operands are read while the current ones are multiplied (after the wave's
+                    // last slab: bytes that are never used)
+                    Ops nxt;
+                    if (b + 1 < NB) {
+                        nxt = read(slot, b + 1);
+                    } else {
+                        arrive(s + 1);
+                        nxt = read(ring + (s + 1) % kDepth * SLOT, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    fma_ops(cur);
+                    __builtin_amdgcn_sched_barrier(0);
+                    cur = nxt;
+                }
+            }
+            if (nfull * KT < len) {                        // the short last slab of K
+                arrive(s);
+                const uint8_t* slot = ring + s % kDepth * SLOT;
+                const int nq = (len - nfull * KT + 3) / 4;
+                for (int q = 0; q < nq; ++q) {
+                    float4 ox[TM];
+                    WV ow[TN];
+                    read4(slot, q, ox, ow);
+                    fma4(ox, ow);
+                }
+                ++s;
+            }
+            lds_wait();
         }
-        // the round's partials join the totals wave by wave, in ascending segment order
-        for (int gg = 0; gg < KS; ++gg) {
-            __syncthreads();
-            if (g == gg && j < J) {
-                if (j > 0) {
+        // fold: partials through the slot of the last computed slab (the other one may be filling), QC
+        // chains per lane at a time
+        const int nact = min(NW, J - t * NW);
+        const bool last = t == rounds - 1;
+        float* part = reinterpret_cast<float*>(ring + (s + kDepth - 1) % kDepth * SLOT);
+        const float* pfull =
+            reinterpret_cast<const float*>(wt_lds + ((t + 1) * NSL + kDepth - 1) % kDepth * SLOT);
+        const float* plast =
+            reinterpret_cast<const float*>(wt_lds + (t * NSL + last_slabs + kDepth - 1) % kDepth * SLOT);
+        const int nfold = last ? nact - 1 : nact;          // waves with whole segments this round
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        const float4 tv = tots[q][lane];
-                        acc[4 * q + 0] = tv.x + acc[4 * q + 0];
-                        acc[4 * q + 1] = tv.y + acc[4 * q + 1];
-                        acc[4 * q + 2] = tv.z + acc[4 * q + 2];
-                        acc[4 * q + 3] = tv.w + acc[4 * q + 3];
-                    }
-                }
-                if (j + 1 < J) {
+        for (int ch = 0; ch < NA / QC; ++ch) {
+            if (j < J) {
 #pragma unroll
-                    for (int q = 0; q < 16; ++q)
-                        tots[q][lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                for (int q = 0; q < QC; ++q) part[64 * q + lane] = acc[(ch * QC + q) / TN][(ch * QC + q) % TN];
+            }
+            wg_barrier();
+            for (int o = tid; o < 64 * QC; o += NT) {
+                float v;
+                int w = 0;
+                if (t > 0) {
+                    v = tots[ch * QC * 64 + o];
                 } else {
-                    // the last segment: the totals are the outputs
+                    v = nfold > 0 ? pfull[o] : plast[o];   // the first partial starts the sum
+                    w = 1;
+                }
+                for (; w + 4 <= nfold; w += 4) {
+                    float pv[4];
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const int64_t gm = m0 + (r < 4 ? 4 * mi + r : 32 + 4 * mi + (r - 4));
-                        if (gm >= M) continue;
+                    for (int u = 0; u < 4; ++u) pv[u] = pfull[(w + u) * (RING / 4) + o];
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) {
-                            const int64_t gn = n0 + (c < 4 ? 4 * ni + c : 32 + 4 * ni + (c - 4));
-                            if (gn < N) y[gm * N + gn] = bias ? acc[8 * r + c] + bias[gn] : acc[8 * r + c];
-                        }
-                    }
+                    for (int u = 0; u < 4; ++u) v = v + pv[u];
+                }
+                for (; w < nfold; ++w) v = v + pfull[w * (RING / 4) + o];
+                if (w < nact) v = v + plast[w * (RING / 4) + o];
+                if (last) {
+                    const int q = ch * QC + o / 64, ln = o % 64;
+                    const int64_t gm = m0 + (q / TN) * LM + ln % LM, gn = n0 + (q % TN) * LN + ln / LM;
+                    if (gm < M && gn < N) a.y[gm * N + gn] = a.bias ? v + a.bias[gn] : v;
+                } else {
+                    tots[ch * QC * 64 + o] = v;
                 }
             }
+            wg_barrier();
         }
     }
 }
 
 namespace {
 
+// The builds: tile shape (LM, TM, TN, KT, NWMAX, WPE, KB) and `rate`, the multiply-adds per ns one CU
+// sustains on it with at least eight waves (measured on an MI355X: the slope between 512 and 1024
+// tiles at K = 4096).  Larger tiles run faster per multiply-add; smaller ones fill the CUs of a narrow layer.
+#define RG_WTILE_BF16(B)                                                            \
+    B(8, 8, 8, 16, 8, 2, 4, 161) /* 64 x 64 */ B(8, 8, 7, 16, 8, 2, 4, 158) /* 64 x 56 */ \
+    B(8, 8, 6, 16, 8, 2, 4, 152) /* 64 x 48 */ B(8, 8, 5, 16, 8, 2, 4, 151) /* 64 x 40 */ \
+    B(8, 7, 8, 16, 8, 2, 4, 156) /* 56 x 64 */ B(8, 6, 8, 16, 8, 2, 4, 148) /* 48 x 64 */ \
+    B(8, 6, 6, 16, 8, 2, 4, 144) /* 48 x 48 */ B(8, 5, 8, 16, 8, 2, 4, 131) /* 40 x 64 */ \
+    B(4, 8, 4, 32, 8, 2, 4, 145) /* 32 x 64 */ B(8, 4, 6, 32, 8, 2, 4, 134) /* 32 x 48 */ \
+    B(8, 4, 4, 32, 16, 4, 4, 126) /* 32 x 32 */ B(4, 6, 4, 32, 8, 2, 4, 134) /* 24 x 64 */ \
+    B(8, 3, 6, 32, 8, 2, 4, 115) /* 24 x 48 */ B(8, 3, 4, 32, 16, 4, 4, 107) /* 24 x 32 */ \
+    B(4, 4, 4, 32, 16, 4, 4, 120) /* 16 x 64 */ B(4, 4, 2, 32, 16, 4, 4, 111) /* 16 x 32 */ \
+    B(8, 2, 3, 32, 16, 4, 8, 94) /* 16 x 24 */ B(4, 4, 1, 32, 16, 4, 8, 94) /* 16 x 16 */
+#define RG_WTILE_F32(B)                                                             \
+    B(8, 8, 8, 16, 8, 2, 4, 144) /* 64 x 64 */ B(8, 8, 6, 16, 8, 2, 4, 137) /* 64 x 48 */ \
+    B(8, 8, 4, 16, 8, 2, 4, 128) /* 64 x 32 */ B(8, 4, 6, 16, 8, 2, 4, 110) /* 32 x 48 */ \
+    B(8, 4, 4, 16, 8, 2, 4, 107) /* 32 x 32 */ B(4, 4, 2, 32, 16, 4, 4, 70) /* 16 x 32 */ \
+    B(8, 2, 3, 32, 16, 4, 4, 72) /* 16 x 24 */ \
+    B(4, 4, 1, 32, 16, 4, 8, 71) /* 16 x 16 */
+#define RG_WTILE_ANY(B)                                                             \
+    B(8, 6, 4, 16, 8, 2, 4, 110) /* 48 x 32 */ B(8, 4, 4, 16, 8, 2, 4, 100) /* 32 x 32 */ \
+    B(4, 4, 2, 16, 8, 2, 4, 70) /* 16 x 32 */ B(4, 4, 1, 16, 16, 4, 4, 60) /* 16 x 16 */ \
+    B(4, 2, 2, 16, 16, 4, 4, 40) /* 8 x 32 */ B(4, 2, 1, 16, 16, 4, 4, 40) /* 8 x 16 */
+
+struct WtileBuild {
+    int bm, bn, slab, nwmax, rate;
+    void (*kernel)(WtileArgs);
+};
+
+template <typename WT, bool AL>
+const WtileBuild* wtile_builds(int* count) {
+#define RG_B(LM, TM, TN, KT, NWMAX, WPE, KB, RATE)                                                                 \
+    {(LM) * (TM), 64 / (LM) * (TN), Slab<(LM) * (TM), 64 / (LM) * (TN), KT, WT>::BYTES, NWMAX, RATE,              \
+     wtile_kernel<LM, TM, TN, KT, NWMAX, WPE, KB, WT, AL>},
+    if constexpr (!AL) {
+        static const WtileBuild b[] = {RG_WTILE_ANY(RG_B)};
+        *count = (int)(sizeof b / sizeof b[0]);
+        return b;
+    } else if constexpr (sizeof(WT) == 2) {
+        static const WtileBuild b[] = {RG_WTILE_BF16(RG_B)};
+        *count = (int)(sizeof b / sizeof b[0]);
+        return b;
+    } else {
+        static const WtileBuild b[] = {RG_WTILE_F32(RG_B)};
+        *count = (int)(sizeof b / sizeof b[0]);
+        return b;
+    }
+#undef RG_B
+}
+
+int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
+    return (int64_t)nw * kDepth * b.slab + (J > nw ? (int64_t)b.bm * b.bn * 4 : 0);
+}
+
+// Waves of a workgroup: the fewest that give the fewest rounds of segments, within `most` and LDS.
+int wtile_waves(const WtileBuild& b, int64_t J, int most) {
+    int nw = (int)(J < most ? J : most);
+    while (nw > 1 && wtile_lds(b, J, nw) > kWtileLds) --nw;
+    const int64_t rounds = (J + nw - 1) / nw;
+    return (int)((J + rounds - 1) / rounds);
+}
+
+// Tile and waves for a shape: the least estimated time over the builds, a function of (M, N, K), the weight
+// type and the alignment.  A CU works off ceil(tiles / 256) tiles at the build's rate (a
+// share of it while fewer than eight waves are resident), with a fixed cost per tile for
+// its first slabs and folds (1.5 us), and never faster than HBM streams W (6.2 GB per ms).  With one tile per CU
+// the workgroup brings all the waves that fit, with several eight, and four where many tiles have 16 rows
+// (several workgroups share a CU then and one's folds hide behind the others: the 128256 x 4096 head
+// at M = 16 305 -> 286 us; 64-row tiles are faster on eight: 8192 x 28672 at M = 2048 10.61 -> 10.36 ms).
+template <typename WT, bool AL>
+bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
+    int nb = 0;
+    const WtileBuild* bs = wtile_builds<WT, AL>(&nb);
+    const int64_t J = (K + kChunk - 1) / kChunk;
+    double best = 0.0;
+    *build = nullptr;
+    for (int i = 0; i < nb; ++i) {
+        const WtileBuild& b = bs[i];
+        const double tiles = (double)((M + b.bm - 1) / b.bm) * (double)((N + b.bn - 1) / b.bn);
+        if (tiles > 2.0e9) continue;
+        const double percu = (double)(((int64_t)tiles + 255) / 256);
+        const int nw = wtile_waves(b, J, percu > 2.0 && b.bm <= 16 ? 4 : percu > 1.0 && b.nwmax > 8 ? 8 : b.nwmax);
+        double resident = (double)(kWtileLds / wtile_lds(b, J, nw));
+        if (resident * nw > b.nwmax) resident = b.nwmax / nw > 0 ? b.nwmax / nw : 1;
+        if (resident > percu) resident = percu;
+        double share = resident * nw / 8.0;
+        if (share > 1.0) share = 1.0;
+        double us = percu * (1.5 / resident + (double)b.bm * b.bn * (double)K / (b.rate * 1000.0 * share));
+        const double hbm = (double)N * (double)K * sizeof(WT) / 6.2e6;
+        if (us < hbm) us = hbm + 0.05 * us;
+        if (!*build || us < best) {
+            best = us;
+            *build = &b;
+            *waves = nw;
+        }
+    }
+    return *build != nullptr;
+}
+
 template <typename WT>
 hipError_t launch_wtile_t(const float* x, const WT* w, const float* bias, float* y, int64_t M, int64_t N,
                           int64_t K, int waves, int reverse, hipStream_t stream) {
-    const int64_t tiles = ((M + kT - 1) / kT) * ((N + kT - 1) / kT);
-    if (tiles < 1 || tiles > 0x7fffffff || (waves != 4 && waves != 8)) return hipErrorInvalidValue;
-    if (waves == 4)
-        hipLaunchKernelGGL((wtile_kernel<4, WT>), dim3((unsigned)tiles), dim3(256), 0, stream, x, w, bias, y, M, N, K,
-                           reverse);
-    else
-        hipLaunchKernelGGL((wtile_kernel<8, WT>), dim3((unsigned)tiles), dim3(512), 0, stream, x, w, bias, y, M, N, K,
-                           reverse);
+    if (K > kWtileMaxK || (waves != 0 && waves != 4 && waves != 8)) return hipErrorInvalidValue;
+    const bool aligned = (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && K % (16 / (int)sizeof(WT)) == 0;
+    const int64_t J = (K + kChunk - 1) / kChunk;
+    const WtileBuild* b = nullptr;
+    int nw = waves;
+    if (waves != 0) {
+        if (!aligned) return hipErrorInvalidValue;
+        int nb = 0;
+        b = wtile_builds<WT, true>(&nb);                   // the 64 x 64 tile
+    } else if (!(aligned ? wtile_choose<WT, true>(M, N, K, &b, &nw) : wtile_choose<WT, false>(M, N, K, &b, &nw))) {
+        return hipErrorInvalidValue;
+    }
+    const int64_t tm = (M + b->bm - 1) / b->bm, tn = (N + b->bn - 1) / b->bn;
+    if (tm > 0x7fffffff || tn > 0x7fffffff || tm * tn > 0x7ffffff0) return hipErrorInvalidValue;
+    const int64_t grid = (tm * tn + 7) / 8 * 8;            // the same number of workgroups on every XCD
+    const WtileArgs a{x, w, bias, y, M, N, K, (int)J, (int)tm, (int)tn, reverse};
+    hipLaunchKernelGGL(b->kernel, dim3((unsigned)grid), dim3(64 * nw), (size_t)wtile_lds(*b, J, nw), stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
-
-static_assert(wtile_lds_bytes(4) == sizeof(float) * (4 * 2 * kKT * kPad * 2 + 16 * 64 * 4), "LDS size");
 
 hipError_t launch_wtile(const float* x, const uint16_t* w, const float* bias, float* y, int64_t M, int64_t N,
                         int64_t K, int waves, int reverse, hipStream_t stream) {

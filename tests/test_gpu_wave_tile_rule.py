@@ -1,0 +1,95 @@
+"""The wave-tile builds that default launches choose among (rg_linear for M > 8, FP32 weights at
+M > 4, and any K or alignment the 16-byte kernels do not take) against the oracle, bit for bit.
+
+Every shape below makes the rule choose another build: the tiles from 8 x 16 to 64 x 64, with
+ragged last tiles in M and N, a short last segment and slab, one and several rounds of
+segments, K below one slab, odd K (rows of x and W at every alignment), the bias and pointers off
+their 16-byte alignment.  No tolerance: the order fixes every bit.
+"""
+import numpy as np
+import pytest
+
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+ALIGNED = [(9, 32, 264), (17, 2057, 1288), (17, 12458, 264), (33, 19492, 264), (17, 24804, 264), (33, 22129, 264),
+           (33, 27340, 264), (49, 14987, 264), (49, 20592, 264), (49, 24637, 264), (33, 29519, 520), (33, 22313, 520),
+           (129, 20954, 264), (49, 29065, 520), (100, 16597, 264), (100, 21828, 264), (100, 26152, 264),
+           (57, 29759, 520), (10, 70, 8), (333, 1000, 24), (65, 130, 4360)]
+ALIGNED_F32 = [(5, 33, 264), (9, 33, 260), (17, 2055, 1288), (17, 18553, 264), (17, 21688, 268), (17, 18609, 520),
+               (33, 24923, 264), (33, 20900, 520), (33, 27095, 520), (65, 130, 4364)]
+ANY = [(1, 31, 1), (1, 28970, 263), (3, 1000, 1001), (9, 20555, 3), (17, 26667, 5), (100, 9427, 7), (100, 16491, 31),
+       (47, 300, 4099), (8, 77, 513)]
+
+
+def _inputs(M, N, K, f32, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((M, K), dtype=np.float32)
+    w = (0.02 * rng.standard_normal((N, K), dtype=np.float32)).astype(np.float32)
+    return x, w if f32 else (w.view(np.uint32) >> 16).astype(np.uint16)
+
+
+def _check(M, N, K, f32=False, bias=False, shift=0):
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    rg.rg_linear_set_launch(None)
+    gu.log(f"wave-tile rule M={M} N={N} K={K} f32={f32} bias={bias} shift={shift}")
+    x, w = _inputs(M, N, K, f32, M + N + K)
+    # `shift` elements between the allocation's start and the first row
+    xb = torch.zeros(M * K + shift, dtype=torch.float32, device=gu.dev())
+    wb = torch.zeros(N * K + shift, dtype=torch.float32 if f32 else torch.int16, device=gu.dev())
+    xd, wd = xb[shift:].view(M, K), wb[shift:].view(N, K)
+    xd.copy_(torch.from_numpy(x))
+    wd.copy_(torch.from_numpy(w if f32 else w.view(np.int16)))
+    y = torch.full((M, N), 7.0, dtype=torch.float32, device=gu.dev())
+    if bias:
+        b = np.random.default_rng(1).standard_normal(N, dtype=np.float32)
+        rg.rg_linear_bias(xd, wd, torch.from_numpy(b).to(gu.dev()), y)
+        want = oracle.linear_bias(x, w, b)
+    elif f32:
+        rg.rg_linear_f32w(xd, wd, y)
+        want = oracle.linear_f32w(x, w)
+    else:
+        rg.rg_linear(xd, wd, y)
+        want = oracle.linear_fast(x, w)
+    torch.cuda.synchronize()
+    gu.assert_bitwise(y.cpu().numpy(), want, f"({M},{N},{K})")
+
+
+@pytest.mark.parametrize("M,N,K", ALIGNED)
+def test_bf16_builds(M, N, K):
+    _check(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", ALIGNED_F32)
+def test_f32_builds(M, N, K):
+    _check(M, N, K, f32=True)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("M,N,K", ANY)
+def test_odd_k_builds(M, N, K, f32):
+    _check(M, N, K, f32=f32)
+
+
+@pytest.mark.parametrize("M,N,K,shift", [(5, 100, 1003, 0), (12, 300, 512, 1), (70, 500, 264, 3), (2, 40, 256, 1)])
+def test_bias_and_shifted_pointers(M, N, K, shift):
+    _check(M, N, K, bias=True, shift=shift)
+
+
+@pytest.mark.parametrize("K", [255, 270, 264])
+def test_negative_zero_sums_survive_the_padding(K):
+    # products that underflow to -0 from the first k on: every chain and every fold stays -0 only if the
+    # staged k past K multiply as fmaf(+0, -0, -0) = -0
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    M, N = 11, 50
+    x = np.full((M, K), 1e-30, dtype=np.float32)
+    w = np.full((N, K), 0xa000, dtype=np.uint16)     # about -1.1e-19: the product rounds to -0
+    want = oracle.linear_fast(x, w)
+    y = gu.run(*gu.to_dev(x, w))
+    torch.cuda.synchronize()
+    gu.assert_bitwise(y.cpu().numpy(), want, f"-0 sums K={K}")
