@@ -1,9 +1,8 @@
 // Fixed-order decode attention kernels for gfx950 (MI355X): the order
 // RG-ATTN-1 and its exponential EXP1, both defined in include/rg_attn.h.
 //
-// Four launches (three when the partials kernel takes the row maxima itself),
-// each deterministic by construction (no atomics, no order that depends on the
-// grid):
+// One launch for short caches, three (four for other head dims) otherwise, each
+// deterministic by construction (no order that depends on the grid):
 //   1. scores:   work item (b, g, j) = segment j (positions [256j, 256j + 256))
 //                of kv head g of sequence b; its keys are staged in LDS and
 //                thread l runs the dot product chain of position l for every
@@ -18,16 +17,18 @@
 //                ascending order; values and e staged in LDS).
 //   4. fold:     workgroup (b, h) folds the S_j and n_j[d] in ascending j and
 //                divides.
-// Kernels 1 and 3 are persistent: a workgroup (kernel 1; kernel 3 for head dims
-// other than 128 and 256) walks work items it, it + grid, ... in steps of one
-// 32 KB tile (for the usual head dims), or for kernel 3 with head dims 128 and
-// 256 a single wave walks them in 8 KB steps; either fetches the next step into
-// registers while it computes the current one from LDS.
+// The fused kernel runs 1 to 4 in one workgroup per (b, g).
+// Kernels 1, and 3 for other head dims, are persistent: a workgroup walks work items it,
+// it + grid, ... in steps of one 32 KB tile, fetching the next step into registers while it
+// computes the current one from LDS.  Kernel 3 for head dims 64, 128 and 256 and the fused kernel
+// stream rows wave by wave through LDS rings by DMA.
 // Arithmetic: binary32 fmaf / add / multiply / correctly rounded divide,
 // denormals kept, no contraction (the build uses -ffp-contract=off).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "rg_kernels.h"
 
@@ -60,6 +61,24 @@ __device__ __forceinline__ float exp1(float u) {
     p = __builtin_fmaf(p, r, 1.0f);
     p = __builtin_fmaf(p, r, 1.0f);
     return p * __uint_as_float((uint32_t)((int)k + 127) << 23);
+}
+
+// The same without branches (the discarded 2^k of u < -87 is any value).
+__device__ __forceinline__ float exp1_select(float u) {
+    const float k = __builtin_rintf(u * 0x1.715476p+0f);
+    float r = __builtin_fmaf(-k, 0x1.62e4p-1f, u);
+    r = __builtin_fmaf(-k, 0x1.7f7d1cp-20f, r);
+    float p = 0x1.a01a02p-13f;
+    p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
+    p = __builtin_fmaf(p, r, 0x1.111112p-7f);
+    p = __builtin_fmaf(p, r, 0x1.555556p-5f);
+    p = __builtin_fmaf(p, r, 0x1.555556p-3f);
+    p = __builtin_fmaf(p, r, 0.5f);
+    p = __builtin_fmaf(p, r, 1.0f);
+    p = __builtin_fmaf(p, r, 1.0f);
+    const float k0 = u >= -87.0f ? k : 0.0f;          // a k the conversion is defined for
+    const float e = p * __uint_as_float((uint32_t)((int)k0 + 127) << 23);
+    return u != u ? u : (u < -87.0f ? 0.0f : e);
 }
 
 __device__ __forceinline__ int clamp_len(const int32_t* lens, int64_t b, int64_t Lmax) {
@@ -485,271 +504,425 @@ __global__ void __launch_bounds__(256) attn_partials_kernel(AttnArgs a) {
     }
 }
 
-// 3'. the same partials with one wave per work item (head dims 128 and 256).
-// Lane p owns the value columns 2p, 2p + 1 (and 2p + 128, 2p + 129 for D = 256)
-// for all G query heads of the group, so a value pair is read from LDS and
-// widened once and feeds 2G fmaf chains.  The item's positions are taken in
-// steps of RS = 32 (D = 128) or 16 (D = 256) rows (8 KB); the wave loads the
-// next step's value rows and scores into registers while it computes the
-// current step, and stages them in its own LDS region (waves never wait for
-// each other).  e for a step is computed into LDS as [position][head].  The
-// chains run over the valid positions only (the same values as chains over the
-// +0-padded segment).  INMAX: the wave takes its item's row maxima from the
-// segment maxima itself (the largest one per head, exact), so the maximum kernel
-// is not launched; used when no wave has more than one item.  CS = 2: the value
-// columns of an item are split between two waves (columns [0, D/2) and [D/2, D)),
-// each running the full chains of its columns (the same order: a chain is one
-// column's sum over the positions), for grids that would otherwise hold about one
-// wave per SIMD; with D = 128 a lane then owns one column.
-template <int G, int D, bool INMAX, int CS>
-__global__ void __launch_bounds__(256) attn_partials_wave_kernel(AttnArgs a) {
-    static_assert(CS == 1 || CS == 2, "column split");
-    constexpr int DH = D / CS;                         // value columns of this wave
-    constexpr int RS = 4096 / DH;                      // rows per step (8 KB of bf16)
-    constexpr int PPL = DH >= 128 ? DH / 128 : 0;      // value pairs per lane (0: one column)
-    constexpr int GP = G <= 4 ? 4 : 8;                 // e row stride (floats)
-    constexpr int NVL = RS * DH / 8 / 64;              // 16-byte vectors per lane per step (8)
-    constexpr int NTL = (RS * G + 63) / 64;            // scores per lane per step
-    constexpr int NC = PPL > 0 ? PPL : 1;              // chain sets per head
-    __shared__ __attribute__((aligned(16))) uint16_t vs[4][RS * DH];
-    __shared__ __attribute__((aligned(16))) float es[4][RS * GP];
+// One 16-byte global -> LDS DMA per lane (lane l writes LDS [lds_base + 16 l, +16)).  M0 is saved and
+// restored and never read in the cycle after a write.
+__device__ __forceinline__ void attn_dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
+    uint32_t saved;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %3\n\t"
+        "s_mov_b32 m0, %0\n\t"
+        : "=&s"(saved)
+        : "v"(voff), "s"(lds_base), "s"(sbase)
+        : "memory");
+}
+template <int N>
+__device__ __forceinline__ void attn_vm_wait() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void attn_lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// The two bfloat16 of a dword, widened exactly; the odd element in the even register of a pair and the even
+// element in the odd one (the other operand's registers have the parity of the element, and an FMA whose operands
+// all have one parity holds up the SIMD's other wave).
+__device__ __forceinline__ void attn_widen2(uint32_t d, float& even, float& odd) {
+    uint64_t pair = ((uint64_t)(d << 16) << 32) | (d & 0xffff0000u);
+    asm volatile("" : "+v"(pair));                    // volatile: kept in order, so that few pairs are live at a time
+    even = __uint_as_float((uint32_t)(pair >> 32));
+    odd = __uint_as_float((uint32_t)pair);
+}
+
+// ---------------------------------------------------------------------------
+// Wave passes (head dims 64, 128 and 256).  Each wave streams its own rows by DMA through its own LDS ring
+// and meets no barrier inside a pass.
+// ---------------------------------------------------------------------------
+template <int GP, int D>
+struct KeySteps {
+    static constexpr int DC = D < 128 ? D : 128;                // columns whose q a lane holds at a time
+    static constexpr int NCK = D / DC;                          // passes over the keys
+    static constexpr int P = 64 / GP;                           // positions a wave's lanes hold at a time
+    static constexpr int CC = GP == 1 && DC == 128 ? 64 : DC;   // columns per step
+    static constexpr int NSUB = DC / CC;                        // steps per row group
+    // row groups per step (chains per lane, two where a step then stays within 8 KB: a lone chain waits for itself)
+    static constexpr int NCH = P * CC * 2 >= 8192 ? 1 : P * CC * 2 >= 2048 ? 2 : 4;
+    static constexpr int RS = P * NCH;                          // key rows per step
+    static constexpr int STEP = RS * CC * 2;                    // bytes: 4 or 8 KB
+    static constexpr int RING = STEP > 4096 ? 2 * STEP : 12288;
+    static constexpr int NS = RING / STEP;                      // steps in the ring
+    static constexpr int UNIT = 128;                            // positions per unit
+};
+template <int GP, int D, int CS, int RINGB = 12288>
+struct ValueSteps {
+    static constexpr int DH = D / CS;                           // value columns of a unit
+    static constexpr int RS = 4096 / (DH * 2);                  // value rows per 4 KB step
+    static constexpr int EC = GP >= 4 ? 128 : 256;              // positions whose e are in LDS at a time
+    static constexpr int RING = RINGB;
+};
+
+// Scores of units first, first + stride, ... (128 positions each) of kv head g of sequence b, `nu` of them.  Lane
+// (position p, head h) = (lane / GP, lane % GP) runs the whole dot product chain of its position and head
+// with its head's q in registers; key rows are XOR-swizzled in 16-byte pieces.  t goes to the workspace; returns the
+// lane's largest t (its head's; -inf if it has none).
+template <int GP, int D>
+__device__ __forceinline__ float key_pass(const AttnArgs& a, int b, int g, int G, int L, int first, int stride, int nu,
+                                          uint8_t* ring) {
+    using KS = KeySteps<GP, D>;
+    constexpr int CC = KS::CC, NCH = KS::NCH, P = KS::P, NSUB = KS::NSUB, NS = KS::NS, STEP = KS::STEP;
+    constexpr int NI = STEP / 1024;                   // DMA instructions per step
+    constexpr int SPU = KS::UNIT / KS::RS * NSUB;     // steps per unit
+    constexpr int PCK = CC / 8;                       // 16-byte pieces per row of a step
+    constexpr int LOGGP = GP == 1 ? 0 : GP == 2 ? 1 : GP == 4 ? 2 : 3;
+    static_assert(KS::RS <= KS::UNIT && PCK % 8 == 0 && KS::UNIT % KS::RS == 0, "key step");
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int items = (int)(a.B * a.Hkv * a.J);
-    const int tw = (int)gridDim.x * 4 / CS;            // waves in the grid per column half
-    const int gw = ((int)blockIdx.x * 4 + wave) / CS;
-    const int half = ((int)blockIdx.x * 4 + wave) % CS;   // 0 for CS = 1
-    uint16_t* vw = vs[wave];
-    float* ew = es[wave];
-
-    // the wave's items gw, gw + tw, ... that hold positions
-    auto next = [&](int it) {
-        while (it < items && item_of(a, it).rows <= 0) it += tw;
-        return it;
-    };
-    uint4 vr[NVL];
-    float tr[NTL];
-    // INMAX: the first 512 of the item's G * Jb segment maxima are loaded with its first
-    // step into smv and reduced before its exponentials; lane-local maxima of any further
-    // values (sequences longer than 512 / G segments) are taken at once into mr.  When G
-    // divides 64, lane l only ever holds values of head l % G, kept in mr[0].
-    float smv[INMAX ? 8 : 1];
-    float mr[G];
-    auto fetch = [&](const Item& w, int s) {
-        const int r0 = s * RS;
-        const int nrow = min(RS, w.rows - r0);          // >= 1
-        const uint16_t* vb = a.v + (((int64_t)w.b * a.Hkv + w.g) * a.Lmax + w.l0 + r0) * D + half * DH;
+    const uint32_t ring_base = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)ring);
+    const int64_t h0 = (int64_t)b * a.H + (int64_t)g * G;
+    float* tb = a.t + h0 * a.Lmax;
+    const int hq = lane & (GP - 1), pos = lane >> LOGGP;
+    const int hh = hq < G ? hq : G - 1;               // lanes past the group's heads repeat the last one
+    const int S = nu * SPU;
+    float mymax = -__builtin_inff();
+#pragma unroll 1
+    for (int ck = 0; ck < KS::NCK; ++ck) {
+        const char* kb = reinterpret_cast<const char*>(a.k + ((int64_t)b * a.Hkv + g) * a.Lmax * D + ck * KS::DC);
+        auto issue = [&](int s) {
+            const int u = s / SPU, r = s - u * SPU;
+            const int l0 = (first + stride * u) * KS::UNIT + r / NSUB * KS::RS;   // the step's first position
+            const int from = min(l0, L - 1), rmax = L - 1 - from;               // past L: the last row again
+            const char* sb = kb + (int64_t)from * (D * 2) + (r % NSUB) * (CC * 2);
+            const uint32_t slot = ring_base + (uint32_t)(s % NS * STEP);
 #pragma unroll
-        for (int u = 0; u < NVL; ++u) {
-            const int i = lane + 64 * u;                // vector i: row i / (DH / 8), column 8 (i % (DH / 8))
-            const int row = i / (DH / 8);
-            vr[u] = row < nrow ? ldnt(reinterpret_cast<const uint4*>(vb + (int64_t)row * D + 8 * (i % (DH / 8))))
-                               : make_uint4(0u, 0u, 0u, 0u);
+            for (int i = 0; i < NI; ++i) {
+                const int p = 64 * i + lane, row = p / PCK, pc = (p % PCK) ^ (row & 7);
+                attn_dma16(sb, (uint32_t)(min(row, rmax) * (D * 2) + 16 * pc), slot + 1024u * i);
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < NS - 1; ++s)
+            if (s < S) issue(s);
+        float q[KS::DC];
+        const float4* qp = reinterpret_cast<const float4*>(a.q + (h0 + hh) * D + ck * KS::DC);
+#pragma unroll
+        for (int i = 0; i < KS::DC / 4; ++i) {
+            const float4 v = qp[i];
+            q[4 * i] = v.x; q[4 * i + 1] = v.y; q[4 * i + 2] = v.z; q[4 * i + 3] = v.w;
         }
-        const int64_t tb = ((int64_t)w.b * a.H + (int64_t)w.g * G) * a.Lmax + w.l0 + r0;
+        float z[NCH];
+#pragma unroll 1
+        for (int s0 = 0; s0 < S; s0 += NSUB) {
+            const int u = s0 / SPU, r = s0 - u * SPU;
+            const int l0 = (first + stride * u) * KS::UNIT + r / NSUB * KS::RS + pos;   // this lane's first position
 #pragma unroll
-        for (int u = 0; u < NTL; ++u) {
-            const int q = lane + 64 * u;                // (position q / G, head q % G)
-            const int l = q / G, h = q - l * G;
-            tr[u] = (q < RS * G && l < nrow) ? a.t[tb + (int64_t)h * a.Lmax + l] : 0.0f;
-        }
-        if (s == 0) {
-            if constexpr (INMAX) {
-                const int jb = (w.L + kAttnSeg - 1) / kAttnSeg;
-                const float* smb = a.segmax + ((int64_t)w.b * a.H + (int64_t)w.g * G) * a.J;   // head h at h * J
-                const int snv = G * jb;
+            for (int c = 0; c < NCH; ++c) {
+                z[c] = 0.0f;
+                if (KS::NCK > 1 && ck > 0 && l0 + c * P < L) z[c] = tb[(int64_t)hh * a.Lmax + l0 + c * P];
+            }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int idx = lane + 64 * u;
-                    smv[u] = idx < snv ? smb[(int64_t)(idx % G) * a.J + idx / G] : -__builtin_inff();
-                }
+            for (int sub = 0; sub < NSUB; ++sub) {
+                const int s = s0 + sub;
+                if (NS > 2 && s + NS - 2 < S) attn_vm_wait<(NS - 2) * NI>();
+                else attn_vm_wait<0>();
+                attn_lds_wait();
+                if (s + NS - 1 < S) issue(s + NS - 1);
+                const uint8_t* slot = ring + s % NS * STEP;
+                // the next piece of each row is read while the current ones are multiplied
+                auto piece = [&](int pc, uint4 (&kv)[NCH]) {
 #pragma unroll
-                for (int h = 0; h < G; ++h) mr[h] = -__builtin_inff();
-                for (int base = 512; base < snv; base += 64) {
-                    const int idx = base + lane;
-                    if (idx < snv) {
-                        const float v = smb[(int64_t)(idx % G) * a.J + idx / G];
-                        if constexpr (64 % G == 0) {
-                            mr[0] = __builtin_fmaxf(mr[0], v);
-                        } else {
-                            const int h = idx % G;
-#pragma unroll
-                            for (int i = 0; i < G; ++i) mr[i] = (h == i) ? __builtin_fmaxf(mr[i], v) : mr[i];
-                        }
+                    for (int c = 0; c < NCH; ++c) {
+                        const int row = c * P + pos;
+                        kv[c] = *reinterpret_cast<const uint4*>(slot + row * (CC * 2) + 16 * (pc ^ (row & 7)));
                     }
-                }
-            } else {
+                };
+                uint4 kv[NCH], kn[NCH];
+                piece(0, kv);
 #pragma unroll
-                for (int h = 0; h < G; ++h) mr[h] = a.mmax[(int64_t)w.b * a.H + (int64_t)w.g * G + h];
+                for (int pc = 0; pc < PCK; ++pc) {
+                    if (pc + 1 < PCK) piece(pc + 1, kn);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float k0[NCH], k1[NCH];
+#pragma unroll
+                        for (int c = 0; c < NCH; ++c) {
+                            const uint32_t w = e == 0 ? kv[c].x : e == 1 ? kv[c].y : e == 2 ? kv[c].z : kv[c].w;
+                            attn_widen2(w, k0[c], k1[c]);
+                        }
+                        const float q0 = q[sub * CC + 8 * pc + 2 * e], q1 = q[sub * CC + 8 * pc + 2 * e + 1];
+#pragma unroll
+                        for (int c = 0; c < NCH; ++c) z[c] = __builtin_fmaf(q0, k0[c], z[c]);
+#pragma unroll
+                        for (int c = 0; c < NCH; ++c) z[c] = __builtin_fmaf(q1, k1[c], z[c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c) asm volatile("" : "+v"(z[c]));   // this piece's FMAs end here
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c) kv[c] = kn[c];
+                }
             }
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const float t = ck == KS::NCK - 1 ? z[c] * a.scale : z[c];
+                if (l0 + c * P < L) {
+                    if (ck == KS::NCK - 1) mymax = __builtin_fmaxf(mymax, t);
+                    if (hq < G) tb[(int64_t)hq * a.Lmax + l0 + c * P] = t;
+                }
+            }
+        }
+        attn_lds_wait();
+    }
+    return mymax;
+}
+
+// Segment partials of units first, first + stride, ... below Jb * CS (segment unit / CS, value columns part unit % CS) of
+// kv head g of sequence b.  The value stream starts, then row_max(m) brings the group's row maxima;
+// the wave turns t into e (LDS, [position][head], EC positions at a time) and lane p runs the numerator chains of its
+// columns for all heads.  Lanes < G sum e.
+template <int GP, int D, int CS, int RINGB, typename F>
+__device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int G, int L, int Jb, int first, int stride,
+                                           uint8_t* ring, float* es, F row_max) {
+    using VS = ValueSteps<GP, D, CS, RINGB>;
+    constexpr int DH = VS::DH, RS = VS::RS, EC = VS::EC, NS = VS::RING / 4096, NI = 4;
+    constexpr int SEG = kAttnSeg / RS;                // steps of a whole segment
+    constexpr int SVC = EC / RS;                      // steps per chunk of e
+    constexpr int NT = EC * GP / 64;                  // scores per lane per chunk
+    constexpr int PPL = DH >= 128 ? DH / 128 : 0;     // value pairs per lane (0: one column)
+    constexpr int NC = PPL > 0 ? PPL : 1;
+    static_assert(EC % RS == 0 && kAttnSeg % EC == 0, "value step");
+    const int lane = threadIdx.x & 63;
+    const uint32_t ring_base = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)ring);
+    const int64_t h0 = (int64_t)b * a.H + (int64_t)g * G;
+    const float* tb = a.t + h0 * a.Lmax;
+    const char* vb = reinterpret_cast<const char*>(a.v + ((int64_t)b * a.Hkv + g) * a.Lmax * D);
+    const int units = Jb * CS;
+    const int nv = first < units ? (units - 1 - first) / stride + 1 : 0;
+    // steps of this wave's units: whole segments but for the last one of the sequence
+    const int last_rows = L - (Jb - 1) * kAttnSeg;
+    const bool has_last = nv > 0 && (first + stride * (nv - 1)) / CS == Jb - 1;
+    const int S = nv * SEG - (has_last ? (kAttnSeg - last_rows) / RS : 0);
+    auto issue = [&](int s) {
+        const int u = s / SEG, r = s - u * SEG;
+        const int unit = first + stride * u;
+        const int l0 = unit / CS * kAttnSeg + r * RS;                           // < L
+        const char* sb = vb + ((int64_t)l0 * D + unit % CS * DH) * 2;
+        const int rmax = L - 1 - l0;
+        const uint32_t slot = ring_base + (uint32_t)(s % NS * 4096);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int p = 64 * i + lane, row = p / (DH / 8), pc = p % (DH / 8);
+            attn_dma16(sb, (uint32_t)(min(row, rmax) * (D * 2) + 16 * pc), slot + 1024u * i);
         }
     };
-
-    int it = next(gw);
-    if (it >= items) return;
-    Item w = item_of(a, it);
-    int st = 0;
-    fetch(w, 0);
-    float n0[NC][G], n1[NC][G], ssum = 0.0f;
-    float mcur[G];
-    while (it < items) {
-        const Item cur = w;
-        const int ss = st;
-        const int nrow = min(RS, cur.rows - ss * RS);
-        // stage this step: value rows and e = EXP1(t - m) for the valid positions (+0 elsewhere)
-        if (ss == 0) {
-            if constexpr (!INMAX) {
+    float tr[NT];                                     // score (position lane + 64 i, head h) at GP i + h
+    auto tload = [&](int s) {                         // the chunk that begins at step s
+        const int u = s / SEG, r = s - u * SEG;
+        const int l0 = (first + stride * u) / CS * kAttnSeg + r * RS;
 #pragma unroll
-                for (int h = 0; h < G; ++h) mcur[h] = mr[h];
-            } else if constexpr (64 % G == 0) {
-                // reduce over the lanes of each head, then take head h's maximum from lane h
-                float ml = mr[0];
+        for (int i = 0; i < EC / 64; ++i)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) ml = __builtin_fmaxf(ml, smv[u]);
+            for (int h = 0; h < GP; ++h) {
+                // (past L the last score again: its e is never used)
+                const int l = min(l0 + lane + 64 * i, L - 1);
+                tr[GP * i + h] = tb[(int64_t)(h < G ? h : G - 1) * a.Lmax + l];
+            }
+    };
 #pragma unroll
-                for (int sh = 32; sh >= G; sh >>= 1) ml = __builtin_fmaxf(ml, __shfl_xor(ml, sh, 64));
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < S) issue(s);
+    float m[GP];
+    row_max(m);
+    if (S > 0) tload(0);
+    float n0[NC][GP], n1[NC][GP], ssum = 0.0f;
+#pragma unroll 1
+    for (int s = 0; s < S; ++s) {
+        const int u = s / SEG, r = s - u * SEG;
+        const int unit = first + stride * u;
+        const int j = unit / CS, part = unit % CS;
+        const int rows = min(kAttnSeg, L - j * kAttnSeg);
+        if (r % SVC == 0) {
+            attn_lds_wait();                          // the previous chunk's reads are done
 #pragma unroll
-                for (int h = 0; h < G; ++h)
-                    mcur[h] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ml), h));
-            } else {
-                float ml[G];
+            for (int i = 0; i < EC / 64; ++i)
 #pragma unroll
-                for (int h = 0; h < G; ++h) ml[h] = mr[h];
+                for (int h = 0; h < GP; ++h) es[(lane + 64 * i) * GP + h] = exp1_select(tr[GP * i + h] - m[h]);
+            // the next chunk's scores: of this unit if it has more rows, else of the next unit
+            const int next = (r + SVC) * RS < rows ? s + SVC : (u + 1) * SEG;
+            if (next < S) tload(next);
+            if (r == 0) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int h = (lane + 64 * u) % G;
+                for (int k = 0; k < NC; ++k)
 #pragma unroll
-                    for (int i = 0; i < G; ++i) ml[i] = (h == i) ? __builtin_fmaxf(ml[i], smv[u]) : ml[i];
-                }
-#pragma unroll
-                for (int sh = 32; sh > 0; sh >>= 1)
-#pragma unroll
-                    for (int h = 0; h < G; ++h) ml[h] = __builtin_fmaxf(ml[h], __shfl_xor(ml[h], sh, 64));
-#pragma unroll
-                for (int h = 0; h < G; ++h) mcur[h] = ml[h];
+                    for (int h = 0; h < GP; ++h) n0[k][h] = n1[k][h] = 0.0f;
+                ssum = 0.0f;
             }
         }
+        if (NS > 2 && s + NS - 2 < S) attn_vm_wait<(NS - 2) * NI>();
+        else attn_vm_wait<0>();
+        attn_lds_wait();
+        if (s + NS - 1 < S) issue(s + NS - 1);
+        const uint16_t* vw = reinterpret_cast<const uint16_t*>(ring + s % NS * 4096);
+        const float* er = es + (r % SVC) * (RS * GP);
+        const float* eo = er + (lane < GP ? lane : 0);
+        auto row_step = [&](int l) {
+            float ev[GP];
 #pragma unroll
-        for (int u = 0; u < NVL; ++u) *reinterpret_cast<uint4*>(vw + 8 * (lane + 64 * u)) = vr[u];
-#pragma unroll
-        for (int u = 0; u < NTL; ++u) {
-            const int q = lane + 64 * u;
-            if (q < RS * G) {
-                const int l = q / G, h = q - l * G;
-                float mh = mcur[0];
-#pragma unroll
-                for (int i = 1; i < G; ++i) mh = (h == i) ? mcur[i] : mh;
-                ew[l * GP + h] = l < nrow ? exp1(tr[u] - mh) : 0.0f;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // next step (this item's, or the next item's first) in flight during the chains
-        if (st + 1 < (cur.rows + RS - 1) / RS) {
-            ++st;
-        } else {
-            st = 0;
-            it = next(it + tw);
-            if (it < items) w = item_of(a, it);
-        }
-        if (it < items) fetch(w, st);
-        if (ss == 0) {
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-#pragma unroll
-                for (int h = 0; h < G; ++h) n0[k][h] = n1[k][h] = 0.0f;
-            ssum = 0.0f;
-        }
-        const float* es_own = ew + (lane < G ? lane : 0);
-#pragma unroll 4
-        for (int l = 0; l < nrow; ++l) {
-            float ev[G];
-#pragma unroll
-            for (int h = 0; h < G; ++h) ev[h] = ew[l * GP + h];
+            for (int h = 0; h < GP; ++h) ev[h] = er[l * GP + h];
             if constexpr (PPL == 0) {
-                // one column per lane
                 const float v1 = __uint_as_float((uint32_t)vw[l * DH + lane] << 16);
 #pragma unroll
-                for (int h = 0; h < G; ++h) n0[0][h] = __builtin_fmaf(ev[h], v1, n0[0][h]);
+                for (int h = 0; h < GP; ++h) n0[0][h] = __builtin_fmaf(ev[h], v1, n0[0][h]);
             } else {
 #pragma unroll
                 for (int k = 0; k < PPL; ++k) {
                     const uint32_t v2 = *reinterpret_cast<const uint32_t*>(vw + l * DH + 128 * k + 2 * lane);
                     const float vlo = __uint_as_float(v2 << 16), vhi = __uint_as_float(v2 & 0xffff0000u);
 #pragma unroll
-                    for (int h = 0; h < G; ++h) {
+                    for (int h = 0; h < GP; ++h) {
                         n0[k][h] = __builtin_fmaf(ev[h], vlo, n0[k][h]);
                         n1[k][h] = __builtin_fmaf(ev[h], vhi, n1[k][h]);
                     }
                 }
             }
-            ssum = ssum + es_own[l * GP];               // lanes < G: head `lane`'s segment sum
+            ssum = ssum + eo[l * GP];
+        };
+        const int nrow = min(RS, rows - r * RS);
+        if (nrow == RS) {
+#pragma unroll 8
+            for (int l = 0; l < RS; ++l) row_step(l);
+        } else {
+            for (int l = 0; l < nrow; ++l) row_step(l);
         }
-        if (ss == (cur.rows + RS - 1) / RS - 1) {
-            const int64_t hb = (int64_t)cur.b * a.H + (int64_t)cur.g * G;
+        if (r * RS + RS >= rows) {                    // the unit's last step
 #pragma unroll
-            for (int h = 0; h < G; ++h) {
-                float* nb = a.npart + ((hb + h) * a.J + cur.j) * D + half * DH;
+            for (int h = 0; h < GP; ++h) {
+                if (h >= G) break;
+                float* nb = a.npart + ((h0 + h) * a.J + j) * D + part * DH;
                 if constexpr (PPL == 0) {
                     nb[lane] = n0[0][h];
                 } else {
 #pragma unroll
-                    for (int k = 0; k < PPL; ++k) {
-                        nb[128 * k + 2 * lane] = n0[k][h];
-                        nb[128 * k + 2 * lane + 1] = n1[k][h];
-                    }
+                    for (int k = 0; k < PPL; ++k)
+                        *reinterpret_cast<float2*>(nb + 128 * k + 2 * lane) = make_float2(n0[k][h], n1[k][h]);
                 }
             }
-            // (both halves sum the same e in the same order; the first writes the sums)
-            if (lane < G && half == 0) a.spart[(hb + lane) * a.J + cur.j] = ssum;
+            if (lane < G && part == 0) a.spart[(h0 + lane) * a.J + j] = ssum;
         }
-        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// out of head h0 + h, column d: the ascending folds of its Jb segment partials and the division.
+template <int BATCH>
+__device__ __forceinline__ void fold_out(const AttnArgs& a, int64_t bh, int d, int D, int Jb) {
+    const float* sp = a.spart + bh * a.J;
+    const float* np = a.npart + bh * a.J * D + d;
+    float S = 0.0f, N = 0.0f;
+    int jj = 0;
+    auto batch = [&](auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        for (; jj + NB <= Jb; jj += NB) {             // loads issued in groups, additions in order
+            float sv[NB], nv[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                sv[i] = sp[jj + i];
+                nv[i] = np[(int64_t)(jj + i) * D];
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                S = (jj + i == 0) ? sv[i] : S + sv[i];
+                N = (jj + i == 0) ? nv[i] : N + nv[i];
+            }
+        }
+    };
+    if constexpr (BATCH > 8) batch(std::integral_constant<int, BATCH>{});
+    batch(std::integral_constant<int, 8>{});
+    for (; jj < Jb; ++jj) {
+        S = (jj == 0) ? sp[0] : S + sp[jj];
+        N = (jj == 0) ? np[0] : N + np[(int64_t)jj * D];
+    }
+    a.out[bh * D + d] = N / S;
+}
+
+// 3'. the same partials with one wave per (segment, value columns part); each takes the group's row maxima from the
+// segment maxima itself (exact, so no launch of the maximum kernel).  One unit per workgroup (more only beyond the
+// largest grid): the waves of a CU are then at different points of their units, and a short sequence's
+// waves leave at once.
+template <int GP, int D, int CS, int RINGB>
+__global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t ring[RINGB];
+    __shared__ __attribute__((aligned(16))) float es[ValueSteps<GP, D, CS>::EC * GP];
+    const int lane = threadIdx.x;
+    const int G = (int)(a.H / a.Hkv);
+    const uint32_t units = (uint32_t)(a.B * a.Hkv * a.J) * CS;
+    for (uint32_t it = blockIdx.x; it < units; it += gridDim.x) {
+        const Item w = item_of(a, (int)(it / CS));
+        if (w.rows <= 0) continue;
+        const int b = __builtin_amdgcn_readfirstlane(w.b), g = __builtin_amdgcn_readfirstlane(w.g);
+        const int j = __builtin_amdgcn_readfirstlane(w.j), L = __builtin_amdgcn_readfirstlane(w.L);
+        const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
+        value_pass<GP, D, CS, RINGB>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GP]) {
+            const float* sm = a.segmax + ((int64_t)b * a.H + (int64_t)g * G) * a.J;
+#pragma unroll
+            for (int h = 0; h < GP; ++h) m[h] = -__builtin_inff();
+            for (int j0 = lane; j0 < Jb; j0 += 64)
+#pragma unroll
+                for (int h = 0; h < GP; ++h) m[h] = __builtin_fmaxf(m[h], sm[(int64_t)(h < G ? h : G - 1) * a.J + j0]);
+#pragma unroll
+            for (int sh = 32; sh > 0; sh >>= 1)
+#pragma unroll
+                for (int h = 0; h < GP; ++h) m[h] = __builtin_fmaxf(m[h], __shfl_xor(m[h], sh, 64));
+        });
+        attn_lds_wait();                              // before the next unit's rows arrive
+    }
+}
+
+// The whole call for one (sequence, kv head) in one workgroup of eight waves, with barriers in place of launches.
+template <int GP, int D, int CS>
+__global__ void __launch_bounds__(512, 2) attn_fused_kernel(AttnArgs a) {
+    using KS = KeySteps<GP, D>;
+    using VS = ValueSteps<GP, D, CS>;
+    constexpr int RING = KS::RING > VS::RING ? KS::RING : VS::RING;
+    __shared__ __attribute__((aligned(16))) uint8_t ring[8][RING];
+    __shared__ __attribute__((aligned(16))) float es[8][VS::EC * GP];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Hkv = (int)a.Hkv, G = (int)(a.H / a.Hkv);
+    const int b = __builtin_amdgcn_readfirstlane((int)blockIdx.x / Hkv);
+    const int g = __builtin_amdgcn_readfirstlane((int)blockIdx.x - b * Hkv);
+    const int L = clamp_len(a.lens, b, a.Lmax);
+    const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
+    const int nunits = (L + KS::UNIT - 1) / KS::UNIT;
+    float mymax = key_pass<GP, D>(a, b, g, G, L, wave, 8, wave < nunits ? (nunits - 1 - wave) / 8 + 1 : 0, ring[wave]);
+    value_pass<GP, D, CS, VS::RING>(a, b, g, G, L, Jb, wave, 8, ring[wave], es[wave], [&](float (&m)[GP]) {
+        // the maxima over the lanes of each head, then over the waves (through the e region, free until then)
+        float v = mymax;
+#pragma unroll
+        for (int sh = 32; sh >= GP; sh >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, sh, 64));
+        if (lane < GP) es[wave][lane] = v;
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < GP; ++h) {
+            m[h] = es[0][h];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) m[h] = __builtin_fmaxf(m[h], es[w][h]);
+        }
+        __syncthreads();
+    });
+    attn_vm_wait<0>();
+    __syncthreads();
+    for (int o = tid; o < G * D; o += 512) {
+        const int h = o / D;
+        fold_out<8>(a, (int64_t)b * a.H + (int64_t)g * G + h, o - h * D, D, Jb);
     }
 }
 
 // 4. out = N / S after the ascending folds of the segment partials.  Workgroup (b, h),
 // thread d.
 __global__ void __launch_bounds__(256) attn_fold_kernel(AttnArgs a) {
-    const int64_t bh = blockIdx.x, b = bh / a.H;
-    const int L = clamp_len(a.lens, b, a.Lmax);
+    const int64_t bh = blockIdx.x;
+    const int L = clamp_len(a.lens, bh / a.H, a.Lmax);
     const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
-    const int D = a.D;
-    const float* sp = a.spart + bh * a.J;
-    for (int d = threadIdx.x; d < D; d += blockDim.x) {
-        const float* np = a.npart + bh * a.J * D + d;
-        float S = 0.0f, N = 0.0f;
-        int jj = 0;
-        for (; jj + 32 <= Jb; jj += 32) {          // loads issued in groups, additions in order
-            float sv[32], nv[32];
-#pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                sv[i] = sp[jj + i];
-                nv[i] = np[(int64_t)(jj + i) * D];
-            }
-#pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                S = (jj + i == 0) ? sv[i] : S + sv[i];
-                N = (jj + i == 0) ? nv[i] : N + nv[i];
-            }
-        }
-        for (; jj + 8 <= Jb; jj += 8) {
-            float sv[8], nv[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                sv[i] = sp[jj + i];
-                nv[i] = np[(int64_t)(jj + i) * D];
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                S = (jj + i == 0) ? sv[i] : S + sv[i];
-                N = (jj + i == 0) ? nv[i] : N + nv[i];
-            }
-        }
-        for (; jj < Jb; ++jj) {
-            S = (jj == 0) ? sp[0] : S + sp[jj];
-            N = (jj == 0) ? np[0] : N + np[(int64_t)jj * D];
-        }
-        a.out[bh * D + d] = N / S;
-    }
+    for (int d = threadIdx.x; d < a.D; d += blockDim.x) fold_out<32>(a, bh, d, (int)a.D, Jb);
 }
 
 // Workgroups each kernel keeps resident per CU: LDS-limited (160 KB per CU).
@@ -774,21 +947,37 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
     return hipGetLastError();
 }
 
-// Fixed head dims (64, 128, 256).  Scores: 64-column key steps (32 KB tiles, four
-// workgroups per CU); with eight query heads per kv head the two-positions-per-
-// thread kernel (32-column steps, 128 threads, about 20 KB of LDS; measured
-// 111 -> 90 us for the scores of a 32 x 64-head, 4096-position batch, and 0-22 %
-// slower than the 64-column kernel with six or fewer heads).  Partials: one wave per
-// work item for D = 128 and 256 (four 4-wave workgroups per CU, each wave walking
-// items gw, gw + waves, ...), two waves per item (value columns split) when there
-// are at most four items per CU (one 32K-token sequence: the pass 21.0 -> 20.3 us,
-// the call level within its spread); for D = 64 the workgroup-per-item kernel with
-// 16384 / D-row value steps (32 KB tiles, four workgroups per CU).  Other D <= DM:
-// launch_any.
+// Fixed head dims (64, 128, 256).
+//
+// Fused (one launch) where the cache holds at most two segments per sequence, so that launches and their gaps are most of
+// the time, or eight with the lightest heads; one launch per pass otherwise: a workgroup per (sequence, kv head)
+// takes as long as its longest sequence, which the passes spread over the device.  Whole calls, us, fused
+// against one launch per pass (4 sequences, 2 kv heads, 400 positions): D = 128, 1 / 2 / 4 heads per kv head 12.6 / 16.9 /
+// 22.6 against 16.2 / 20.5 / 24.5 and their two gaps, 8 heads level; D = 256, 1 / 2 / 4 heads 18.0 / 25.0 / 36.7
+// against 26 / 27 / 34.7; D = 64, 1 / 2 / 4 / 8 heads 10.7 / 13.8 / 17.7 / 24.4 against 15 / 17 / 19 / 24.
+//
+// Scores: 64-column key steps (32 KB tiles, four workgroups per CU); with eight query heads per kv head the
+// two-positions-per-thread kernel (32-column steps, 128 threads, about 20 KB of LDS; measured 111 -> 90 us
+// for the scores of a 32 x 64-head, 4096-position batch, and 0-22 % slower than the 64-column kernel with six or fewer heads).
+//
+// Partials: one wave per segment, or two with half its value columns each where there are at most four segments per CU
+// (64 of D = 64 fill a wave as they are; the heaviest waves, D = 256 with more than four heads, are always split).
+// Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
+// 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
+// 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0 (a workgroup per segment before; that
+// kernel stays for more than four heads and at most one segment per CU: 11.8 against 15.9).
 template <int G, int D>
 hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
-    constexpr int RS = 16384 / D;
+    constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
+    constexpr int RINGB = GP == 8 ? 12288 : 8192;     // (more in flight per wave costs waves: slower)
     const int64_t items = a.B * a.Hkv * a.J;
+    if constexpr (D * GP <= 512) {
+        if (a.J <= 2 || (D * GP == 64 && a.J <= 8)) {
+            constexpr int CS = D == 64 ? 1 : 2;
+            hipLaunchKernelGGL((attn_fused_kernel<GP, D, CS>), dim3((unsigned)(a.B * a.Hkv)), dim3(512), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
     if constexpr (G == 8) {
         const int64_t lds1 = (int64_t)kAttnSeg * (32 + 8) * 2 + 8 * G;
         const int64_t g1 = items < (kLdsPerCU / lds1) * cus ? items : (kLdsPerCU / lds1) * cus;
@@ -800,45 +989,24 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // partials of head dims 128 and 256: one wave per item; when no wave has more than one
-    // item the waves take the row maxima themselves and the maximum kernel is not launched
-    // (measured 1-8 % faster with up to six query heads per kv head, 1 % slower with eight)
-    constexpr bool kInmax = (D == 128 || D == 256) && G < 8;
-    // at most one item per SIMD (one long sequence, say): each item's value columns are
-    // split between two waves
-    const int cs = (D == 128 || D == 256) && items <= 4 * (int64_t)cus ? 2 : 1;
-    const int64_t gw = (cs * items + 3) / 4 < 4 * (int64_t)cus ? (cs * items + 3) / 4 : 4 * (int64_t)cus;
-    const bool inmax = kInmax && cs * items <= 4 * gw;
-    if (!inmax) {
+    if (D == 64 && G > 4 && items <= cus) {
+        constexpr int RS = 16384 / 64;
         hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 255) / 256)), dim3(256), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-    }
-    if constexpr (D == 128 || D == 256) {
-        bool launched = false;
-        if constexpr (kInmax) {
-            if (inmax) {
-                if (cs == 2)
-                    hipLaunchKernelGGL((attn_partials_wave_kernel<G, D, true, 2>), dim3((unsigned)gw), dim3(256), 0,
-                                       stream, a);
-                else
-                    hipLaunchKernelGGL((attn_partials_wave_kernel<G, D, true, 1>), dim3((unsigned)gw), dim3(256), 0,
-                                       stream, a);
-                launched = true;
-            }
-        }
-        if (!launched) {
-            if (cs == 2)
-                hipLaunchKernelGGL((attn_partials_wave_kernel<G, D, false, 2>), dim3((unsigned)gw), dim3(256), 0, stream,
-                                   a);
-            else
-                hipLaunchKernelGGL((attn_partials_wave_kernel<G, D, false, 1>), dim3((unsigned)gw), dim3(256), 0, stream,
-                                   a);
-        }
+        if constexpr (D == 64 && G > 4)
+            hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
-        const int64_t lds3 = (int64_t)G * kAttnSeg * 4 + (int64_t)RS * (D + 8) * 2;
-        const int64_t g3 = items < (kLdsPerCU / lds3) * cus ? items : (kLdsPerCU / lds3) * cus;
-        hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)g3), dim3(256), 0, stream, a);
+        const bool split = D > 64 && ((D == 256 && GP == 8) || items <= 4 * (int64_t)cus);
+        const int64_t units = items * (split ? 2 : 1);
+        const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
+        if constexpr (D > 64) {
+            if (split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RINGB>), grid, dim3(64), 0, stream, a);
+        }
+        if (!split) {
+            if constexpr (!(D == 256 && GP == 8))
+                hipLaunchKernelGGL((attn_values_kernel<GP, D, 1, RINGB>), grid, dim3(64), 0, stream, a);
+        }
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;

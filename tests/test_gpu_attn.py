@@ -205,3 +205,38 @@ def test_in_kernel_maximum_beyond_512_segment_maxima(H, L):
     in its tail loop.  One kv head: few work items, so the in-kernel maximum path is taken."""
     assert H * (-(-L // 256)) > 512
     _check(1, H, 1, L, 128, [L], seed=H * 7 + L)
+
+
+# The one-launch kernel (at most two segments per sequence; eight with one query head per kv head and D = 64) and
+# the wave-per-unit partials: group sizes that fill the lanes and that repeat heads, lengths around the
+# 128-position units, the 256-position segments and the value steps, empty and over-long sequences, segments on
+# either side of the column split (four segments per CU) and of the kept workgroup partials (one per CU).
+@pytest.mark.parametrize("B,H,Hkv,L,D", [
+    (3, 2, 2, 512, 64), (3, 4, 2, 300, 64), (3, 9, 3, 512, 64), (3, 14, 2, 129, 64), (2, 3, 3, 2048, 64),
+    (3, 2, 2, 512, 128), (3, 4, 2, 257, 128), (3, 6, 2, 512, 128), (3, 8, 2, 127, 128),
+    (3, 2, 2, 512, 256), (3, 4, 2, 500, 256),
+    (2, 16, 2, 520, 64), (40, 5, 1, 1800, 64), (3, 24, 4, 1500, 64), (3, 2, 2, 2049, 64),
+    (3, 8, 2, 1030, 128), (20, 16, 8, 1700, 128), (3, 10, 2, 900, 128), (40, 56, 7, 1000, 128),
+    (3, 8, 2, 777, 256), (3, 16, 2, 600, 256), (30, 12, 6, 1500, 256)])
+def test_fused_and_wave_partials(B, H, Hkv, L, D):
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    rng = np.random.default_rng(B * L + D + H)
+    q = rng.standard_normal((B, H, D), dtype=np.float32)
+    kc = (rng.standard_normal((B, Hkv, L, D), dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    vc = (rng.standard_normal((B, Hkv, L, D), dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    edges = [L, 0, 1, 127, 128, 129, 255, 256, 257, L - 1, L + 9, 16, 31, 383]
+    lens = np.array([edges[i % len(edges)] for i in range(B)] if B > 3 else [L, min(L, 130), L - 1][:B], dtype=np.int32)
+    scale = 1.0 / np.sqrt(D)
+    gu.log(f"attn B={B} H={H} Hkv={Hkv} L={L} D={D}")
+    want = oracle.attn_decode(q, kc, vc, lens, scale)
+    dev = gu.dev()
+    out = torch.full((B, H, D), 7.0, dtype=torch.float32, device=dev)
+    rg.rg_attn_decode(torch.from_numpy(q).to(dev), torch.from_numpy(kc.view(np.int16)).to(dev),
+                      torch.from_numpy(vc.view(np.int16)).to(dev), torch.from_numpy(lens).to(dev), out, scale)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    nan = np.isnan(want)
+    assert np.array_equal(nan, np.isnan(got))
+    gu.assert_bitwise(np.where(nan, 0.0, got), np.where(nan, 0.0, want), f"attn ({B},{H},{Hkv},{L},{D})")
