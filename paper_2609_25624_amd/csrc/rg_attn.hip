@@ -965,7 +965,8 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
 // Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
 // 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
 // 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0 (a workgroup per segment before; that
-// kernel stays for more than four heads and at most one segment per CU: 11.8 against 15.9).
+// kernel stays for four and more heads and at most 1.25 segments per CU: eight heads 11.8 against 15.9, four heads 11.2
+// against 12.0).
 template <int G, int D>
 hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
@@ -989,12 +990,12 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (D == 64 && G > 4 && items <= cus) {
+    if (D == 64 && G >= 4 && 4 * items <= 5 * (int64_t)cus) {
         constexpr int RS = 16384 / 64;
         hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 255) / 256)), dim3(256), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if constexpr (D == 64 && G > 4)
+        if constexpr (D == 64 && G >= 4)
             hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
         const bool split = D > 64 && ((D == 256 && GP == 8) || items <= 4 * (int64_t)cus);

@@ -2012,79 +2012,121 @@ __global__ void __launch_bounds__(256) cast_kernel(const uint16_t* __restrict__ 
 // ---------------------------------------------------------------------------
 // argmax per row, lowest index on ties, NaN never wins.  Comparisons are
 // exact, so the result does not depend on the reduction tree.
+//
+// One workgroup per row (a row has no scratch to share between workgroups), so a long row is bound by what one CU
+// streams and by the work per element.  Threads therefore keep only the largest value of their elements (a compare and
+// a select each) and the first batch of loads that holds it; once the row's maximum is known, the threads that have
+// it read that batch again for the lowest index.  128256 values: a (value, index) pair per element 16.7 us,
+// 8.5 us so; rows at any 4-byte alignment take the same 16-byte loads.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool better(float v, int64_t i, float bv, int64_t bi) {
-    return (v == v) & ((bi < 0) | (bv != bv) | (v > bv) | ((v == bv) & (i < bi)));
-}
-
 constexpr int kArgmaxThreads = 1024;
-constexpr int kArgmaxBatch = 16;     // independent loads in flight per thread (4 or 16 bytes each)
+constexpr int kArgmaxBatch = 16;     // independent 16-byte loads in flight per thread
 
 __global__ void __launch_bounds__(kArgmaxThreads) argmax_kernel(const float* __restrict__ y, int64_t* __restrict__ out,
                                                                 int64_t N) {
-    __shared__ float sv[kArgmaxThreads];
-    __shared__ int64_t si[kArgmaxThreads];
+    __shared__ float sv[kArgmaxThreads / 64];
+    __shared__ int64_t si[kArgmaxThreads / 64];
     const int64_t m = blockIdx.x;
     const float* row = y + m * N;
-    float bv = 0.0f;
-    int64_t bi = -1;
-    constexpr int64_t step = (int64_t)kArgmaxThreads * kArgmaxBatch;
-    int64_t n0 = threadIdx.x;
-    if (N % 4 == 0 && ((uintptr_t)row & 15) == 0) {
-        // 16-byte loads: a row of the 128256-entry LM head is two rounds of 16 loads per thread
-        const float4* row4 = reinterpret_cast<const float4*>(row);
-        const int64_t N4 = N / 4;
-        for (int64_t q0 = threadIdx.x; q0 < N4; q0 += step) {
-            float4 v[kArgmaxBatch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float kLow = -__builtin_inff();
+    const int64_t N4 = N / 4;
+    // float4 q of the row, at any alignment of the row
+    auto load4 = [&](int64_t q) {
+        float4 v;
+        __builtin_memcpy(&v, row + 4 * q, sizeof v);
+        return v;
+    };
+    // the largest value of this thread's elements (kLow if it has none above it) and the batch that holds it first: `bn`
+    // float4s from bb, kArgmaxThreads apart.  Batches of 16, 4 and 1 loads, the smaller ones for what is left.
+    float bv = kLow;
+    int64_t bb = -1, base = 0;
+    int bn = 0;
+    auto batches = [&](auto nc) {
+        constexpr int NB = decltype(nc)::value;
+        for (; N4 - base > (int64_t)(NB == 1 ? 0 : NB - 1) * kArgmaxThreads; base += NB * kArgmaxThreads) {
+            const int64_t q0 = base + tid;
+            float4 v[NB];
 #pragma unroll
-            for (int u = 0; u < kArgmaxBatch; ++u) {
+            for (int u = 0; u < NB; ++u) {
                 const int64_t q = q0 + (int64_t)u * kArgmaxThreads;
-                v[u] = q < N4 ? row4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[u] = load4(q < N4 ? q : N4 - 1);             // past the row: its last float4 (again)
+            }
+            float g[4] = {kLow, kLow, kLow, kLow};
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                g[0] = v[u].x > g[0] ? v[u].x : g[0];          // (a NaN is never greater)
+                g[1] = v[u].y > g[1] ? v[u].y : g[1];
+                g[2] = v[u].z > g[2] ? v[u].z : g[2];
+                g[3] = v[u].w > g[3] ? v[u].w : g[3];
             }
 #pragma unroll
-            for (int u = 0; u < kArgmaxBatch; ++u) {
-                const int64_t q = q0 + (int64_t)u * kArgmaxThreads;
-                if (q >= N4) continue;
-                const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const bool take = better(e[h], 4 * q + h, bv, bi);   // selects, not branches
-                    bv = take ? e[h] : bv;
-                    bi = take ? 4 * q + h : bi;
-                }
+            for (int h = 0; h < 4; ++h) {
+                bb = g[h] > bv ? q0 : bb;
+                bn = g[h] > bv ? NB : bn;
+                bv = g[h] > bv ? g[h] : bv;
             }
         }
-        n0 = N;   // nothing left for the scalar loops
-    }
-    for (; n0 + (kArgmaxBatch - 1) * kArgmaxThreads < N; n0 += step) {
-        float v[kArgmaxBatch];
+    };
+    batches(std::integral_constant<int, kArgmaxBatch>{});
+    batches(std::integral_constant<int, 4>{});
+    batches(std::integral_constant<int, 1>{});
+    const int64_t tail = 4 * N4 + tid;                         // the last N % 4 elements, one per thread
+    const float tv = tail < N ? row[tail] : kLow;
+    const float mine = tv > bv ? tv : bv;
+    // the row's maximum
+    float mx = mine;
 #pragma unroll
-        for (int u = 0; u < kArgmaxBatch; ++u) v[u] = row[n0 + (int64_t)u * kArgmaxThreads];
-#pragma unroll
-        for (int u = 0; u < kArgmaxBatch; ++u) {
-            const int64_t n = n0 + (int64_t)u * kArgmaxThreads;
-            if (better(v[u], n, bv, bi)) { bv = v[u]; bi = n; }
-        }
+    for (int sh = 32; sh > 0; sh >>= 1) {
+        const float o = __shfl_xor(mx, sh, 64);
+        mx = o > mx ? o : mx;
     }
-    for (int64_t n = n0; n < N; n += kArgmaxThreads) {
-        const float v = row[n];
-        if (better(v, n, bv, bi)) { bv = v; bi = n; }
-    }
-    sv[threadIdx.x] = bv;
-    si[threadIdx.x] = bi;
+    if (lane == 0) sv[wave] = mx;
     __syncthreads();
-    for (int h = kArgmaxThreads / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            const float v = sv[threadIdx.x + h];
-            const int64_t i = si[threadIdx.x + h];
-            if (i >= 0 && better(v, i, sv[threadIdx.x], si[threadIdx.x])) {
-                sv[threadIdx.x] = v;
-                si[threadIdx.x] = i;
-            }
+#pragma unroll
+    for (int w = 0; w < kArgmaxThreads / 64; ++w) mx = sv[w] > mx ? sv[w] : mx;
+    // the lowest index that holds it (equality takes -0 for +0): the thread's batch if it has the maximum, every batch of
+    // every thread if nothing is above -inf (then -inf itself is the maximum, if the row has one)
+    constexpr int64_t kNone = INT64_MAX;
+    int64_t bi = kNone;
+    // (a float4 past the row is the last one: its index is the true one, whichever thread reports it)
+    auto search = [&](int64_t q0, auto nc) {
+        constexpr int NB = decltype(nc)::value;
+        float4 v[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int64_t q = q0 + (int64_t)u * kArgmaxThreads;
+            v[u] = load4(q < N4 ? q : N4 - 1);
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = NB - 1; u >= 0; --u) {
+            const int64_t qu = q0 + (int64_t)u * kArgmaxThreads, q = qu < N4 ? qu : N4 - 1;
+            bi = v[u].w == mx ? 4 * q + 3 : bi;
+            bi = v[u].z == mx ? 4 * q + 2 : bi;
+            bi = v[u].y == mx ? 4 * q + 1 : bi;
+            bi = v[u].x == mx ? 4 * q : bi;
+        }
+    };
+    if (mx == kLow) {
+        for (int64_t q = tid; q < N4 && bi == kNone; q += kArgmaxThreads) search(q, std::integral_constant<int, 1>{});
+    } else if (bv == mx) {
+        if (bn == kArgmaxBatch) search(bb, std::integral_constant<int, kArgmaxBatch>{});
+        else if (bn == 4) search(bb, std::integral_constant<int, 4>{});
+        else search(bb, std::integral_constant<int, 1>{});
     }
-    if (threadIdx.x == 0) out[m] = si[0];
+    if (bi == kNone && tail < N && tv == mx) bi = tail;
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) {
+        const int64_t o = __shfl_xor(bi, sh, 64);
+        bi = o < bi ? o : bi;
+    }
+    if (lane == 0) si[wave] = bi;
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < kArgmaxThreads / 64; ++w) bi = si[w] < bi ? si[w] : bi;
+        out[m] = bi == kNone ? -1 : bi;
+    }
 }
 
 // ---------------------------------------------------------------------------
