@@ -8,6 +8,8 @@ import fails loudly: there is no CPU fallback.
 import ctypes
 import os
 
+import torch   # before librg.so (see _load); also keeps the calls below free of import lookups
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "librg.so")
 
@@ -44,7 +46,6 @@ def _load():
     # that same runtime (same soname), so device pointers and streams from
     # torch are valid in librg.  Two HIP runtimes in one process do not share
     # the device (the second reports no device).
-    import torch  # noqa: F401
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run __graft_entry__.build() (hipcc, gfx950)")
     L = ctypes.CDLL(LIB_PATH)
@@ -77,6 +78,7 @@ def _load():
 
 
 lib = _load()
+_c_linear, _c_linear_bias, _c_linear_f32w = lib.rg_linear, lib.rg_linear_bias, lib.rg_linear_f32w
 
 # Every symbol include/rg.h declares (checked by the tests).
 EXPORTS = ("rg_linear", "rg_linear_bias", "rg_linear_f32w", "rg_linear_set_launch", "rg_plan", "rg_plan_f32w",
@@ -97,76 +99,99 @@ def _check(code, where):
         raise RgError(code, where)
 
 
-def _stream_ptr(stream):
+# A decode step makes a handful of launches of a few microseconds each, so what a call does besides its launch counts: dtype
+# sets built once, the current device asked for once per call, and the current stream as its raw handle
+# (torch.cuda.current_stream() builds a Stream object: 2.9 us of a 10 us call against 0.1).
+_F32 = (torch.float32,)
+_BF16 = (torch.bfloat16, torch.int16, torch.uint16)
+_U8 = (torch.uint8,)
+_I32 = (torch.int32,)
+_I64 = (torch.int64,)
+_Tensor = torch.Tensor
+_current_device = torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_ptr(stream, cur=None):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(_current_device() if cur is None else cur)
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
-def _tensor_ptr(t, dtypes, name):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+def _tensor_ptr(t, dtypes, name, cur=None):
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype not in dtypes:
         raise TypeError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous (row-major)")
-    cur = torch.cuda.current_device()
-    if t.device.index != cur:
+    if cur is None:
+        cur = _current_device()
+    if t.get_device() != cur:
         # the library launches on the current device; memory of another device is not passed on
         raise ValueError(f"{name} is on {t.device} but the current device is cuda:{cur}")
     return t.data_ptr()
 
 
+def _first_ptr(t, dtypes, name):
+    """The first tensor's pointer and the current device (asked for once the tensor is known to be a device tensor, so
+    that a host tensor is refused without one)."""
+    if not isinstance(t, _Tensor) or not t.is_cuda:
+        raise TypeError(f"{name} must be a CUDA (HIP) tensor")
+    cur = _current_device()
+    return _tensor_ptr(t, dtypes, name, cur), cur
+
+
 def rg_linear(x, w, y, stream=None):
     """y[M,N] = x[M,K] * up(w[N,K])^T in the fixed order (float32 x, y; bfloat16 w)."""
-    import torch
-    px = _tensor_ptr(x, (torch.float32,), "x")
-    pw = _tensor_ptr(w, (torch.bfloat16, torch.int16, torch.uint16), "w")
-    py = _tensor_ptr(y, (torch.float32,), "y")
-    if x.dim() != 2 or w.dim() != 2 or y.dim() != 2:
+    px, cur = _first_ptr(x, _F32, "x")
+    pw = _tensor_ptr(w, _BF16, "w", cur)
+    py = _tensor_ptr(y, _F32, "y", cur)
+    sx, sw, sy = x.shape, w.shape, y.shape
+    if len(sx) != 2 or len(sw) != 2 or len(sy) != 2:
         raise ValueError("x, w, y must be 2-D")
-    M, K = x.shape
-    N = w.shape[0]
-    if w.shape[1] != K or tuple(y.shape) != (M, N):
-        raise ValueError(f"shape mismatch x{tuple(x.shape)} w{tuple(w.shape)} y{tuple(y.shape)}")
-    _check(lib.rg_linear(px, pw, py, M, N, K, _stream_ptr(stream)), "rg_linear")
+    M, K = sx
+    N = sw[0]
+    if sw[1] != K or sy[0] != M or sy[1] != N:
+        raise ValueError(f"shape mismatch x{tuple(sx)} w{tuple(sw)} y{tuple(sy)}")
+    _check(_c_linear(px, pw, py, M, N, K, _stream_ptr(stream, cur)), "rg_linear")
     return y
 
 
 def rg_linear_bias(x, w, b, y, stream=None):
     """y[M,N] = x[M,K] * up(w[N,K])^T + b[N]: the fixed-order product, then one add of b."""
-    import torch
-    px = _tensor_ptr(x, (torch.float32,), "x")
-    pw = _tensor_ptr(w, (torch.bfloat16, torch.int16, torch.uint16), "w")
-    pb = _tensor_ptr(b, (torch.float32,), "b")
-    py = _tensor_ptr(y, (torch.float32,), "y")
-    if x.dim() != 2 or w.dim() != 2 or y.dim() != 2 or b.dim() != 1:
+    px, cur = _first_ptr(x, _F32, "x")
+    pw = _tensor_ptr(w, _BF16, "w", cur)
+    pb = _tensor_ptr(b, _F32, "b", cur)
+    py = _tensor_ptr(y, _F32, "y", cur)
+    sx, sw, sb, sy = x.shape, w.shape, b.shape, y.shape
+    if len(sx) != 2 or len(sw) != 2 or len(sy) != 2 or len(sb) != 1:
         raise ValueError("x, w, y must be 2-D and b 1-D")
-    M, K = x.shape
-    N = w.shape[0]
-    if w.shape[1] != K or tuple(y.shape) != (M, N) or b.shape[0] != N:
-        raise ValueError(f"shape mismatch x{tuple(x.shape)} w{tuple(w.shape)} b{tuple(b.shape)} y{tuple(y.shape)}")
-    _check(lib.rg_linear_bias(px, pw, pb, py, M, N, K, _stream_ptr(stream)), "rg_linear_bias")
+    M, K = sx
+    N = sw[0]
+    if sw[1] != K or sy[0] != M or sy[1] != N or sb[0] != N:
+        raise ValueError(f"shape mismatch x{tuple(sx)} w{tuple(sw)} b{tuple(sb)} y{tuple(sy)}")
+    _check(_c_linear_bias(px, pw, pb, py, M, N, K, _stream_ptr(stream, cur)), "rg_linear_bias")
     return y
 
 
 def rg_linear_f32w(x, w, y, stream=None):
     """y[M,N] = x[M,K] * w[N,K]^T in the fixed order with float32 weights used as they are."""
-    import torch
-    px = _tensor_ptr(x, (torch.float32,), "x")
-    pw = _tensor_ptr(w, (torch.float32,), "w")
-    py = _tensor_ptr(y, (torch.float32,), "y")
-    if x.dim() != 2 or w.dim() != 2 or y.dim() != 2:
+    px, cur = _first_ptr(x, _F32, "x")
+    pw = _tensor_ptr(w, _F32, "w", cur)
+    py = _tensor_ptr(y, _F32, "y", cur)
+    sx, sw, sy = x.shape, w.shape, y.shape
+    if len(sx) != 2 or len(sw) != 2 or len(sy) != 2:
         raise ValueError("x, w, y must be 2-D")
-    M, K = x.shape
-    N = w.shape[0]
-    if w.shape[1] != K or tuple(y.shape) != (M, N):
-        raise ValueError(f"shape mismatch x{tuple(x.shape)} w{tuple(w.shape)} y{tuple(y.shape)}")
-    _check(lib.rg_linear_f32w(px, pw, py, M, N, K, _stream_ptr(stream)), "rg_linear_f32w")
+    M, K = sx
+    N = sw[0]
+    if sw[1] != K or sy[0] != M or sy[1] != N:
+        raise ValueError(f"shape mismatch x{tuple(sx)} w{tuple(sw)} y{tuple(sy)}")
+    _check(_c_linear_f32w(px, pw, py, M, N, K, _stream_ptr(stream, cur)), "rg_linear_f32w")
     return y
 
 
@@ -205,23 +230,21 @@ def rg_plan_f32w(M, N, K):
 
 
 def rg_cast_bf16_f32(w, out, stream=None):
-    import torch
-    pw = _tensor_ptr(w, (torch.bfloat16, torch.int16, torch.uint16), "w")
-    po = _tensor_ptr(out, (torch.float32,), "out")
+    pw, cur = _first_ptr(w, _BF16, "w")
+    po = _tensor_ptr(out, _F32, "out", cur)
     if out.numel() != w.numel():
         raise ValueError("out must have w.numel() elements")
-    _check(lib.rg_cast_bf16_f32(pw, po, w.numel(), _stream_ptr(stream)), "rg_cast_bf16_f32")
+    _check(lib.rg_cast_bf16_f32(pw, po, w.numel(), _stream_ptr(stream, cur)), "rg_cast_bf16_f32")
     return out
 
 
 def rg_argmax_rows(y, out, stream=None):
-    import torch
-    py = _tensor_ptr(y, (torch.float32,), "y")
-    po = _tensor_ptr(out, (torch.int64,), "out")
+    py, cur = _first_ptr(y, _F32, "y")
+    po = _tensor_ptr(out, _I64, "out", cur)
     M, N = y.shape
     if out.numel() != M:
         raise ValueError("out must have one entry per row")
-    _check(lib.rg_argmax_rows(py, po, M, N, _stream_ptr(stream)), "rg_argmax_rows")
+    _check(lib.rg_argmax_rows(py, po, M, N, _stream_ptr(stream, cur)), "rg_argmax_rows")
     return out
 
 
@@ -246,27 +269,32 @@ def rg_attn_workspace_size(B, H, Lmax, D):
     return int(lib.rg_attn_workspace_size(B, H, Lmax, D))
 
 
+def _attn_args(q, kc, vc, lens, out):
+    """Pointers, current device and sizes of a decode-attention call, checked."""
+    pq, cur = _first_ptr(q, _F32, "q")
+    pk = _tensor_ptr(kc, _BF16, "kc", cur)
+    pv = _tensor_ptr(vc, _BF16, "vc", cur)
+    pl = _tensor_ptr(lens, _I32, "lens", cur)
+    po = _tensor_ptr(out, _F32, "out", cur)
+    sq, sk = q.shape, kc.shape
+    if len(sq) != 3 or len(sk) != 4 or vc.shape != sk or out.shape != sq:
+        raise ValueError("q/out [B,H,D], kc/vc [B,Hkv,Lmax,D]")
+    B, H, D = sq
+    Bk, Hkv, Lmax, D2 = sk
+    if Bk != B or D2 != D or lens.numel() != B:
+        raise ValueError(f"shape mismatch q{tuple(sq)} kc{tuple(sk)} lens{tuple(lens.shape)}")
+    return pq, pk, pv, pl, po, cur, (B, H, Hkv, Lmax, D)
+
+
 def rg_attn_decode(q, kc, vc, lens, out, scale, workspace=None, stream=None):
     """Fixed-order decode attention: q f32 [B,H,D], kc/vc bf16 [B,Hkv,Lmax,D], lens int32 [B], out f32 [B,H,D].
     `workspace` (a uint8 device tensor of rg_attn_workspace_size bytes) is allocated by torch if None."""
-    import torch
-    pq = _tensor_ptr(q, (torch.float32,), "q")
-    pk = _tensor_ptr(kc, (torch.bfloat16, torch.int16, torch.uint16), "kc")
-    pv = _tensor_ptr(vc, (torch.bfloat16, torch.int16, torch.uint16), "vc")
-    pl = _tensor_ptr(lens, (torch.int32,), "lens")
-    po = _tensor_ptr(out, (torch.float32,), "out")
-    if q.dim() != 3 or kc.dim() != 4 or tuple(vc.shape) != tuple(kc.shape) or tuple(out.shape) != tuple(q.shape):
-        raise ValueError("q/out [B,H,D], kc/vc [B,Hkv,Lmax,D]")
-    B, H, D = q.shape
-    _, Hkv, Lmax, D2 = kc.shape
-    if kc.shape[0] != B or D2 != D or lens.numel() != B:
-        raise ValueError(f"shape mismatch q{tuple(q.shape)} kc{tuple(kc.shape)} lens{tuple(lens.shape)}")
-    need = rg_attn_workspace_size(B, H, Lmax, D)
+    pq, pk, pv, pl, po, cur, (B, H, Hkv, Lmax, D) = _attn_args(q, kc, vc, lens, out)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
-    pw = _tensor_ptr(workspace, (torch.uint8,), "workspace")
+        workspace = torch.empty(max(rg_attn_workspace_size(B, H, Lmax, D), 1), dtype=torch.uint8, device=q.device)
+    pw = _tensor_ptr(workspace, _U8, "workspace", cur)
     _check(lib.rg_attn_decode(pq, pk, pv, pl, po, B, H, Hkv, Lmax, D, float(scale), pw, workspace.numel(),
-                              _stream_ptr(stream)), "rg_attn_decode")
+                              _stream_ptr(stream, cur)), "rg_attn_decode")
     return out
 
 
@@ -274,18 +302,7 @@ def rg_attn_decode_noalloc(q, kc, vc, lens, out, scale, stream=None):
     """rg_attn_decode with the library's static device scratch as workspace (allocates nothing;
     workspaces beyond ATTN_SCRATCH_BYTES are refused with RG_ERR_RANGE).  Calls that overlap in
     time on one device share that scratch and race."""
-    import torch
-    pq = _tensor_ptr(q, (torch.float32,), "q")
-    pk = _tensor_ptr(kc, (torch.bfloat16, torch.int16, torch.uint16), "kc")
-    pv = _tensor_ptr(vc, (torch.bfloat16, torch.int16, torch.uint16), "vc")
-    pl = _tensor_ptr(lens, (torch.int32,), "lens")
-    po = _tensor_ptr(out, (torch.float32,), "out")
-    if q.dim() != 3 or kc.dim() != 4 or tuple(vc.shape) != tuple(kc.shape) or tuple(out.shape) != tuple(q.shape):
-        raise ValueError("q/out [B,H,D], kc/vc [B,Hkv,Lmax,D]")
-    B, H, D = q.shape
-    _, Hkv, Lmax, D2 = kc.shape
-    if kc.shape[0] != B or D2 != D or lens.numel() != B:
-        raise ValueError(f"shape mismatch q{tuple(q.shape)} kc{tuple(kc.shape)} lens{tuple(lens.shape)}")
-    _check(lib.rg_attn_decode_noalloc(pq, pk, pv, pl, po, B, H, Hkv, Lmax, D, float(scale), _stream_ptr(stream)),
+    pq, pk, pv, pl, po, cur, (B, H, Hkv, Lmax, D) = _attn_args(q, kc, vc, lens, out)
+    _check(lib.rg_attn_decode_noalloc(pq, pk, pv, pl, po, B, H, Hkv, Lmax, D, float(scale), _stream_ptr(stream, cur)),
            "rg_attn_decode_noalloc")
     return out
