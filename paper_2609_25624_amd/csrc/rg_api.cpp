@@ -734,7 +734,7 @@ int linear_impl(const float* x, const uint16_t* w, const float* bias, float* y, 
     hipError_t e = hipSuccess;
     if (takes_wave_tile(p, M, K, 8, o)) {
         e = rg::launch_wtile(x, w, bias, y, M, N, K, 0, 0, st);
-        if (e != hipErrorInvalidValue) return hip_status(e);   // more tiles than a grid holds: the class's kernel
+        if (e != hipErrorInvalidValue) return hip_status(e);   // not its shape: the class's kernel
     }
     if (p.kernel == RG_KERNEL_GEMV) {
         rg::GemvArgs a;

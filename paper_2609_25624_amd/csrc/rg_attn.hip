@@ -970,7 +970,8 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
 template <int G, int D>
 hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
-    constexpr int RINGB = GP == 8 ? 12288 : 8192;     // (more in flight per wave costs waves: slower)
+    // (more in flight per wave costs waves: slower but for the heaviest rows)
+    constexpr int RING1 = GP == 8 ? 12288 : 8192, RING2 = GP == 8 || D == 256 ? 12288 : 8192;
     const int64_t items = a.B * a.Hkv * a.J;
     if constexpr (D * GP <= 512) {
         if (a.J <= 2 || (D * GP == 64 && a.J <= 8)) {
@@ -1002,11 +1003,11 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
         const int64_t units = items * (split ? 2 : 1);
         const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
         if constexpr (D > 64) {
-            if (split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RINGB>), grid, dim3(64), 0, stream, a);
+            if (split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RING2>), grid, dim3(64), 0, stream, a);
         }
         if (!split) {
             if constexpr (!(D == 256 && GP == 8))
-                hipLaunchKernelGGL((attn_values_kernel<GP, D, 1, RINGB>), grid, dim3(64), 0, stream, a);
+                hipLaunchKernelGGL((attn_values_kernel<GP, D, 1, RING1>), grid, dim3(64), 0, stream, a);
         }
     }
     e = hipGetLastError();

@@ -434,30 +434,40 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
                 for (int q = 0; q < QC; ++q) part[64 * q + lane] = acc[(ch * QC + q) / TN][(ch * QC + q) % TN];
             }
             wg_barrier();
-            for (int o = tid; o < 64 * QC; o += NT) {
-                float v;
+            // four neighbouring outputs per thread
+            const float4* pf = reinterpret_cast<const float4*>(pfull);
+            const float4* pl = reinterpret_cast<const float4*>(plast);
+            float4* tt = reinterpret_cast<float4*>(tots + ch * QC * 64);
+            auto add = [](const float4& u, const float4& v) { return make_float4(u.x + v.x, u.y + v.y, u.z + v.z, u.w + v.w); };
+            for (int o = tid; o < 16 * QC; o += NT) {
+                float4 v;
                 int w = 0;
                 if (t > 0) {
-                    v = tots[ch * QC * 64 + o];
+                    v = tt[o];
                 } else {
-                    v = nfold > 0 ? pfull[o] : plast[o];   // the first partial starts the sum
+                    v = nfold > 0 ? pf[o] : pl[o];         // the first partial starts the sum
                     w = 1;
                 }
                 for (; w + 4 <= nfold; w += 4) {
-                    float pv[4];
+                    float4 pv[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) pv[u] = pfull[(w + u) * (RING / 4) + o];
+                    for (int u = 0; u < 4; ++u) pv[u] = pf[(w + u) * (RING / 16) + o];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) v = v + pv[u];
+                    for (int u = 0; u < 4; ++u) v = add(v, pv[u]);
                 }
-                for (; w < nfold; ++w) v = v + pfull[w * (RING / 4) + o];
-                if (w < nact) v = v + plast[w * (RING / 4) + o];
+                for (; w < nfold; ++w) v = add(v, pf[w * (RING / 16) + o]);
+                if (w < nact) v = add(v, pl[w * (RING / 16) + o]);
                 if (last) {
-                    const int q = ch * QC + o / 64, ln = o % 64;
-                    const int64_t gm = m0 + (q / TN) * LM + ln % LM, gn = n0 + (q % TN) * LN + ln / LM;
-                    if (gm < M && gn < N) a.y[gm * N + gn] = a.bias ? v + a.bias[gn] : v;
+                    const int q = ch * QC + o / 16;
+                    const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int ln = (4 * o + i) % 64;
+                        const int64_t gm = m0 + (q / TN) * LM + ln % LM, gn = n0 + (q % TN) * LN + ln / LM;
+                        if (gm < M && gn < N) a.y[gm * N + gn] = a.bias ? e[i] + a.bias[gn] : e[i];
+                    }
                 } else {
-                    tots[ch * QC * 64 + o] = v;
+                    tt[o] = v;
                 }
             }
             wg_barrier();
@@ -521,49 +531,89 @@ int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
     return (int64_t)nw * kDepth * b.slab + (J > nw ? (int64_t)b.bm * b.bn * 4 : 0);
 }
 
-// Waves of a workgroup: the fewest that give the fewest rounds of segments, within `most` and LDS.
-int wtile_waves(const WtileBuild& b, int64_t J, int most) {
-    int nw = (int)(J < most ? J : most);
-    while (nw > 1 && wtile_lds(b, J, nw) > kWtileLds) --nw;
-    const int64_t rounds = (J + nw - 1) / nw;
-    return (int)((J + rounds - 1) / rounds);
-}
-
-// Tile and waves for a shape: the least estimated time over the builds, a function of (M, N, K), the weight
-// type and the alignment.  A CU works off ceil(tiles / 256) tiles at the build's rate (a
-// share of it while fewer than eight waves are resident), with a fixed cost per tile for
-// its first slabs and folds (1.5 us), and never faster than HBM streams W (6.2 GB per ms).  With one tile per CU
-// the workgroup brings all the waves that fit, with several eight, and four where many tiles have 16 rows
-// (several workgroups share a CU then and one's folds hide behind the others: the 128256 x 4096 head
-// at M = 16 305 -> 286 us; 64-row tiles are faster on eight: 8192 x 28672 at M = 2048 10.61 -> 10.36 ms).
+// Tile and waves for a shape: the least estimated time over the builds and a few wave counts each, a function of
+// (M, N, K), the weight type and the alignment.  A wave runs at an eighth of the build's rate; a workgroup of nw
+// waves takes as long as the wave with the most k (`path`: whole rounds of segments, a short last segment alone in
+// its round counted as short), plus 1 us for its first slabs and per round 0.3 us and the fold, which its threads share; a CU works off ceil(tiles / 256) tiles, as many at
+// a time as its eight wave slots and LDS hold (builds of sixteen waves share the slots), and never faster than
+// HBM streams W (6.2 GB per ms).  So 1536 = 6 segments run on 2 waves, four workgroups per CU, not on 6 waves with
+// two slots empty (2048 x 16384 x 1536 1472 -> RG_1536 us).
+//
+// Returns false where the 128 x 128 register tiles are the better ones: at least 512 of them, and their own time
+// (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is pessimistic by that much where
+// tiles are many (2048 x 16384: K = 1024 767 against 785 us, K = 2048 1481 against 1532; from K = 8192 on the wave
+// tiles lead: 2048 x 57344 x 8192 20.8 against 21.8 ms).
 template <typename WT, bool AL>
 bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
     int nb = 0;
     const WtileBuild* bs = wtile_builds<WT, AL>(&nb);
     const int64_t J = (K + kChunk - 1) / kChunk;
+    const double last_len = (double)(K - (J - 1) * kChunk);
+    const double hbm = (double)N * (double)K * sizeof(WT) / 6.2e6;
     double best = 0.0;
     *build = nullptr;
     for (int i = 0; i < nb; ++i) {
         const WtileBuild& b = bs[i];
         const double tiles = (double)((M + b.bm - 1) / b.bm) * (double)((N + b.bn - 1) / b.bn);
         if (tiles > 2.0e9) continue;
-        const double percu = (double)(((int64_t)tiles + 255) / 256);
-        const int nw = wtile_waves(b, J, percu > 2.0 && b.bm <= 16 ? 4 : percu > 1.0 && b.nwmax > 8 ? 8 : b.nwmax);
-        double resident = (double)(kWtileLds / wtile_lds(b, J, nw));
-        if (resident * nw > b.nwmax) resident = b.nwmax / nw > 0 ? b.nwmax / nw : 1;
-        if (resident > percu) resident = percu;
-        double share = resident * nw / 8.0;
-        if (share > 1.0) share = 1.0;
-        double us = percu * (1.5 / resident + (double)b.bm * b.bn * (double)K / (b.rate * 1000.0 * share));
-        const double hbm = (double)N * (double)K * sizeof(WT) / 6.2e6;
-        if (us < hbm) us = hbm + 0.05 * us;
-        if (!*build || us < best) {
-            best = us;
-            *build = &b;
-            *waves = nw;
+        const int percu = (int)(((int64_t)tiles + 255) / 256);
+        // wave counts: the fewest for each of the four smallest numbers of rounds; with one tile per CU a workgroup may
+        // bring sixteen waves, with more eight (and four where many tiles have 16 rows: one's folds hide behind the
+        // others, the 128256 x 4096 head at M = 16 305 -> 286 us)
+        const int most = percu > 2 && b.bm <= 16 ? 4 : percu > 1 && b.nwmax > 8 ? 8 : b.nwmax;
+        int64_t rounds = (J + most - 1) / most;
+        for (int tries = 0; tries < 4; ++tries, ++rounds) {
+            const int nw = (int)((J + rounds - 1) / rounds);
+            const int64_t lds = wtile_lds(b, J, nw);
+            if (lds > kWtileLds) continue;
+            int resident = (int)(kWtileLds / lds);
+            if (resident * nw > b.nwmax) resident = b.nwmax / nw > 0 ? b.nwmax / nw : 1;
+            if (resident > percu) resident = percu;
+            const double share = resident * nw > 8 ? resident * nw / 8.0 : 1.0;
+            const double path = (double)(rounds - 1) * kChunk + (J - (rounds - 1) * nw == 1 ? last_len : kChunk);
+            const double batches = (double)((percu + resident - 1) / resident);
+            double us = batches * (1.0 + (double)rounds * (0.3 + 1.7 / nw * (b.bm * b.bn / 4096.0)) + path * share * (double)(b.bm * b.bn) / (b.rate * 125.0));
+            if (us < hbm) us = hbm + 0.05 * us;
+            if (!*build || us < best) {
+                best = us;
+                *build = &b;
+                *waves = nw;
+            }
+            if (nw == 1) break;
         }
     }
-    return *build != nullptr;
+    if (!*build) return false;
+    if (AL && M > 64) {
+        const double t128 = (double)((M + 127) / 128) * (double)((N + 127) / 128);
+        if (t128 >= 512.0) {
+            const double rounds = (double)(((int64_t)t128 + 511) / 512);
+            if (rounds * 2.0 * 128.0 * 128.0 * (double)K / 175000.0 < 0.9 * best) return false;
+        }
+    }
+    return true;
+}
+
+// wtile_choose, remembered for the shapes a thread has used last (a serving loop launches the same few).
+template <typename WT, bool AL>
+bool wtile_plan(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
+    struct Entry {
+        int64_t M = 0, N = 0, K = 0;
+        const WtileBuild* build = nullptr;
+        int waves = 0;
+        bool ok = false;
+    };
+    constexpr int kEntries = 64;
+    static thread_local Entry seen[kEntries];
+    Entry& e = seen[(uint64_t)(M * 31 + N * 7 + K / 8) % kEntries];
+    if (e.M != M || e.N != N || e.K != K) {
+        e.ok = wtile_choose<WT, AL>(M, N, K, &e.build, &e.waves);
+        e.M = M;
+        e.N = N;
+        e.K = K;
+    }
+    *build = e.build;
+    *waves = e.waves;
+    return e.ok;
 }
 
 template <typename WT>
@@ -578,7 +628,7 @@ hipError_t launch_wtile_t(const float* x, const WT* w, const float* bias, float*
         if (!aligned) return hipErrorInvalidValue;
         int nb = 0;
         b = wtile_builds<WT, true>(&nb);                   // the 64 x 64 tile
-    } else if (!(aligned ? wtile_choose<WT, true>(M, N, K, &b, &nw) : wtile_choose<WT, false>(M, N, K, &b, &nw))) {
+    } else if (!(aligned ? wtile_plan<WT, true>(M, N, K, &b, &nw) : wtile_plan<WT, false>(M, N, K, &b, &nw))) {
         return hipErrorInvalidValue;
     }
     const int64_t tm = (M + b->bm - 1) / b->bm, tn = (N + b->bn - 1) / b->bn;
