@@ -504,15 +504,15 @@ __global__ void __launch_bounds__(256) attn_partials_kernel(AttnArgs a) {
     }
 }
 
-// One 16-byte global -> LDS DMA per lane (lane l writes LDS [lds_base + 16 l, +16)).  M0 is saved and
-// restored and never read in the cycle after a write.
+// One 16-byte global -> LDS DMA per lane (lane l writes LDS [lds_base + 16 l, +16)), non-temporal: key and value rows are
+// read once, in whole 128-byte lines.  M0 is saved and restored and never read in the cycle after a write.
 __device__ __forceinline__ void attn_dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
     uint32_t saved;
     asm volatile(
         "s_mov_b32 %0, m0\n\t"
         "s_mov_b32 m0, %2\n\t"
         "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %3\n\t"
+        "global_load_lds_dwordx4 %1, %3 nt\n\t"
         "s_mov_b32 m0, %0\n\t"
         : "=&s"(saved)
         : "v"(voff), "s"(lds_base), "s"(sbase)
