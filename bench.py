@@ -547,29 +547,30 @@ def trace_summary(path, args):
 
 def attn_trace_summary(path):
     """Per-configuration kernel durations from a rocprofv3 kernel trace of 'bench.py --attention'.
-    Each configuration makes 5 + 5 * 50 + 1 calls, in ATTN_CONFIGS order; a call is three or four
-    kernels (the per-row maximum is its own kernel only for some shapes) and starts with the
-    scores kernel."""
+    Each configuration makes 5 + 5 * 50 + 1 calls, in ATTN_CONFIGS order; a call starts with the
+    scores kernel (a short cache's with the fused one), and the per-row maximum is its own kernel
+    only for some shapes."""
     rows = [r for r in _csv_rows(path) if "attn_" in r["Kernel_Name"]]
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
     dur = lambda r: (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
     calls = []
     for r in rows:
-        if re.search(r"attn_scores\d?_", r["Kernel_Name"]) or not calls:
+        if re.search(r"attn_(scores\d?|fused)_", r["Kernel_Name"]) or not calls:
             calls.append([])
         calls[-1].append(r)
     per = 5 + 5 * 50 + 1
     print(f"dispatches of the attention kernels: {len(rows)} in {len(calls)} calls")
-    print(f"{'config':22s} {'scores_us':>10s} {'max_us':>8s} {'partials_us':>12s} {'fold_us':>8s} {'sum_us':>8s} {'KV TB/s':>8s}")
+    print(f"{'config':22s} {'scores_us':>10s} {'max_us':>8s} {'values_us':>10s} {'fold_us':>8s} {'sum_us':>8s} {'KV TB/s':>8s}")
     for c, (name, B, H, Hkv, Lmax, D) in enumerate(ATTN_CONFIGS):
         timed = calls[c * per:(c + 1) * per][5:5 + 5 * 50]
         avg = {}
-        for key in ("scores", "max", "partials", "fold"):
-            d = [sum(dur(r) for r in call if re.search(rf"attn_{key}\d?_", r["Kernel_Name"])) for call in timed]
+        for key, name_re in (("scores", r"attn_scores\d?_"), ("max", "attn_max_"), ("fold", "attn_fold_"),
+                             ("values", "attn_(values|partials|fused)_")):
+            d = [sum(dur(r) for r in call if re.search(name_re, r["Kernel_Name"])) for call in timed]
             avg[key] = sum(d) / len(d)
         tot = sum(avg.values())
         kvb = 2 * B * Hkv * Lmax * D * 2
-        print(f"{name:22s} {avg['scores']:10.2f} {avg['max']:8.2f} {avg['partials']:12.2f} {avg['fold']:8.2f} "
+        print(f"{name:22s} {avg['scores']:10.2f} {avg['max']:8.2f} {avg['values']:10.2f} {avg['fold']:8.2f} "
               f"{tot:8.2f} {kvb / (tot * 1e-6) / 1e12:8.3f}")
 
 

@@ -454,6 +454,9 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
     // step covers K (J == 16); the slab-streaming kernels elsewhere (they measure faster
     // once x must be re-read from LDS every step)
     const bool ktile_ok = fast_ok && M <= kDecodeMaxM;
+    // The classes from here on name what rg_plan reports and what a forced launch with other
+    // overrides starts from; a default launch of M > 8 runs the wave tiles instead
+    // (takes_wave_tile), so the figures below compare the classes' own kernels.
     // ktile from M = 9 on; for 5 <= M <= 8 only where its 16 x 16 tiles are many (measured:
     // the streaming decode kernel is faster on the narrow layers there)
     const bool ktile_pref = M > 8 || (M > 4 && ceil_div(N, 16) >= 384);

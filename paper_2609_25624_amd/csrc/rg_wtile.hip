@@ -1,5 +1,6 @@
 // Wave-tile kernel for the fused-upcast linear layer (gfx950): the default for M > 8, for FP32
-// weights at M > 4, and for every K or alignment the 16-byte kernels do not take.
+// weights at M > 4 (both except where many 128 x 128 tiles of a short K lead, wtile_choose), and
+// for every K or alignment the 16-byte kernels do not take.
 //
 // Same order as every kernel of the library (include/rg.h, RG-ORDER-1; paper: Design,
 // eq. 2 and rules R1-R4): 256-wide K segments, each a chain of fmaf from +0 in ascending
@@ -531,18 +532,19 @@ int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
     return (int64_t)nw * kDepth * b.slab + (J > nw ? (int64_t)b.bm * b.bn * 4 : 0);
 }
 
-// Tile and waves for a shape: the least estimated time over the builds and a few wave counts each, a function of
-// (M, N, K), the weight type and the alignment.  A wave runs at an eighth of the build's rate; a workgroup of nw
-// waves takes as long as the wave with the most k (`path`: whole rounds of segments, a short last segment alone in
-// its round counted as short), plus 1 us for its first slabs and per round 0.3 us and the fold, which its threads share; a CU works off ceil(tiles / 256) tiles, as many at
-// a time as its eight wave slots and LDS hold (builds of sixteen waves share the slots), and never faster than
-// HBM streams W (6.2 GB per ms).  So 1536 = 6 segments run on 2 waves, four workgroups per CU, not on 6 waves with
-// two slots empty (2048 x 16384 x 1536 1472 -> RG_1536 us).
+// Tile and waves for a shape: the least estimated time over the builds and a few wave counts each, a
+// function of (M, N, K), the weight type and the alignment.  A wave runs at an eighth of the build's
+// rate; a workgroup of nw waves takes as long as the wave with the most k (`path`: whole rounds of
+// segments, a short last segment alone in its round counted as short), plus 1 us for its first slabs and
+// per round 0.3 us and the fold, which its threads share; a CU works off ceil(tiles / 256) tiles, as many
+// at a time as its eight wave slots and LDS hold (builds of sixteen waves share the slots), and never
+// faster than HBM streams W (6.2 GB per ms).  So 1536 = 6 segments run on 2 waves, four workgroups per
+// CU, not on 6 waves with two slots empty (2048 x 16384 x 1536 1472 -> 1116 us).
 //
-// Returns false where the 128 x 128 register tiles are the better ones: at least 512 of them, and their own time
-// (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is pessimistic by that much where
-// tiles are many (2048 x 16384: K = 1024 767 against 785 us, K = 2048 1481 against 1532; from K = 8192 on the wave
-// tiles lead: 2048 x 57344 x 8192 20.8 against 21.8 ms).
+// Returns false where the 128 x 128 register tiles are the better ones: at least 512 of them, and their
+// own time (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is
+// pessimistic by that much where tiles are many (2048 x 16384: K = 1024 767 against 785 us, K = 2048 1481
+// against 1532; from K = 8192 on the wave tiles lead: 2048 x 57344 x 8192 20.8 against 21.8 ms).
 template <typename WT, bool AL>
 bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
     int nb = 0;
@@ -557,9 +559,9 @@ bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int
         const double tiles = (double)((M + b.bm - 1) / b.bm) * (double)((N + b.bn - 1) / b.bn);
         if (tiles > 2.0e9) continue;
         const int percu = (int)(((int64_t)tiles + 255) / 256);
-        // wave counts: the fewest for each of the four smallest numbers of rounds; with one tile per CU a workgroup may
-        // bring sixteen waves, with more eight (and four where many tiles have 16 rows: one's folds hide behind the
-        // others, the 128256 x 4096 head at M = 16 305 -> 286 us)
+        // wave counts: the fewest for each of the four smallest numbers of rounds; with one tile per CU a
+        // workgroup may bring sixteen waves, with more eight (and four where many tiles have 16 rows: one's
+        // folds hide behind the others, the 128256 x 4096 head at M = 16 305 -> 286 us)
         const int most = percu > 2 && b.bm <= 16 ? 4 : percu > 1 && b.nwmax > 8 ? 8 : b.nwmax;
         int64_t rounds = (J + most - 1) / most;
         for (int tries = 0; tries < 4; ++tries, ++rounds) {
@@ -572,7 +574,9 @@ bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int
             const double share = resident * nw > 8 ? resident * nw / 8.0 : 1.0;
             const double path = (double)(rounds - 1) * kChunk + (J - (rounds - 1) * nw == 1 ? last_len : kChunk);
             const double batches = (double)((percu + resident - 1) / resident);
-            double us = batches * (1.0 + (double)rounds * (0.3 + 1.7 / nw * (b.bm * b.bn / 4096.0)) + path * share * (double)(b.bm * b.bn) / (b.rate * 125.0));
+            const double tile = (double)(b.bm * b.bn);
+            double us = batches * (1.0 + (double)rounds * (0.3 + 1.7 / nw * (tile / 4096.0)) +
+                                   path * share * tile / (b.rate * 125.0));
             if (us < hbm) us = hbm + 0.05 * us;
             if (!*build || us < best) {
                 best = us;
