@@ -13,14 +13,15 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-ALIGNED = [(9, 32, 264), (17, 2057, 1288), (17, 12458, 264), (33, 19492, 264), (17, 24804, 264), (33, 22129, 264),
-           (33, 27340, 264), (49, 14987, 264), (49, 20592, 264), (49, 24637, 264), (33, 29519, 520), (33, 22313, 520),
-           (129, 20954, 264), (49, 29065, 520), (100, 16597, 264), (100, 21828, 264), (100, 26152, 264),
-           (57, 29759, 520), (10, 70, 8), (333, 1000, 24), (65, 130, 4360)]
-ALIGNED_F32 = [(5, 33, 264), (9, 33, 260), (17, 2055, 1288), (17, 18553, 264), (17, 21688, 268), (17, 18609, 520),
-               (33, 24923, 264), (33, 20900, 520), (33, 27095, 520), (65, 130, 4364)]
-ANY = [(1, 31, 1), (1, 28970, 263), (3, 1000, 1001), (9, 20555, 3), (17, 26667, 5), (100, 9427, 7), (100, 16491, 31),
-       (47, 300, 4099), (8, 77, 513)]
+# one shape per build, from 64 x 64 down to 16 x 16, then K below a slab, long K and many short rows
+ALIGNED = [(57, 28818, 776), (49, 12370, 1288), (49, 22599, 776), (49, 8452, 1288), (49, 14341, 1288), (41, 30135, 776),
+           (33, 11110, 1288), (33, 27477, 776), (49, 13426, 776), (49, 10663, 776), (25, 4445, 2056), (17, 24777, 776),
+           (17, 9299, 1288), (17, 4149, 2056), (9, 24770, 776), (17, 6361, 776), (17, 2055, 2056), (9, 32, 264),
+           (10, 70, 8), (333, 1000, 24), (65, 130, 4360), (129, 20954, 264), (17, 2057, 1288)]
+ALIGNED_F32 = [(33, 14762, 1288), (33, 10921, 1288), (33, 7053, 1288), (17, 10506, 1288), (17, 6148, 1288), (5, 6361, 2056),
+               (5, 4639, 1288), (5, 33, 264), (9, 33, 260), (17, 21688, 268), (65, 130, 4364)]
+ANY = [(33, 5753, 1289), (17, 6160, 1289), (17, 6351, 775), (9, 2055, 1289), (1, 4231, 2061), (1, 31, 263), (1, 31, 1),
+       (3, 1000, 1001), (9, 20555, 3), (100, 16491, 31), (47, 300, 4099), (8, 77, 513)]
 
 
 def _inputs(M, N, K, f32, seed):
