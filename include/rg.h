@@ -69,14 +69,15 @@ typedef enum {
     RG_ERR_ALIAS = 6     /* y overlaps x or W */
 } rg_status;
 
-/* Kernel ids reported by rg_plan (scheduling only; the order is the same).  A shape's id names its class:
- * the kernel a launch forced with rg_linear_set_launch runs.  Default launches (no override) of the
- * classes GENERIC, and SKINNY, KTILE, WTILE and TILED with M > 8 (FP32 weights: M > 4), run the wave-tile kernel,
- * whose output tile (8 x 16 to 64 x 64) and waves are a function of M, N, K, the weight type and the alignment. */
+/* Kernel ids reported by rg_plan (scheduling only; the order is the same).  Default launches (no
+ * override) run GEMV or SKINNY for M <= 8 (FP32 weights: STREAM for M <= 4) and WTILE for larger M and for every
+ * K or alignment those do not take, but for the shapes TILED's 128 x 128 tiles are better at; the others run
+ * when forced, in launches with overrides, or where K is beyond what these take. */
 typedef enum {
     RG_KERNEL_GENERIC = 0,   /* one thread per output; any K, any alignment */
-    RG_KERNEL_DECODE = 1,    /* M <= 4 (or K < 4096 up to M = 64): streaming skinny GEMM, x in registers */
-    RG_KERNEL_TILED = 2,     /* larger M: register-tiled kernel, whole K per workgroup */
+    RG_KERNEL_DECODE = 1,    /* M <= 64: streaming skinny GEMM, x in registers, slices of at most 4 rows */
+    RG_KERNEL_TILED = 2,     /* register-tiled kernel, whole K per workgroup (the default for many
+                                128 x 128 tiles of a short K) */
     RG_KERNEL_DECODE_XS = 3, /* M == 1 (when forced, or where the skinny kernel's x does not fit its
                                 registers): streaming GEMV with x streamed through LDS beside W */
     RG_KERNEL_GEMV = 4,      /* M == 1, K % 256 == 0, K >= 4096 (the default for K == 4096 with
@@ -84,14 +85,12 @@ typedef enum {
                                 does not fit): 32 KB W bursts, whole rows per wave */
     RG_KERNEL_STREAM = 5,    /* M <= 4: 8-row blocks of W streamed through LDS, one chain per lane
                                 (FP32 weights by default; BF16 weights when forced) */
-    RG_KERNEL_KTILE = 6,     /* 16 < M <= 64 (any M when forced): 4 x 4 register tiles, K segments
-                                shared out over thread groups */
-    RG_KERNEL_SKINNY = 7,    /* M <= 16, and narrow layers to M = 64: waves of 16 W rows x 4
-                                segments, x of a segment shared by 16 lanes through DPP row
-                                broadcasts, slices of 1, 2, 4 or 8 rows of x */
-    RG_KERNEL_WTILE = 8      /* 32 < M <= 64 on wide layers (forced: 64 x 64 output tiles): each wave the
-                                whole tile for one segment at a time (8 x 8 chains per lane), its
-                                own LDS slabs, the partials of a round folded in segment order */
+    RG_KERNEL_KTILE = 6,     /* 4 x 4 register tiles, K segments shared out over thread groups */
+    RG_KERNEL_SKINNY = 7,    /* waves of 16 W rows x 4 segments, x of a segment shared by 16 lanes
+                                through DPP row broadcasts, slices of 1, 2, 4 or 8 rows of x */
+    RG_KERNEL_WTILE = 8      /* output tiles of 8 x 16 to 64 x 64 (64 x 64 when forced): each wave the
+                                whole tile for one segment at a time, its own LDS slabs, the
+                                partials of a round folded in segment order; any K, any alignment */
 } rg_kernel_id;
 
 /* Scheduling overrides for the determinism tests.  0 in a field = planner
@@ -127,9 +126,8 @@ typedef struct {
     int32_t reserved;
 } rg_launch_t;
 
-/* The class of a shape and its kernel's schedule (on a 256-CU MI355X) under the current overrides; where
- * a default launch takes the wave-tile kernel (see rg_kernel_id) the fields from waves_per_wg on are the
- * class's own kernel's. */
+/* What rg_linear will do for a shape (on a 256-CU MI355X) with 16-byte aligned x and W under the current
+ * overrides. */
 typedef struct {
     int32_t order_id;      /* RG_ORDER_ID */
     int32_t chunk;         /* C = 256 */
@@ -140,7 +138,8 @@ typedef struct {
     int32_t depth;         /* decode: pipeline depth; tiled 128 x 128: waves per SIMD (2 or 3);
                               ktile: 2 = 4 x 4, 3 = 4 x 8 outputs per thread */
     int32_t rows_per_round;/* decode: W rows per workgroup round; skinny: 16 */
-    int32_t tile_m, tile_n;/* tiled, ktile, wtile: output tile; skinny: rows of x per slice, 16 W rows */
+    int32_t tile_m, tile_n;/* tiled, ktile, wtile: output tile (grid_wgs of them); skinny: rows of x
+                              per slice, 16 W rows */
 } rg_plan_t;
 
 /*
@@ -179,8 +178,9 @@ int rg_linear_bias(const float* x, const uint16_t* w_bf16, const float* bias, fl
  *   w_f32  device pointer, float32 [N][K], 4-byte aligned
  *   y      device pointer, float32 [M][N], 4-byte aligned, must not overlap x or W
  * Kernels: RG_KERNEL_STREAM for M <= 4 with 16-byte aligned x and W and K % 4 == 0, the
- * wave-tile kernel otherwise; ktile, tiled, wtile and generic when forced.  Errors, streams and ownership as rg_linear; the same
- * rg_linear_set_launch overrides apply (decode, decode_xs and gemv cannot be
+ * wave-tile kernel otherwise, but for many 128 x 128 tiles of a short K (tiled); ktile, tiled,
+ * wtile and generic when forced.  Errors, streams and ownership as rg_linear; the same
+ * rg_linear_set_launch overrides apply (decode, decode_xs, gemv and skinny cannot be
  * forced here: RG_ERR_RANGE).
  */
 int rg_linear_f32w(const float* x, const float* w_f32, float* y, int64_t M, int64_t N, int64_t K, void* stream);

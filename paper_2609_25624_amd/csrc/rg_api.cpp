@@ -73,6 +73,8 @@ struct Plan {
     int spw = 0;         // skinny: segment groups per wave
     int jp = 0;          // skinny: row stride of the LDS partials
     int64_t groups = 0;  // skinny: row-group walkers per slice
+    int wbuild = 0;      // wtile: index of its build, and whether that is one for aligned calls
+    bool waligned = true;
 };
 
 // Largest decode pipeline depth whose LDS ring fits for a wave count.
@@ -231,9 +233,10 @@ bool ktile_schedule(int64_t M, int64_t N, int64_t K, const rg_launch_t& o, Plan*
     return true;
 }
 
-// Wave-tile kernel: 64 x 64 tiles, one per workgroup of four waves (eight when forced: more
-// segments in flight per tile, one workgroup per CU); the grid order applies.
-bool wtile_schedule(int64_t M, int64_t N, const rg_launch_t& o, Plan* p) {
+// Wave-tile kernel, forced or where overrides leave it its class: 64 x 64 tiles, one per workgroup of four waves
+// (eight when asked for: more segments in flight per tile, one workgroup per CU); the grid order applies.  K beyond
+// its 32-bit offsets: the 64 x 64 tiles of the register-tiled kernel.
+bool wtile_schedule(int64_t M, int64_t N, int64_t K, const rg_launch_t& o, Plan* p) {
     if ((o.waves_per_wg != 0 && o.waves_per_wg != 4 && o.waves_per_wg != 8) || o.grid_wgs != 0 || o.depth != 0 ||
         (o.tile_n != 0 && o.tile_n != 64) || o.slice_m != 0)
         return false;
@@ -244,6 +247,13 @@ bool wtile_schedule(int64_t M, int64_t N, const rg_launch_t& o, Plan* p) {
     p->grid = (int)tiles;
     p->nw = o.waves_per_wg > 0 ? o.waves_per_wg : 4;
     p->depth = 0;
+    p->wbuild = 0;
+    p->waligned = true;
+    p->kernel = RG_KERNEL_WTILE;
+    if (K > rg::kWtileMaxK) {
+        p->kernel = RG_KERNEL_TILED;
+        p->nw = 4;
+    }
     return true;
 }
 
@@ -440,8 +450,64 @@ void generic_schedule(int64_t M, int64_t N, const rg_launch_t& o, Plan* p) {
     p->nw = 4;
 }
 
+// No override at all: the launch is the planner's to choose.
+bool is_default(const rg_launch_t& o) {
+    return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.grid_order == 0 &&
+           o.tile_n == 0 && o.slice_m == 0;
+}
+
+// rg::wtile_choose, remembered for the shapes a thread has used last (a serving loop launches the same few).
+rg::WtileChoice wave_tile(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
+    struct Entry {
+        int64_t M = 0, N = 0, K = 0;
+        bool f32 = false, aligned = false;
+        rg::WtileChoice c;
+    };
+    constexpr int kEntries = 64;
+    static thread_local Entry seen[kEntries];
+    Entry& e = seen[(uint64_t)(M * 31 + N * 7 + K / 8) % kEntries];
+    if (e.M != M || e.N != N || e.K != K || e.f32 != f32 || e.aligned != aligned) {
+        e.c = rg::wtile_choose(M, N, K, f32, aligned);
+        e.M = M;
+        e.N = N;
+        e.K = K;
+        e.f32 = f32;
+        e.aligned = aligned;
+    }
+    return e.c;
+}
+
+// The shapes a default launch runs on the wave-tile kernel (tile and waves by the rule in rg_wtile.h): more than
+// `own_max_m` rows of x (BF16 weights 8, FP32 weights 4), and every K or alignment the 16-byte kernels do not take.
+// Measured against the kernel each shape ran on before, us, interleaved on one MI355X (BF16 weights; before -> now):
+//   skinny, M > 8    QKV 6144 x 4096 at M = 16 / 24 / 64: 23.5 / 41.8 / 73.6 -> 20.2 / 26.8 / 46;
+//                    down 4096 x 14336: 60.6 / 168 / 219 -> 46 / 85 / 109; at M = 8 the skinny
+//                    kernel stays (QKV 17.4 against 16.9, gate+up 50.8 against 57)
+//   ktile, wtile     gate+up 28672 x 4096 at M = 24 / 64: 143 / 220 -> 91 / 183
+//   tiled            gate+up at M = 333: 1118 -> 1036; 8192 x 28672 at M = 2048: 10650 -> 10280
+//   generic          one thread per output, a serial chain of 2-byte loads each: 2999 x 1003
+//                    at M = 5: 255 -> 12
+bool wave_tile_plan(int64_t M, int64_t N, int64_t K, bool f32, bool fast_ok, int64_t own_max_m, const rg_launch_t& o,
+                    Plan* p) {
+    if (!is_default(o) || K > rg::kWtileMaxK || (fast_ok && M <= own_max_m)) return false;
+    const rg::WtileChoice c = wave_tile(M, N, K, f32, fast_ok);
+    if (!c.ok) return false;
+    int nb = 0;
+    const rg::WtileBuild& b = rg::wtile_builds(f32, fast_ok, &nb)[c.build];
+    p->kernel = RG_KERNEL_WTILE;
+    p->wbuild = c.build;
+    p->waligned = fast_ok;
+    p->nw = c.waves;
+    p->tile_m = b.bm;
+    p->tile_n = b.bn;
+    p->grid = (int)(ceil_div(M, b.bm) * ceil_div(N, b.bn));
+    p->reverse = 0;
+    return true;
+}
+
 // The planner.  `fast_ok`: x and W 16-byte aligned and K % 8 == 0.
 int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& o, Plan* p) {
+    if (wave_tile_plan(M, N, K, false, fast_ok, 8, o, p)) return RG_OK;
     const int64_t J = ceil_div(K, rg::kChunk);
     int want = RG_KERNEL_GENERIC;
     // decode kernels take x in slices of mt <= 4 rows (several slices for M > 4)
@@ -454,9 +520,8 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
     // step covers K (J == 16); the slab-streaming kernels elsewhere (they measure faster
     // once x must be re-read from LDS every step)
     const bool ktile_ok = fast_ok && M <= kDecodeMaxM;
-    // The classes from here on name what rg_plan reports and what a forced launch with other
-    // overrides starts from; a default launch of M > 8 runs the wave tiles instead
-    // (takes_wave_tile), so the figures below compare the classes' own kernels.
+    // For M > 8 the choice from here on is for launches with overrides and for what wave_tile_plan leaves, so
+    // the figures below compare these kernels with each other.
     // ktile from M = 9 on; for 5 <= M <= 8 only where its 16 x 16 tiles are many (measured:
     // the streaming decode kernel is faster on the narrow layers there)
     const bool ktile_pref = M > 8 || (M > 4 && ceil_div(N, 16) >= 384);
@@ -518,7 +583,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
                              : (decode_ok ? RG_KERNEL_DECODE : (tiled_ok ? RG_KERNEL_TILED : RG_KERNEL_GENERIC));
     }
     if (want == RG_KERNEL_WTILE) {
-        if (wtile_schedule(M, N, o, p)) return RG_OK;
+        if (wtile_schedule(M, N, K, o, p)) return RG_OK;
         if (forced) return RG_ERR_RANGE;
         want = p->kernel = RG_KERNEL_KTILE;   // overrides the wave-tile kernel does not take
     }
@@ -558,9 +623,10 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
 
 // The planner for FP32 weights (rg_linear_f32w).  `fast_ok`: x and W 16-byte
 // aligned and K % 4 == 0.  M <= 4: the FP32-weight streaming kernel; then the
-// same ktile / tiled / generic kernels as BF16 weights (their weight loads are
-// templated on the element type).
+// wave tiles, and for launches with overrides the same ktile / tiled / generic
+// kernels as BF16 weights (their weight loads are templated on the element type).
 int make_plan_f32w(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& o, Plan* p) {
+    if (wave_tile_plan(M, N, K, true, fast_ok, 4, o, p)) return RG_OK;
     int want = RG_KERNEL_GENERIC;
     if (fast_ok && M <= 4) want = RG_KERNEL_STREAM;
     else if (fast_ok && M <= kDecodeMaxM) want = RG_KERNEL_KTILE;
@@ -579,7 +645,7 @@ int make_plan_f32w(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launc
     p->mslices = 1;
     if (want == RG_KERNEL_STREAM) return stream_schedule(M, N, o, p) ? RG_OK : RG_ERR_RANGE;
     if (want == RG_KERNEL_KTILE) return ktile_schedule(M, N, K, o, p) ? RG_OK : RG_ERR_RANGE;
-    if (want == RG_KERNEL_WTILE) return wtile_schedule(M, N, o, p) ? RG_OK : RG_ERR_RANGE;
+    if (want == RG_KERNEL_WTILE) return wtile_schedule(M, N, K, o, p) ? RG_OK : RG_ERR_RANGE;
     if (want == RG_KERNEL_TILED) return tiled_schedule(M, N, o, p);
     generic_schedule(M, N, o, p);
     return RG_OK;
@@ -600,34 +666,6 @@ int validate_launch(const rg_launch_t& c) {
 rg_launch_t current_launch() {
     std::lock_guard<std::mutex> lk(g_launch_mu);
     return g_launch;
-}
-
-// No override at all: the launch is the planner's to choose.
-bool is_default(const rg_launch_t& o) {
-    return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.grid_order == 0 &&
-           o.tile_n == 0 && o.slice_m == 0;
-}
-
-// The shapes a default launch runs on the wave-tile kernel (tile and waves by the rule in
-// rg_wtile.hip) in place of the class's own kernel, which forced launches still run.
-// Measured against the class's kernel, us, interleaved on one MI355X (BF16 weights; before -> now):
-//   skinny, M > 8    QKV 6144 x 4096 at M = 16 / 24 / 64: 23.5 / 41.8 / 73.6 -> 20.2 / 26.8 / 46;
-//                    down 4096 x 14336: 60.6 / 168 / 219 -> 46 / 85 / 109; at M = 8 the skinny
-//                    kernel stays (QKV 17.4 against 16.9, gate+up 50.8 against 57)
-//   ktile, wtile     gate+up 28672 x 4096 at M = 24 / 64: 143 / 220 -> 91 / 183
-//   tiled            gate+up at M = 333: 1118 -> 1036; 8192 x 28672 at M = 2048: 10650 -> 10280
-//   generic          one thread per output, a serial chain of 2-byte loads each: 2999 x 1003
-//                    at M = 5: 255 -> 12
-bool takes_wave_tile(const Plan& p, int64_t M, int64_t K, int64_t own_max_m, const rg_launch_t& o) {
-    if (!is_default(o) || K > rg::kWtileMaxK) return false;
-    switch (p.kernel) {
-        case RG_KERNEL_GENERIC: return true;
-        case RG_KERNEL_SKINNY:
-        case RG_KERNEL_KTILE:
-        case RG_KERNEL_WTILE:
-        case RG_KERNEL_TILED: return M > own_max_m;
-        default: return false;
-    }
 }
 
 // Map a launch result to an rg_status, remembering the HIP code for rg_last_hip_error.
@@ -729,16 +767,11 @@ int linear_impl(const float* x, const uint16_t* w, const float* bias, float* y, 
     if (dc != RG_OK) return dc;
     const bool fast_ok = (K % 8) == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)w & 15) == 0;
     Plan p;
-    const rg_launch_t o = current_launch();
-    const int s = make_plan(M, N, K, fast_ok, o, &p);
+    const int s = make_plan(M, N, K, fast_ok, current_launch(), &p);
     if (s != RG_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();   // drop an error left by an unrelated earlier HIP call on this thread
     hipError_t e = hipSuccess;
-    if (takes_wave_tile(p, M, K, 8, o)) {
-        e = rg::launch_wtile(x, w, bias, y, M, N, K, 0, 0, st);
-        if (e != hipErrorInvalidValue) return hip_status(e);   // not its shape: the class's kernel
-    }
     if (p.kernel == RG_KERNEL_GEMV) {
         rg::GemvArgs a;
         a.x = x;
@@ -804,9 +837,9 @@ int linear_impl(const float* x, const uint16_t* w, const float* bias, float* y, 
         e = launch_stream(x, w, bias, y, M, N, K, p, false, st);
     } else if (p.kernel == RG_KERNEL_KTILE) {
         e = rg::launch_ktile(x, w, bias, y, M, N, K, p.tile_m, p.tile_n, 64 * p.nw, p.cn, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_WTILE && K <= rg::kWtileMaxK) {
-        e = rg::launch_wtile(x, w, bias, y, M, N, K, p.nw, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_TILED || p.kernel == RG_KERNEL_WTILE) {   // (wtile: K beyond its offsets)
+    } else if (p.kernel == RG_KERNEL_WTILE) {
+        e = rg::launch_wtile(x, w, bias, y, M, N, K, p.wbuild, p.nw, p.waligned, p.reverse, st);
+    } else if (p.kernel == RG_KERNEL_TILED) {
         e = rg::launch_tiled(x, w, bias, y, M, N, K, p.tile_m, p.tile_n, p.depth, p.reverse, st);
     } else {
         e = rg::launch_generic(x, w, bias, y, M, N, K, p.grid, p.reverse, st);
@@ -825,23 +858,18 @@ int linear_f32w_impl(const float* x, const float* w, float* y, int64_t M, int64_
     if (dc != RG_OK) return dc;
     const bool fast_ok = (K % 4) == 0 && ((uintptr_t)x & 15) == 0 && ((uintptr_t)w & 15) == 0;
     Plan p;
-    const rg_launch_t o = current_launch();
-    const int s = make_plan_f32w(M, N, K, fast_ok, o, &p);
+    const int s = make_plan_f32w(M, N, K, fast_ok, current_launch(), &p);
     if (s != RG_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     (void)hipGetLastError();
     hipError_t e = hipSuccess;
-    if (takes_wave_tile(p, M, K, 4, o)) {
-        e = rg::launch_wtile(x, w, nullptr, y, M, N, K, 0, 0, st);
-        if (e != hipErrorInvalidValue) return hip_status(e);
-    }
     if (p.kernel == RG_KERNEL_STREAM) {
         e = launch_stream(x, w, nullptr, y, M, N, K, p, true, st);
     } else if (p.kernel == RG_KERNEL_KTILE) {
         e = rg::launch_ktile(x, w, nullptr, y, M, N, K, p.tile_m, p.tile_n, 64 * p.nw, p.cn, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_WTILE && K <= rg::kWtileMaxK) {
-        e = rg::launch_wtile(x, w, nullptr, y, M, N, K, p.nw, p.reverse, st);
-    } else if (p.kernel == RG_KERNEL_TILED || p.kernel == RG_KERNEL_WTILE) {   // (wtile: K beyond its offsets)
+    } else if (p.kernel == RG_KERNEL_WTILE) {
+        e = rg::launch_wtile(x, w, nullptr, y, M, N, K, p.wbuild, p.nw, p.waligned, p.reverse, st);
+    } else if (p.kernel == RG_KERNEL_TILED) {
         e = rg::launch_tiled(x, w, nullptr, y, M, N, K, p.tile_m, p.tile_n, p.depth, p.reverse, st);
     } else {
         e = rg::launch_generic(x, w, nullptr, y, M, N, K, p.grid, p.reverse, st);

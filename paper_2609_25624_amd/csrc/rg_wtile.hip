@@ -60,20 +60,7 @@ struct WtileArgs {
     int reverse;          // 1: reversed workgroup-to-tile mapping
 };
 
-constexpr int kDepth = 2;             // slabs of a wave's LDS ring: one computed, one in flight
 constexpr int kGroupM = 8;            // m tiles that share an n tile before the next n tile (large M)
-constexpr int kWtileLds = 160 * 1024;
-
-// LDS bytes of one slab of a wave: x then W, each padded to whole 1 KB DMA instructions.
-template <int BM, int BN, int KT, typename WT>
-struct Slab {
-    static constexpr int PX = KT / 4;                         // 16-byte pieces of an x row
-    static constexpr int PW = KT * (int)sizeof(WT) / 16;      // ... of a W row
-    static constexpr int XI = (BM * PX + 63) / 64;            // DMA instructions for x
-    static constexpr int WI = (BN * PW + 63) / 64;            // ... for W
-    static constexpr int WOFF = XI * 1024;
-    static constexpr int BYTES = (XI + WI) * 1024;
-};
 
 __device__ __forceinline__ uint32_t lds_addr32(const void* p) {
     return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)p);
@@ -144,9 +131,9 @@ __device__ __forceinline__ void widen2(uint32_t d, float& even_k, float& odd_k) 
 template <int LM, int TM, int TN, int KT, int NWMAX, int WPE, int KB, typename WT, bool AL>
 __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
     constexpr int LN = 64 / LM, BM = LM * TM, BN = LN * TN;
-    using SL = Slab<BM, BN, KT, WT>;
+    using SL = WtileSlab<BM, BN, KT, WT>;
     constexpr int PX = SL::PX, PW = SL::PW, XI = SL::XI, WI = SL::WI;
-    constexpr int SLOT = SL::BYTES, RING = kDepth * SLOT;
+    constexpr int SLOT = SL::BYTES, RING = kWtileDepth * SLOT;
     constexpr bool BF = sizeof(WT) == 2;
     constexpr int NSL = kChunk / KT;                // slabs per segment
     constexpr int NB = KT / KB;                     // operand reads per slab
@@ -157,7 +144,7 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
                        : (NA % 3 == 0 && NA / 3 * 256 <= SLOT) ? NA / 3
                        : (NA % 4 == 0 && NA / 4 * 256 <= SLOT) ? NA / 4 : NA / 8;
     static_assert(QC >= 1 && NA % QC == 0 && QC * 256 <= SLOT, "fold pass");
-    static_assert(KT % KB == 0 && KB % 4 == 0 && kChunk % KT == 0 && kDepth == 2, "slab split");
+    static_assert(KT % KB == 0 && KB % 4 == 0 && kChunk % KT == 0 && kWtileDepth == 2, "slab split");
     extern __shared__ __attribute__((aligned(16))) uint8_t wt_lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -223,7 +210,7 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
     // the slab and are never multiplied.
     auto issue = [&](int s) {
         const int64_t k0 = slab_k(s);
-        const uint32_t slot = ring_base + (uint32_t)(s % kDepth * SLOT);
+        const uint32_t slot = ring_base + (uint32_t)(s % kWtileDepth * SLOT);
         const char* sx = xb + k0 * 4;
         const char* sw = wb + k0 * (int)sizeof(WT);
         if (k0 + KT <= K) {
@@ -291,7 +278,7 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
             dma_wait();
         } else {
             if (s < arrived || s >= S) return;
-            uint4* slot = reinterpret_cast<uint4*>(ring + s % kDepth * SLOT);
+            uint4* slot = reinterpret_cast<uint4*>(ring + s % kWtileDepth * SLOT);
 #pragma unroll
             for (int u = 0; u < XI; ++u) slot[64 * u + lane] = rx[AL ? 0 : u];
 #pragma unroll
@@ -378,10 +365,10 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
             const int nfull = len / KT;
             if (nfull > 0) {
                 arrive(s);
-                cur = read(ring + s % kDepth * SLOT, 0);
+                cur = read(ring + s % kWtileDepth * SLOT, 0);
             }
             for (int sl = 0; sl < nfull; ++sl, ++s) {
-                const uint8_t* slot = ring + s % kDepth * SLOT;
+                const uint8_t* slot = ring + s % kWtileDepth * SLOT;
                 // the other slot's reads are done: fill it with the next slab while this one is computed
                 if constexpr (AL) {
                     lds_wait();
@@ -396,7 +383,7 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
                         nxt = read(slot, b + 1);
                     } else {
                         arrive(s + 1);
-                        nxt = read(ring + (s + 1) % kDepth * SLOT, 0);
+                        nxt = read(ring + (s + 1) % kWtileDepth * SLOT, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     fma_ops(cur);
@@ -406,7 +393,7 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
             }
             if (nfull * KT < len) {                        // the short last slab of K
                 arrive(s);
-                const uint8_t* slot = ring + s % kDepth * SLOT;
+                const uint8_t* slot = ring + s % kWtileDepth * SLOT;
                 const int nq = (len - nfull * KT + 3) / 4;
                 for (int q = 0; q < nq; ++q) {
                     float4 ox[TM];
@@ -422,11 +409,11 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
         // chains per lane at a time
         const int nact = min(NW, J - t * NW);
         const bool last = t == rounds - 1;
-        float* part = reinterpret_cast<float*>(ring + (s + kDepth - 1) % kDepth * SLOT);
+        float* part = reinterpret_cast<float*>(ring + (s + kWtileDepth - 1) % kWtileDepth * SLOT);
         const float* pfull =
-            reinterpret_cast<const float*>(wt_lds + ((t + 1) * NSL + kDepth - 1) % kDepth * SLOT);
+            reinterpret_cast<const float*>(wt_lds + ((t + 1) * NSL + kWtileDepth - 1) % kWtileDepth * SLOT);
         const float* plast =
-            reinterpret_cast<const float*>(wt_lds + (t * NSL + last_slabs + kDepth - 1) % kDepth * SLOT);
+            reinterpret_cast<const float*>(wt_lds + (t * NSL + last_slabs + kWtileDepth - 1) % kWtileDepth * SLOT);
         const int nfold = last ? nact - 1 : nact;          // waves with whole segments this round
 #pragma unroll
         for (int ch = 0; ch < NA / QC; ++ch) {
@@ -478,181 +465,55 @@ __global__ void __launch_bounds__(64 * NWMAX, WPE) wtile_kernel(WtileArgs a) {
 
 namespace {
 
-// The builds: tile shape (LM, TM, TN, KT, NWMAX, WPE, KB) and `rate`, the multiply-adds per ns one CU
-// sustains on it with at least eight waves (measured on an MI355X: the slope between 512 and 1024
-// tiles at K = 4096).  Larger tiles run faster per multiply-add; smaller ones fill the CUs of a narrow layer.
-#define RG_WTILE_BF16(B)                                                            \
-    B(8, 8, 8, 16, 8, 2, 4, 161) /* 64 x 64 */ B(8, 8, 7, 16, 8, 2, 4, 158) /* 64 x 56 */ \
-    B(8, 8, 6, 16, 8, 2, 4, 152) /* 64 x 48 */ B(8, 8, 5, 16, 8, 2, 4, 151) /* 64 x 40 */ \
-    B(8, 7, 8, 16, 8, 2, 4, 156) /* 56 x 64 */ B(8, 6, 8, 16, 8, 2, 4, 148) /* 48 x 64 */ \
-    B(8, 6, 6, 16, 8, 2, 4, 144) /* 48 x 48 */ B(8, 5, 8, 16, 8, 2, 4, 131) /* 40 x 64 */ \
-    B(4, 8, 4, 32, 8, 2, 4, 145) /* 32 x 64 */ B(8, 4, 6, 32, 8, 2, 4, 134) /* 32 x 48 */ \
-    B(8, 4, 4, 32, 16, 4, 4, 126) /* 32 x 32 */ B(4, 6, 4, 32, 8, 2, 4, 134) /* 24 x 64 */ \
-    B(8, 3, 6, 32, 8, 2, 4, 115) /* 24 x 48 */ B(8, 3, 4, 32, 16, 4, 4, 107) /* 24 x 32 */ \
-    B(4, 4, 4, 32, 16, 4, 4, 120) /* 16 x 64 */ B(4, 4, 2, 32, 16, 4, 4, 111) /* 16 x 32 */ \
-    B(8, 2, 3, 32, 16, 4, 8, 94) /* 16 x 24 */ B(4, 4, 1, 32, 16, 4, 8, 94) /* 16 x 16 */
-#define RG_WTILE_F32(B)                                                             \
-    B(8, 8, 8, 16, 8, 2, 4, 144) /* 64 x 64 */ B(8, 8, 6, 16, 8, 2, 4, 137) /* 64 x 48 */ \
-    B(8, 8, 4, 16, 8, 2, 4, 128) /* 64 x 32 */ B(8, 4, 6, 16, 8, 2, 4, 110) /* 32 x 48 */ \
-    B(8, 4, 4, 16, 8, 2, 4, 107) /* 32 x 32 */ B(4, 4, 2, 32, 16, 4, 4, 70) /* 16 x 32 */ \
-    B(8, 2, 3, 32, 16, 4, 4, 72) /* 16 x 24 */ \
-    B(4, 4, 1, 32, 16, 4, 8, 71) /* 16 x 16 */
-#define RG_WTILE_ANY(B)                                                             \
-    B(8, 6, 4, 16, 8, 2, 4, 110) /* 48 x 32 */ B(8, 4, 4, 16, 8, 2, 4, 100) /* 32 x 32 */ \
-    B(4, 4, 2, 16, 8, 2, 4, 70) /* 16 x 32 */ B(4, 4, 1, 16, 16, 4, 4, 60) /* 16 x 16 */ \
-    B(4, 2, 2, 16, 16, 4, 4, 40) /* 8 x 32 */ B(4, 2, 1, 16, 16, 4, 4, 40) /* 8 x 16 */
+using WtileKernel = void (*)(WtileArgs);
 
-struct WtileBuild {
-    int bm, bn, slab, nwmax, rate;
-    void (*kernel)(WtileArgs);
-};
-
+// The kernels of wtile_builds, in its order.
 template <typename WT, bool AL>
-const WtileBuild* wtile_builds(int* count) {
-#define RG_B(LM, TM, TN, KT, NWMAX, WPE, KB, RATE)                                                                 \
-    {(LM) * (TM), 64 / (LM) * (TN), Slab<(LM) * (TM), 64 / (LM) * (TN), KT, WT>::BYTES, NWMAX, RATE,              \
-     wtile_kernel<LM, TM, TN, KT, NWMAX, WPE, KB, WT, AL>},
+const WtileKernel* wtile_kernels() {
+#define RG_B(LM, TM, TN, KT, NWMAX, WPE, KB, RATE) wtile_kernel<LM, TM, TN, KT, NWMAX, WPE, KB, WT, AL>,
     if constexpr (!AL) {
-        static const WtileBuild b[] = {RG_WTILE_ANY(RG_B)};
-        *count = (int)(sizeof b / sizeof b[0]);
-        return b;
+        static const WtileKernel k[] = {RG_WTILE_ANY(RG_B)};
+        return k;
     } else if constexpr (sizeof(WT) == 2) {
-        static const WtileBuild b[] = {RG_WTILE_BF16(RG_B)};
-        *count = (int)(sizeof b / sizeof b[0]);
-        return b;
+        static const WtileKernel k[] = {RG_WTILE_BF16(RG_B)};
+        return k;
     } else {
-        static const WtileBuild b[] = {RG_WTILE_F32(RG_B)};
-        *count = (int)(sizeof b / sizeof b[0]);
-        return b;
+        static const WtileKernel k[] = {RG_WTILE_F32(RG_B)};
+        return k;
     }
 #undef RG_B
 }
 
-int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
-    return (int64_t)nw * kDepth * b.slab + (J > nw ? (int64_t)b.bm * b.bn * 4 : 0);
-}
-
-// Tile and waves for a shape: the least estimated time over the builds and a few wave counts each, a
-// function of (M, N, K), the weight type and the alignment.  A wave runs at an eighth of the build's
-// rate; a workgroup of nw waves takes as long as the wave with the most k (`path`: whole rounds of
-// segments, a short last segment alone in its round counted as short), plus 1 us for its first slabs and
-// per round 0.3 us and the fold, which its threads share; a CU works off ceil(tiles / 256) tiles, as many
-// at a time as its eight wave slots and LDS hold (builds of sixteen waves share the slots), and never
-// faster than HBM streams W (6.2 GB per ms).  So 1536 = 6 segments run on 2 waves, four workgroups per
-// CU, not on 6 waves with two slots empty (2048 x 16384 x 1536 1472 -> 1116 us).
-//
-// Returns false where the 128 x 128 register tiles are the better ones: at least 512 of them, and their
-// own time (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is
-// pessimistic by that much where tiles are many (2048 x 16384: K = 1024 767 against 785 us, K = 2048 1481
-// against 1532; from K = 8192 on the wave tiles lead: 2048 x 57344 x 8192 20.8 against 21.8 ms).
-template <typename WT, bool AL>
-bool wtile_choose(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
-    int nb = 0;
-    const WtileBuild* bs = wtile_builds<WT, AL>(&nb);
-    const int64_t J = (K + kChunk - 1) / kChunk;
-    const double last_len = (double)(K - (J - 1) * kChunk);
-    const double hbm = (double)N * (double)K * sizeof(WT) / 6.2e6;
-    double best = 0.0;
-    *build = nullptr;
-    for (int i = 0; i < nb; ++i) {
-        const WtileBuild& b = bs[i];
-        const double tiles = (double)((M + b.bm - 1) / b.bm) * (double)((N + b.bn - 1) / b.bn);
-        if (tiles > 2.0e9) continue;
-        const int percu = (int)(((int64_t)tiles + 255) / 256);
-        // wave counts: the fewest for each of the four smallest numbers of rounds; with one tile per CU a
-        // workgroup may bring sixteen waves, with more eight (and four where many tiles have 16 rows: one's
-        // folds hide behind the others, the 128256 x 4096 head at M = 16 305 -> 286 us)
-        const int most = percu > 2 && b.bm <= 16 ? 4 : percu > 1 && b.nwmax > 8 ? 8 : b.nwmax;
-        int64_t rounds = (J + most - 1) / most;
-        for (int tries = 0; tries < 4; ++tries, ++rounds) {
-            const int nw = (int)((J + rounds - 1) / rounds);
-            const int64_t lds = wtile_lds(b, J, nw);
-            if (lds > kWtileLds) continue;
-            int resident = (int)(kWtileLds / lds);
-            if (resident * nw > b.nwmax) resident = b.nwmax / nw > 0 ? b.nwmax / nw : 1;
-            if (resident > percu) resident = percu;
-            const double share = resident * nw > 8 ? resident * nw / 8.0 : 1.0;
-            const double path = (double)(rounds - 1) * kChunk + (J - (rounds - 1) * nw == 1 ? last_len : kChunk);
-            const double batches = (double)((percu + resident - 1) / resident);
-            const double tile = (double)(b.bm * b.bn);
-            double us = batches * (1.0 + (double)rounds * (0.3 + 1.7 / nw * (tile / 4096.0)) +
-                                   path * share * tile / (b.rate * 125.0));
-            if (us < hbm) us = hbm + 0.05 * us;
-            if (!*build || us < best) {
-                best = us;
-                *build = &b;
-                *waves = nw;
-            }
-            if (nw == 1) break;
-        }
-    }
-    if (!*build) return false;
-    if (AL && M > 64) {
-        const double t128 = (double)((M + 127) / 128) * (double)((N + 127) / 128);
-        if (t128 >= 512.0) {
-            const double rounds = (double)(((int64_t)t128 + 511) / 512);
-            if (rounds * 2.0 * 128.0 * 128.0 * (double)K / 175000.0 < 0.9 * best) return false;
-        }
-    }
-    return true;
-}
-
-// wtile_choose, remembered for the shapes a thread has used last (a serving loop launches the same few).
-template <typename WT, bool AL>
-bool wtile_plan(int64_t M, int64_t N, int64_t K, const WtileBuild** build, int* waves) {
-    struct Entry {
-        int64_t M = 0, N = 0, K = 0;
-        const WtileBuild* build = nullptr;
-        int waves = 0;
-        bool ok = false;
-    };
-    constexpr int kEntries = 64;
-    static thread_local Entry seen[kEntries];
-    Entry& e = seen[(uint64_t)(M * 31 + N * 7 + K / 8) % kEntries];
-    if (e.M != M || e.N != N || e.K != K) {
-        e.ok = wtile_choose<WT, AL>(M, N, K, &e.build, &e.waves);
-        e.M = M;
-        e.N = N;
-        e.K = K;
-    }
-    *build = e.build;
-    *waves = e.waves;
-    return e.ok;
-}
-
 template <typename WT>
 hipError_t launch_wtile_t(const float* x, const WT* w, const float* bias, float* y, int64_t M, int64_t N,
-                          int64_t K, int waves, int reverse, hipStream_t stream) {
-    if (K > kWtileMaxK || (waves != 0 && waves != 4 && waves != 8)) return hipErrorInvalidValue;
-    const bool aligned = (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && K % (16 / (int)sizeof(WT)) == 0;
-    const int64_t J = (K + kChunk - 1) / kChunk;
-    const WtileBuild* b = nullptr;
-    int nw = waves;
-    if (waves != 0) {
-        if (!aligned) return hipErrorInvalidValue;
-        int nb = 0;
-        b = wtile_builds<WT, true>(&nb);                   // the 64 x 64 tile
-    } else if (!(aligned ? wtile_plan<WT, true>(M, N, K, &b, &nw) : wtile_plan<WT, false>(M, N, K, &b, &nw))) {
+                          int64_t K, int build, int waves, bool aligned, int reverse, hipStream_t stream) {
+    int nb = 0;
+    const WtileBuild* bs = wtile_builds(sizeof(WT) == 4, aligned, &nb);
+    if (build < 0 || build >= nb || waves < 1 || waves > bs[build].nwmax || K > kWtileMaxK) return hipErrorInvalidValue;
+    if (aligned && ((((uintptr_t)x | (uintptr_t)w) & 15) != 0 || K % (16 / (int)sizeof(WT)) != 0))
         return hipErrorInvalidValue;
-    }
-    const int64_t tm = (M + b->bm - 1) / b->bm, tn = (N + b->bn - 1) / b->bn;
-    if (tm > 0x7fffffff || tn > 0x7fffffff || tm * tn > 0x7ffffff0) return hipErrorInvalidValue;
+    const WtileBuild& b = bs[build];
+    const int64_t J = (K + kChunk - 1) / kChunk;
+    const int64_t lds = wtile_lds(b, J, waves);
+    const int64_t tm = (M + b.bm - 1) / b.bm, tn = (N + b.bn - 1) / b.bn;
+    if (lds > kWtileLds || tm > 0x7fffffff || tn > 0x7fffffff || tm * tn > 0x7ffffff0) return hipErrorInvalidValue;
     const int64_t grid = (tm * tn + 7) / 8 * 8;            // the same number of workgroups on every XCD
     const WtileArgs a{x, w, bias, y, M, N, K, (int)J, (int)tm, (int)tn, reverse};
-    hipLaunchKernelGGL(b->kernel, dim3((unsigned)grid), dim3(64 * nw), (size_t)wtile_lds(*b, J, nw), stream, a);
+    const WtileKernel kernel = (aligned ? wtile_kernels<WT, true>() : wtile_kernels<WT, false>())[build];
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), (size_t)lds, stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_wtile(const float* x, const uint16_t* w, const float* bias, float* y, int64_t M, int64_t N,
-                        int64_t K, int waves, int reverse, hipStream_t stream) {
-    return launch_wtile_t(x, w, bias, y, M, N, K, waves, reverse, stream);
+                        int64_t K, int build, int waves, bool aligned, int reverse, hipStream_t stream) {
+    return launch_wtile_t(x, w, bias, y, M, N, K, build, waves, aligned, reverse, stream);
 }
 
 hipError_t launch_wtile(const float* x, const float* w, const float* bias, float* y, int64_t M, int64_t N,
-                        int64_t K, int waves, int reverse, hipStream_t stream) {
-    return launch_wtile_t(x, w, bias, y, M, N, K, waves, reverse, stream);
+                        int64_t K, int build, int waves, bool aligned, int reverse, hipStream_t stream) {
+    return launch_wtile_t(x, w, bias, y, M, N, K, build, waves, aligned, reverse, stream);
 }
 
 }  // namespace rg

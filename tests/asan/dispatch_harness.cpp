@@ -1,0 +1,161 @@
+// What rg_linear, rg_linear_bias and rg_linear_f32w launch, against what rg_plan and rg_plan_f32w report: the
+// library's own rg_api.cpp with stubs in place of the kernel launchers (each notes what it was asked for) and of the
+// three HIP queries on the way to a launch, so that every call reaches its launcher without a device.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <string.h>
+
+#include "../../include/rg.h"
+#include "../../include/rg_attn.h"
+#include "../../paper_2609_25624_amd/csrc/rg_kernels.h"
+#include "../../paper_2609_25624_amd/csrc/rg_wtile.h"
+
+extern "C" {
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
+    memset(p, 0, sizeof *p);
+    strcpy(p->gcnArchName, "gfx950");
+    p->multiProcessorCount = 256;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+}
+
+static struct Seen {
+    int calls, kernel, tm, tn, waves;
+    int64_t grid;             // 0: not compared
+    hipError_t answer;        // what the launcher returns
+} seen;
+
+static hipError_t saw(int kernel, int tm, int tn, int waves, int64_t grid) {
+    ++seen.calls;
+    seen.kernel = kernel;
+    seen.tm = tm;
+    seen.tn = tn;
+    seen.waves = waves;
+    seen.grid = grid;
+    return seen.answer;
+}
+
+namespace rg {
+template <bool F32>
+static hipError_t saw_wtile(int64_t M, int64_t N, int build, int waves, bool aligned) {
+    int nb = 0;
+    const WtileBuild* bs = wtile_builds(F32, aligned, &nb);
+    if (build < 0 || build >= nb) return saw(-1, 0, 0, 0, 0);
+    const int64_t tiles = (M + bs[build].bm - 1) / bs[build].bm * ((N + bs[build].bn - 1) / bs[build].bn);
+    return saw(RG_KERNEL_WTILE, bs[build].bm, bs[build].bn, waves, tiles);
+}
+hipError_t launch_attn(const AttnArgs&, int, hipStream_t) { return saw(-1, 0, 0, 0, 0); }
+hipError_t launch_cast(const uint16_t*, float*, int64_t, hipStream_t) { return saw(-1, 0, 0, 0, 0); }
+hipError_t launch_argmax(const float*, int64_t*, int64_t, int64_t, hipStream_t) { return saw(-1, 0, 0, 0, 0); }
+hipError_t launch_gemv(const GemvArgs&, int grid, int nw, hipStream_t) { return saw(RG_KERNEL_GEMV, 0, 0, nw, grid); }
+hipError_t launch_decode(const DecodeArgs& a, int, int, int nw, int, hipStream_t) {
+    return saw(RG_KERNEL_DECODE, 0, 0, nw, a.groups);
+}
+hipError_t launch_decode1(const DecodeArgs&, int grid, int nw, int, hipStream_t) {
+    return saw(RG_KERNEL_DECODE_XS, 0, 0, nw, grid);
+}
+hipError_t launch_skinny(const SkinnyArgs& a, int mt, int, int nw, int, hipStream_t) {
+    return saw(RG_KERNEL_SKINNY, mt, 16, nw, a.groups * a.mslices);
+}
+hipError_t launch_stream(const StreamArgs&, bool, int, int grid, hipStream_t) {
+    return saw(RG_KERNEL_STREAM, 0, 0, 4, grid);
+}
+hipError_t launch_ktile(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int bm, int bn,
+                        int nt, int, int, hipStream_t) { return saw(RG_KERNEL_KTILE, bm, bn, nt / 64, 0); }
+hipError_t launch_ktile(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int bm, int bn,
+                        int nt, int, int, hipStream_t) { return saw(RG_KERNEL_KTILE, bm, bn, nt / 64, 0); }
+hipError_t launch_tiled(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int bm, int bn,
+                        int, int, hipStream_t) { return saw(RG_KERNEL_TILED, bm, bn, 4, 0); }
+hipError_t launch_tiled(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int bm, int bn,
+                        int, int, hipStream_t) { return saw(RG_KERNEL_TILED, bm, bn, 4, 0); }
+hipError_t launch_wtile(const float*, const uint16_t*, const float*, float*, int64_t M, int64_t N, int64_t, int build,
+                        int waves, bool aligned, int, hipStream_t) { return saw_wtile<false>(M, N, build, waves, aligned); }
+hipError_t launch_wtile(const float*, const float*, const float*, float*, int64_t M, int64_t N, int64_t, int build,
+                        int waves, bool aligned, int, hipStream_t) { return saw_wtile<true>(M, N, build, waves, aligned); }
+hipError_t launch_generic(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int grid, int,
+                          hipStream_t) { return saw(RG_KERNEL_GENERIC, 0, 0, 4, grid); }
+hipError_t launch_generic(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int grid, int,
+                          hipStream_t) { return saw(RG_KERNEL_GENERIC, 0, 0, 4, grid); }
+}  // namespace rg
+
+// pointers far enough apart for every size below, never read
+static float* const X = reinterpret_cast<float*>((uintptr_t)1 << 58);
+static uint16_t* const W = reinterpret_cast<uint16_t*>((uintptr_t)2 << 58);
+static float* const Y = reinterpret_cast<float*>((uintptr_t)3 << 58);
+static float* const BIAS = reinterpret_cast<float*>((uintptr_t)4 << 58);
+
+static int call(int entry, int64_t M, int64_t N, int64_t K) {
+    if (entry == 0) return rg_linear(X, W, Y, M, N, K, nullptr);
+    if (entry == 1) return rg_linear_bias(X, W, BIAS, Y, M, N, K, nullptr);
+    return rg_linear_f32w(X, reinterpret_cast<float*>(W), Y, M, N, K, nullptr);
+}
+
+int main() {
+    const int64_t Ms[] = {1, 2, 4, 5, 8, 9, 16, 17, 33, 48, 64, 65, 100, 333, 2048, 65536, 1 << 20};
+    const int64_t Ns[] = {1, 16, 300, 1030, 4096, 6144, 28672, 128256, 1048579, 1 << 28};
+    const int64_t Ks[] = {1, 7, 8, 255, 264, 1000, 1001, 4096, 14336, 28672, 32776, 1 << 20, (1 << 24) - 8, 1 << 24,
+                          (1 << 26) + 8};
+    rg_launch_t cfgs[24] = {};
+    int nc = 1;                                                   // cfgs[0]: the defaults
+    for (int k = 1; k <= 9; ++k) cfgs[nc++].kernel = k;           // every kernel forced
+    cfgs[nc++].grid_order = 1;
+    cfgs[nc++].waves_per_wg = 4;
+    cfgs[nc++].waves_per_wg = 8;
+    cfgs[nc++].tile_n = 32;
+    cfgs[nc++].slice_m = 2;
+    cfgs[nc++].depth = 3;
+    long compared = 0;
+    for (int c = 0; c < nc; ++c) {
+        if (rg_linear_set_launch(&cfgs[c]) != RG_OK) return 2;
+        for (int64_t M : Ms)
+            for (int64_t N : Ns)
+                for (int64_t K : Ks)
+                    for (int entry = 0; entry < 3; ++entry) {
+                        rg_plan_t p;
+                        const int ps = entry == 2 ? rg_plan_f32w(M, N, K, &p) : rg_plan(M, N, K, &p);
+                        seen = Seen{};
+                        const int st = call(entry, M, N, K);
+                        if (ps != RG_OK) {
+                            if (st == ps && seen.calls == 0) continue;
+                            printf("refused by the plan only: entry %d (%ld,%ld,%ld)\n", entry, (long)M, (long)N, (long)K);
+                            return 3;
+                        }
+                        if (st == RG_ERR_RANGE && seen.calls == 0 && p.kernel == RG_KERNEL_DECODE) continue;   // its grid
+                        const bool tiles = p.kernel == RG_KERNEL_WTILE || p.kernel == RG_KERNEL_KTILE ||
+                                           p.kernel == RG_KERNEL_TILED || p.kernel == RG_KERNEL_SKINNY;
+                        if (st != RG_OK || seen.calls != 1 || seen.kernel != p.kernel || seen.waves != p.waves_per_wg ||
+                            (tiles && (seen.tm != p.tile_m || seen.tn != p.tile_n)) ||
+                            (seen.grid != 0 && seen.grid != p.grid_wgs)) {
+                            printf("config %d entry %d (%ld,%ld,%ld): plan kernel %d %d x %d waves %d grid %d, launched "
+                                   "%d %d x %d waves %d grid %ld (%d calls, status %d)\n",
+                                   c, entry, (long)M, (long)N, (long)K, p.kernel, p.tile_m, p.tile_n, p.waves_per_wg,
+                                   p.grid_wgs, seen.kernel, seen.tm, seen.tn, seen.waves, (long)seen.grid, seen.calls, st);
+                            return 4;
+                        }
+                        ++compared;
+                    }
+    }
+    // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel
+    rg_linear_set_launch(nullptr);
+    for (hipError_t err : {hipErrorInvalidValue, hipErrorInvalidConfiguration, hipErrorOutOfMemory})
+        for (int64_t M : {1, 4, 16, 333, 2048})
+            for (int entry = 0; entry < 3; ++entry)
+                for (int64_t K : {1001, 4096}) {
+                    seen = Seen{};
+                    seen.answer = err;
+                    const int st = call(entry, M, 4096, K);
+                    if (st != RG_ERR_HIP || seen.calls != 1 || rg_last_hip_error() != (int)err) {
+                        printf("launch error %d at entry %d (%ld,4096,%ld): status %d after %d launches\n", (int)err, entry,
+                               (long)M, (long)K, st, seen.calls);
+                        return 5;
+                    }
+                }
+    printf("ok: %ld launches as planned\n", compared);
+    return 0;
+}

@@ -29,10 +29,10 @@ hipError_t launch_tiled(const float*, const uint16_t*, const float*, float*, int
                         int, hipStream_t) { return stub(); }
 hipError_t launch_tiled(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int, int, int, int,
                         hipStream_t) { return stub(); }
-hipError_t launch_wtile(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int, int,
-                        hipStream_t) { return stub(); }
-hipError_t launch_wtile(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int, int,
-                        hipStream_t) { return stub(); }
+hipError_t launch_wtile(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int, int, bool,
+                        int, hipStream_t) { return stub(); }
+hipError_t launch_wtile(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int, int, bool,
+                        int, hipStream_t) { return stub(); }
 hipError_t launch_generic(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int, int,
                           hipStream_t) { return stub(); }
 hipError_t launch_generic(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int, int,

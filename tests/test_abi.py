@@ -45,6 +45,12 @@ def test_every_declared_symbol_is_exported_and_bound():
     assert sorted(rg.EXPORTS) == names
 
 
+@pytest.fixture(autouse=True)
+def _reset_launch():
+    yield
+    rg.rg_linear_set_launch(None)
+
+
 def test_strerror_never_null():
     for c in range(-2, 10):
         assert isinstance(rg.strerror(c), str) and rg.strerror(c)
@@ -112,12 +118,16 @@ def test_skinny_slice_width():
     # the slice of x rows while that gives more workgroups; elsewhere the widest slice that fits
     want = {(1, 6144, 4096): 1, (2, 6144, 4096): 1, (2, 4096, 4096): 1, (3, 6144, 4096): 2,
             (4, 6144, 4096): 2, (4, 4096, 4096): 2, (4, 28672, 4096): 4, (4, 4096, 14336): 4,
-            (4, 128256, 4096): 4, (8, 6144, 4096): 4, (16, 6144, 4096): 8, (16, 28672, 4096): 8,
-            (16, 4096, 14336): 4}
-    for shape, mt in want.items():
-        p = rg.rg_plan(*shape)
-        assert (p["kernel_name"], p["tile_m"]) == ("skinny", mt), (shape, p)
-        assert p["grid_wgs"] <= 512
+            (4, 128256, 4096): 4, (8, 6144, 4096): 4}
+    forced = {(16, 6144, 4096): 8, (16, 28672, 4096): 8, (16, 4096, 14336): 4}   # M > 8: not the default there
+    try:
+        for shape, mt in {**want, **forced}.items():
+            rg.rg_linear_set_launch(kernel="skinny") if shape in forced else rg.rg_linear_set_launch(None)
+            p = rg.rg_plan(*shape)
+            assert (p["kernel_name"], p["tile_m"]) == ("skinny", mt), (shape, p)
+            assert p["grid_wgs"] <= 512
+    finally:
+        rg.rg_linear_set_launch(None)
     with pytest.raises(rg.RgError):
         rg.rg_linear_set_launch(slice_m=3)
     try:
@@ -141,8 +151,13 @@ def test_one_row_kernel_choice():
 
 
 def test_mid_batch_kernel_choice():
-    # 16 < M <= 64: skinny on layers with fewer than 448 tiles of 64 W rows and K <= 16384, the
-    # wave-tile kernel above M = 32 with 448 to 1024 such tiles, ktile elsewhere
+    # The kernel a launch with overrides (here the waves) starts from.  16 < M <= 64: skinny on layers with fewer
+    # than 448 tiles of 64 W rows and K <= 16384, the wave-tile kernel's 64 x 64 tiles above M = 32 with 448 to
+    # 1024 such tiles, ktile elsewhere.  Default launches run the wave tiles.
+    wide = ((32, 28672, 4096), (33, 28672, 4096), (64, 28672, 4096), (64, 57344, 8192), (64, 8192, 28672), (65, 4096, 4096))
+    for shape in wide:
+        assert rg.rg_plan(*shape)["kernel_name"] == "wtile", shape
+    rg.rg_linear_set_launch(waves_per_wg=4)
     for shape, name in (((32, 6144, 4096), "skinny"), ((64, 4096, 4096), "skinny"), ((64, 4096, 14336), "skinny"),
                         ((17, 300, 1000), "skinny"), ((32, 28672, 4096), "ktile"), ((64, 128256, 4096), "ktile"),
                         ((33, 28672, 4096), "wtile"), ((64, 28672, 4096), "wtile"), ((64, 57344, 8192), "wtile"),
@@ -158,7 +173,9 @@ def test_mid_batch_kernel_choice():
 
 def test_tiled_128_build_choice():
     # three waves per SIMD only where its rounds of 768 resident tiles are clearly fuller than
-    # the two-wave build's rounds of 512; other tiles report depth 0
+    # the two-wave build's rounds of 512; other tiles report depth 0 (forced: where the default runs the
+    # wave tiles these are not reported)
+    rg.rg_linear_set_launch(kernel="tiled")
     cases = {(2048, 8192, 8192): 2,     # 1024 tiles: 2 full rounds of 512, 1.33 rounds of 768
              (2048, 57344, 8192): 2,    # 7168 tiles: 14 full rounds of 512
              (2048, 4096, 4096): 2,     # 512 tiles: one round either way
@@ -167,6 +184,9 @@ def test_tiled_128_build_choice():
         p = rg.rg_plan(*shape)
         assert (p["kernel_name"], p["tile_m"], p["depth"]) == ("tiled", 128, depth), (shape, p)
     assert rg.rg_plan(256, 28672, 4096)["depth"] == 0          # 64 x 128 tiles
+    rg.rg_linear_set_launch(None)
+    for shape, kernel in (((2000, 4096, 1032), "tiled"), ((2048, 8192, 28672), "wtile")):
+        assert rg.rg_plan(*shape)["kernel_name"] == kernel    # 128 x 128 tiles: many of a short K
     rg.rg_linear_set_launch(depth=3)
     try:
         assert rg.rg_plan(2048, 8192, 8192)["depth"] == 3
@@ -265,9 +285,17 @@ def test_f32w_planner_and_argument_checks():
     rg.rg_linear_set_launch(None)
     assert rg.rg_plan_f32w(1, 4096, 14336)["kernel_name"] == "stream"
     assert rg.rg_plan_f32w(4, 6144, 4096)["kernel_name"] == "stream"
-    assert rg.rg_plan_f32w(16, 6144, 4096)["kernel_name"] == "ktile"
-    assert rg.rg_plan_f32w(100, 1000, 1000)["kernel_name"] == "tiled"
-    assert rg.rg_plan_f32w(1, 100, 1001)["kernel_name"] == "generic"      # K % 4 != 0
+    assert rg.rg_plan_f32w(16, 6144, 4096)["kernel_name"] == "wtile"
+    assert rg.rg_plan_f32w(100, 1000, 1000)["kernel_name"] == "wtile"
+    assert rg.rg_plan_f32w(1, 100, 1001)["kernel_name"] == "wtile"        # K % 4 != 0
+    assert rg.rg_plan_f32w(1, 100, (1 << 24) + 1)["kernel_name"] == "generic"   # beyond the wave tiles' offsets
+    try:
+        rg.rg_linear_set_launch(waves_per_wg=4)                           # what a launch with overrides starts from
+        assert rg.rg_plan_f32w(16, 6144, 4096)["kernel_name"] == "ktile"
+        assert rg.rg_plan_f32w(100, 1000, 1000)["kernel_name"] == "tiled"
+        assert rg.rg_plan_f32w(1, 100, 1001)["kernel_name"] == "generic"
+    finally:
+        rg.rg_linear_set_launch(None)
     assert rg.rg_plan_f32w(1, 4096, 4100)["nchunks"] == 17
     try:
         for k in ("decode", "decode_xs", "gemv"):

@@ -73,7 +73,25 @@ def test_tiled_with_fp32_weights(M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(1, 10, 7), (3, 33, 1001), (70, 20, 259)])
 def test_generic_with_fp32_weights(M, N, K):
-    _check(M, N, K, seed=5)          # K % 4 != 0: the planner's generic kernel
+    _check(M, N, K, seed=5, kernel="generic")
+
+
+@pytest.mark.parametrize("kernel", [None, "generic"])
+def test_misaligned_x_with_fp32_weights(kernel):
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    M, N, K = 6, 45, 520
+    x, w = _inputs(M, N, K, 8)
+    xb = torch.zeros(M * K + 1, dtype=torch.float32, device=gu.dev())
+    xb[1:] = torch.from_numpy(np.ascontiguousarray(x).ravel()).to(gu.dev())     # 4-byte, not 16-byte aligned
+    wd = torch.from_numpy(np.ascontiguousarray(w)).to(gu.dev())
+    y = torch.empty((M, N), dtype=torch.float32, device=gu.dev())
+    if kernel:
+        rg.rg_linear_set_launch(kernel=kernel)
+    rg.rg_linear_f32w(xb[1:].view(M, K), wd, y)
+    torch.cuda.synchronize()
+    gu.assert_bitwise(y.cpu().numpy(), oracle.linear_f32w(x, w), f"f32w misaligned x {kernel}")
 
 
 @pytest.mark.parametrize("launch", [dict(grid_wgs=1), dict(grid_wgs=7, grid_order=1), dict(grid_wgs=3000),

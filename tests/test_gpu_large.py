@@ -26,10 +26,11 @@ def _reset_launch():
 
 @pytest.mark.parametrize("M,N,K,kernel,forced", [(1, 1048579, 2304, "skinny", False), (1, 524309, 4096, "skinny", False),
                                                  (1, 1048579, 2304, "decode_xs", True), (1, 524309, 4096, "gemv", True),
-                                                 (3, 1048579, 2304, "skinny", False), (16, 1048579, 2304, "skinny", False),
+                                                 (3, 1048579, 2304, "skinny", False), (16, 1048579, 2304, "skinny", True),
+                                                 (16, 1048579, 2304, "wtile", False),
                                                  (3, 1048579, 2304, "decode", True), (16, 1048579, 2304, "ktile", True),
                                                  (40, 1048579, 2304, "wtile", True), (40, 1048579, 2304, "skinny", True),
-                                                 (70, 1048579, 2304, "tiled", False)])
+                                                 (70, 1048579, 2304, "tiled", True), (70, 1048579, 2304, "wtile", False)])
 def test_weights_beyond_4_gib(M, N, K, kernel, forced):
     import torch
     import paper_2609_25624_amd as rg

@@ -181,19 +181,25 @@ def test_config5_70b_m1(name, N, K):
 
 
 @pytest.mark.parametrize("name,N,K", [("70b_gate_up", 57344, 8192), ("70b_down", 8192, 28672)])
-def test_config5_70b_m2048_full(name, N, K):
+@pytest.mark.parametrize("kernel", [None, "tiled"])
+def test_config5_70b_m2048_full(name, N, K, kernel):
     """Every output of the 2048-row prefill layers against the oracle's stored full-output digest
     (on a mismatch the same-order vectorised oracle names the first differing output), and a
-    sample against the definitional oracle computed here."""
+    sample against the definitional oracle computed here; through the default's wave tiles and the
+    128 x 128 register tiles."""
     import torch
     import oracle
     import paper_2609_25624_amd as rg
-    assert rg.rg_plan(2048, N, K)["kernel_name"] == "tiled"
-    gu.log(f"case 70B {name} M=2048")
-    x, w = gu.layer(2048, N, K, w_std=0.01, layer_id=9)
-    xd, wd = gu.to_dev(x, w)
-    y = gu.run(xd, wd)
-    torch.cuda.synchronize()
+    rg.rg_linear_set_launch(kernel=kernel) if kernel else rg.rg_linear_set_launch(None)
+    try:
+        assert rg.rg_plan(2048, N, K)["kernel_name"] == (kernel or "wtile")
+        gu.log(f"case 70B {name} M=2048 kernel={kernel}")
+        x, w = gu.layer(2048, N, K, w_std=0.01, layer_id=9)
+        xd, wd = gu.to_dev(x, w)
+        y = gu.run(xd, wd)
+        torch.cuda.synchronize()
+    finally:
+        rg.rg_linear_set_launch(None)
     got = y.cpu().numpy()
     del xd, wd, y
     gu.assert_full_output(got, x, w, f"{name}_m2048")
@@ -205,8 +211,12 @@ def test_config5_70b_m2048_full(name, N, K):
                                    (300, 77, 520), (256, 4096, 4096), (2048, 192, 8200)])
 def test_tiled_shapes(M, N, K):
     import paper_2609_25624_amd as rg
-    assert rg.rg_plan(M, N, K)["kernel_name"] == "tiled"
-    _check_layer(M, N, K, seed=M + K)
+    rg.rg_linear_set_launch(kernel="tiled")
+    try:
+        assert rg.rg_plan(M, N, K)["kernel_name"] == "tiled"
+        _check_layer(M, N, K, seed=M + K)
+    finally:
+        rg.rg_linear_set_launch(None)
 
 
 @pytest.mark.parametrize("M,N,K", [(2048, 4100, 264), (2000, 4096, 1032), (4096, 2048, 520)])
@@ -354,19 +364,33 @@ def _probes_in_rows(K, N):
 
 @pytest.mark.parametrize("M,N,K", [(1, 10, 7), (2, 33, 301), (3, 5, 1), (1, 4, 257), (100, 1000, 1000)])
 def test_generic_shapes(M, N, K):
-    _check_layer(M, N, K, seed=K)
+    import paper_2609_25624_amd as rg
+    rg.rg_linear_set_launch(kernel="generic")
+    try:
+        assert rg.rg_plan(M, N, K)["kernel_name"] == "generic"
+        _check_layer(M, N, K, seed=K)
+    finally:
+        rg.rg_linear_set_launch(None)
 
 
-def test_misaligned_pointers_take_the_generic_path():
+@pytest.mark.parametrize("kernel", [None, "generic"])
+def test_misaligned_pointers(kernel):
+    """x off its 16-byte alignment: the default's register-staged wave tiles, and the generic kernel."""
     import torch
+    import paper_2609_25624_amd as rg
     M, N, K = 2, 37, 1024
     x, w = gu.layer(M, N, K, seed=11)
     xb = torch.zeros(M * K + 1, dtype=torch.float32, device=gu.dev())
     xb[1:] = torch.from_numpy(np.array(x, copy=True).ravel()).to(gu.dev())
     xd = xb[1:].view(M, K)                      # 4-byte but not 16-byte aligned
     wd = gu.to_dev(x, w)[1]
-    y = gu.run(xd, wd)
-    gu.assert_bitwise(y.cpu().numpy(), gu.oracle_full(x, w), "misaligned x")
+    rg.rg_linear_set_launch(kernel=kernel) if kernel else rg.rg_linear_set_launch(None)
+    try:
+        y = gu.run(xd, wd)
+        torch.cuda.synchronize()
+    finally:
+        rg.rg_linear_set_launch(None)
+    gu.assert_bitwise(y.cpu().numpy(), gu.oracle_full(x, w), f"misaligned x {kernel}")
 
 
 def test_order_probes_on_gpu():

@@ -66,6 +66,7 @@ def _check_planted(M, N, K, rows, cols, full=True, seed=0):
 def test_tiled_short_last_slab_keeps_minus_zero(K):
     import paper_2609_25624_amd as rg
     M, N = 65, 130
+    rg.rg_linear_set_launch(kernel="tiled")
     assert rg.rg_plan(M, N, K)["kernel_name"] == "tiled"
     _check_planted(M, N, K, rows=[0, 33, 64], cols=[0, 77, 129], seed=K)
 
