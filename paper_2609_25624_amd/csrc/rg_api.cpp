@@ -465,7 +465,7 @@ rg::WtileChoice wave_tile(int64_t M, int64_t N, int64_t K, bool f32, bool aligne
     };
     constexpr int kEntries = 64;
     static thread_local Entry seen[kEntries];
-    Entry& e = seen[(uint64_t)(M * 31 + N * 7 + K / 8) % kEntries];
+    Entry& e = seen[((uint64_t)M * 31 + (uint64_t)N * 7 + (uint64_t)K / 8) % kEntries];
     if (e.M != M || e.N != N || e.K != K || e.f32 != f32 || e.aligned != aligned) {
         e.c = rg::wtile_choose(M, N, K, f32, aligned);
         e.M = M;

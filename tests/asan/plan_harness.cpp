@@ -73,6 +73,15 @@ int main() {
                 }
     }
     rg_linear_set_launch(nullptr);
+    // sizes at the limits the argument checks let through (no launch could follow)
+    for (int64_t big : {(int64_t)1 << 40, (int64_t)1 << 58, (int64_t)1 << 60, ((int64_t)1 << 61) - 1})
+        for (int64_t K : {1, 8}) {
+            rg_plan_t p;
+            for (int f32 = 0; f32 < 2; ++f32) {
+                (void)(f32 ? rg_plan_f32w(big / K, 1, K, &p) : rg_plan(big / K, 1, K, &p));
+                (void)(f32 ? rg_plan_f32w(1, big / K, K, &p) : rg_plan(1, big / K, K, &p));
+            }
+        }
     // argument checks that fail before any device work
     float* x = reinterpret_cast<float*>(0x10000);
     uint16_t* w = reinterpret_cast<uint16_t*>(0x200000);
