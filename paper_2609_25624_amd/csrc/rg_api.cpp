@@ -241,11 +241,12 @@ bool wtile_schedule(int64_t M, int64_t N, int64_t K, const rg_launch_t& o, Plan*
         (o.tile_n != 0 && o.tile_n != 64) || o.slice_m != 0)
         return false;
     const int64_t tiles = ceil_div(M, rg::kWtileRows) * ceil_div(N, rg::kWtileRows);
-    if (tiles > 0x7fffffff) return false;
+    const int nw = o.waves_per_wg > 0 ? o.waves_per_wg : 4;
+    if (!rg::wtile_grid_ok(tiles, nw)) return false;
     p->tile_m = rg::kWtileRows;
     p->tile_n = rg::kWtileRows;
     p->grid = (int)tiles;
-    p->nw = o.waves_per_wg > 0 ? o.waves_per_wg : 4;
+    p->nw = nw;
     p->depth = 0;
     p->wbuild = 0;
     p->waligned = true;

@@ -13,6 +13,11 @@ constexpr int64_t kWtileMaxK = (1 << 24) - 1;   // byte offsets within a tile (a
 constexpr int kWtileDepth = 2;             // slabs of a wave's LDS ring: one computed, one in flight
 constexpr int kWtileLds = 160 * 1024;
 
+// Workgroups of a launch of `tiles` tiles (the same number on every XCD), and whether one of `waves` waves each stays
+// within the 2^32 - 1 threads a launch holds.
+inline int64_t wtile_grid(int64_t tiles) { return (tiles + 7) / 8 * 8; }
+inline bool wtile_grid_ok(int64_t tiles, int waves) { return wtile_grid(tiles) <= 0xffffffffLL / (64 * waves); }
+
 // LDS bytes of one slab of a wave: x then W, each padded to whole 1 KB DMA instructions.
 template <int BM, int BN, int KT, typename WT>
 struct WtileSlab {
@@ -82,8 +87,8 @@ inline int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
 // faster than HBM streams W (6.2 GB per ms).  So 1536 = 6 segments run on 2 waves, four workgroups per
 // CU, not on 6 waves with two slots empty (2048 x 16384 x 1536 1472 -> 1116 us).
 //
-// Not ok where the 128 x 128 register tiles are the better ones: at least 512 of them, and their
-// own time (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is
+// Not ok where no build's tiles fit a launch, and where the 128 x 128 register tiles are the better ones: at
+// least 512 of them, and their own time (rounds of 512, 175 multiply-adds per ns and CU) under 0.9 of the estimate here, which is
 // pessimistic by that much where tiles are many (2048 x 16384: K = 1024 767 against 785 us, K = 2048 1481
 // against 1532; from K = 8192 on the wave tiles lead: 2048 x 57344 x 8192 20.8 against 21.8 ms).
 struct WtileChoice {
@@ -112,7 +117,7 @@ inline WtileChoice wtile_choose(int64_t M, int64_t N, int64_t K, bool f32, bool 
         for (int tries = 0; tries < 4; ++tries, ++rounds) {
             const int nw = (int)((J + rounds - 1) / rounds);
             const int64_t lds = wtile_lds(b, J, nw);
-            if (lds > kWtileLds) continue;
+            if (lds > kWtileLds || !wtile_grid_ok((int64_t)tiles, nw)) continue;
             int resident = (int)(kWtileLds / lds);
             if (resident * nw > b.nwmax) resident = b.nwmax / nw > 0 ? b.nwmax / nw : 1;
             if (resident > percu) resident = percu;

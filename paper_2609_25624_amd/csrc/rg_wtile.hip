@@ -496,8 +496,8 @@ hipError_t launch_wtile_t(const float* x, const WT* w, const float* bias, float*
     const int64_t J = (K + kChunk - 1) / kChunk;
     const int64_t lds = wtile_lds(b, J, waves);
     const int64_t tm = (M + b.bm - 1) / b.bm, tn = (N + b.bn - 1) / b.bn;
-    if (lds > kWtileLds || tm > 0x7fffffff || tn > 0x7fffffff || tm * tn > 0x7ffffff0) return hipErrorInvalidValue;
-    const int64_t grid = (tm * tn + 7) / 8 * 8;            // the same number of workgroups on every XCD
+    if (lds > kWtileLds || tm > 0x7fffffff || tn > 0x7fffffff || !wtile_grid_ok(tm * tn, waves)) return hipErrorInvalidValue;
+    const int64_t grid = wtile_grid(tm * tn);
     const WtileArgs a{x, w, bias, y, M, N, K, (int)J, (int)tm, (int)tn, reverse};
     const WtileKernel kernel = (aligned ? wtile_kernels<WT, true>() : wtile_kernels<WT, false>())[build];
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), (size_t)lds, stream, a);

@@ -48,6 +48,7 @@ static hipError_t saw_wtile(int64_t M, int64_t N, int build, int waves, bool ali
     const WtileBuild* bs = wtile_builds(F32, aligned, &nb);
     if (build < 0 || build >= nb) return saw(-1, 0, 0, 0, 0);
     const int64_t tiles = (M + bs[build].bm - 1) / bs[build].bm * ((N + bs[build].bn - 1) / bs[build].bn);
+    if ((tiles + 7) / 8 * 8 * 64 * waves > 0xffffffffLL) return saw(-2, 0, 0, 0, 0);   // more threads than a launch holds
     return saw(RG_KERNEL_WTILE, bs[build].bm, bs[build].bn, waves, tiles);
 }
 hipError_t launch_attn(const AttnArgs&, int, hipStream_t) { return saw(-1, 0, 0, 0, 0); }
@@ -141,6 +142,23 @@ int main() {
                         ++compared;
                     }
     }
+    // outputs in numbers whose tiles come near a launch's 2^32 threads: a kernel that can be launched is chosen
+    rg_linear_set_launch(nullptr);
+    for (int64_t MN : {(int64_t)1 << 30, (int64_t)1 << 31, ((int64_t)1 << 31) + 12345, (int64_t)1 << 33, (int64_t)1 << 35,
+                       (int64_t)1 << 38})
+        for (int64_t M : {1, 3, 17, 333, 1 << 17, 1 << 19})
+            for (int64_t K : {1, 8, 255, 256, 1001, 2048, 4096})
+                for (int entry = 0; entry < 3; ++entry) {
+                    if (K % 8 == 0 && MN > ((int64_t)1 << 37)) continue;      // (the register tiles' own limit)
+                    if (K % 8 == 0 && M <= 8) continue;                       // (not the wave tiles' shapes)
+                    seen = Seen{};
+                    const int st = call(entry, M, MN / M, K);
+                    if (st != RG_OK || seen.calls != 1 || seen.kernel < 0) {
+                        printf("entry %d (%ld,%ld,%ld): status %d, launched %d\n", entry, (long)M, (long)(MN / M), (long)K,
+                               st, seen.kernel);
+                        return 6;
+                    }
+                }
     // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel
     rg_linear_set_launch(nullptr);
     for (hipError_t err : {hipErrorInvalidValue, hipErrorInvalidConfiguration, hipErrorOutOfMemory})
