@@ -451,10 +451,9 @@ void generic_schedule(int64_t M, int64_t N, const rg_launch_t& o, Plan* p) {
     p->nw = 4;
 }
 
-// No override at all: the launch is the planner's to choose.
+// No override but perhaps the grid order: kernel, tile and waves are the planner's to choose.
 bool is_default(const rg_launch_t& o) {
-    return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.grid_order == 0 &&
-           o.tile_n == 0 && o.slice_m == 0;
+    return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.tile_n == 0 && o.slice_m == 0;
 }
 
 // rg::wtile_choose, remembered for the shapes a thread has used last (a serving loop launches the same few).
@@ -502,7 +501,7 @@ bool wave_tile_plan(int64_t M, int64_t N, int64_t K, bool f32, bool fast_ok, int
     p->tile_m = b.bm;
     p->tile_n = b.bn;
     p->grid = (int)(ceil_div(M, b.bm) * ceil_div(N, b.bn));
-    p->reverse = 0;
+    p->reverse = o.grid_order;
     return true;
 }
 

@@ -26,7 +26,7 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 }
 
 static struct Seen {
-    int calls, kernel, tm, tn, waves;
+    int calls, kernel, tm, tn, waves, reverse;
     int64_t grid;             // 0: not compared
     hipError_t answer;        // what the launcher returns
 } seen;
@@ -43,7 +43,8 @@ static hipError_t saw(int kernel, int tm, int tn, int waves, int64_t grid) {
 
 namespace rg {
 template <bool F32>
-static hipError_t saw_wtile(int64_t M, int64_t N, int build, int waves, bool aligned) {
+static hipError_t saw_wtile(int64_t M, int64_t N, int build, int waves, bool aligned, int reverse) {
+    seen.reverse = reverse;
     int nb = 0;
     const WtileBuild* bs = wtile_builds(F32, aligned, &nb);
     if (build < 0 || build >= nb) return saw(-1, 0, 0, 0, 0);
@@ -76,9 +77,13 @@ hipError_t launch_tiled(const float*, const uint16_t*, const float*, float*, int
 hipError_t launch_tiled(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int bm, int bn,
                         int, int, hipStream_t) { return saw(RG_KERNEL_TILED, bm, bn, 4, 0); }
 hipError_t launch_wtile(const float*, const uint16_t*, const float*, float*, int64_t M, int64_t N, int64_t, int build,
-                        int waves, bool aligned, int, hipStream_t) { return saw_wtile<false>(M, N, build, waves, aligned); }
+                        int waves, bool aligned, int reverse, hipStream_t) {
+    return saw_wtile<false>(M, N, build, waves, aligned, reverse);
+}
 hipError_t launch_wtile(const float*, const float*, const float*, float*, int64_t M, int64_t N, int64_t, int build,
-                        int waves, bool aligned, int, hipStream_t) { return saw_wtile<true>(M, N, build, waves, aligned); }
+                        int waves, bool aligned, int reverse, hipStream_t) {
+    return saw_wtile<true>(M, N, build, waves, aligned, reverse);
+}
 hipError_t launch_generic(const float*, const uint16_t*, const float*, float*, int64_t, int64_t, int64_t, int grid, int,
                           hipStream_t) { return saw(RG_KERNEL_GENERIC, 0, 0, 4, grid); }
 hipError_t launch_generic(const float*, const float*, const float*, float*, int64_t, int64_t, int64_t, int grid, int,
@@ -142,6 +147,27 @@ int main() {
                         ++compared;
                     }
     }
+    // the grid order alone reverses the default's own kernel, tile and waves
+    for (int64_t M : Ms)
+        for (int64_t N : Ns)
+            for (int64_t K : Ks)
+                for (int entry = 0; entry < 3; ++entry) {
+                    rg_plan_t a, b;
+                    rg_launch_t rev = {};
+                    rev.grid_order = 1;
+                    rg_linear_set_launch(nullptr);
+                    const int sa = entry == 2 ? rg_plan_f32w(M, N, K, &a) : rg_plan(M, N, K, &a);
+                    rg_linear_set_launch(&rev);
+                    const int sb = entry == 2 ? rg_plan_f32w(M, N, K, &b) : rg_plan(M, N, K, &b);
+                    if (sa != RG_OK || a.kernel != RG_KERNEL_WTILE) continue;
+                    seen = Seen{};
+                    const int st = call(entry, M, N, K);
+                    if (sb != RG_OK || memcmp(&a, &b, sizeof a) != 0 || st != RG_OK || seen.reverse != 1) {
+                        printf("reversed: entry %d (%ld,%ld,%ld) kernel %d %d x %d, forward %d x %d\n", entry, (long)M,
+                               (long)N, (long)K, b.kernel, b.tile_m, b.tile_n, a.tile_m, a.tile_n);
+                        return 7;
+                    }
+                }
     // outputs in numbers whose tiles come near a launch's 2^32 threads: a kernel that can be launched is chosen
     rg_linear_set_launch(nullptr);
     for (int64_t MN : {(int64_t)1 << 30, (int64_t)1 << 31, ((int64_t)1 << 31) + 12345, (int64_t)1 << 33, (int64_t)1 << 35,

@@ -44,19 +44,26 @@ def _check(M, N, K, f32=False, bias=False, shift=0):
     xd, wd = xb[shift:].view(M, K), wb[shift:].view(N, K)
     xd.copy_(torch.from_numpy(x))
     wd.copy_(torch.from_numpy(w if f32 else w.view(np.int16)))
-    y = torch.full((M, N), 7.0, dtype=torch.float32, device=gu.dev())
     if bias:
         b = np.random.default_rng(1).standard_normal(N, dtype=np.float32)
-        rg.rg_linear_bias(xd, wd, torch.from_numpy(b).to(gu.dev()), y)
+        bd = torch.from_numpy(b).to(gu.dev())
         want = oracle.linear_bias(x, w, b)
     elif f32:
-        rg.rg_linear_f32w(xd, wd, y)
         want = oracle.linear_f32w(x, w)
     else:
-        rg.rg_linear(xd, wd, y)
         want = oracle.linear_fast(x, w)
-    torch.cuda.synchronize()
-    gu.assert_bitwise(y.cpu().numpy(), want, f"({M},{N},{K})")
+    for order in (0, 1):                 # the tiles' workgroups forward and reversed
+        rg.rg_linear_set_launch(grid_order=order)
+        y = torch.full((M, N), 7.0, dtype=torch.float32, device=gu.dev())
+        if bias:
+            rg.rg_linear_bias(xd, wd, bd, y)
+        elif f32:
+            rg.rg_linear_f32w(xd, wd, y)
+        else:
+            rg.rg_linear(xd, wd, y)
+        torch.cuda.synchronize()
+        gu.assert_bitwise(y.cpu().numpy(), want, f"({M},{N},{K}) order {order}")
+    rg.rg_linear_set_launch(None)
 
 
 @pytest.mark.parametrize("M,N,K", ALIGNED)
@@ -78,6 +85,39 @@ def test_odd_k_builds(M, N, K, f32):
 @pytest.mark.parametrize("M,N,K,shift", [(5, 100, 1003, 0), (12, 300, 512, 1), (70, 500, 264, 3), (2, 40, 256, 1)])
 def test_bias_and_shifted_pointers(M, N, K, shift):
     _check(M, N, K, bias=True, shift=shift)
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 4096, 4096), (16, 6144, 4096), (40, 1030, 4104), (5, 2999, 1003), (333, 1000, 2056)])
+def test_cu_masks(M, N, K):
+    """The default's tiles on streams that own only some of the compute units."""
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    rg.rg_linear_set_launch(None)
+    gu.log(f"wave-tile rule cu masks {rg.rg_plan(M, N, K)}")
+    x, w = _inputs(M, N, K, False, 3)
+    xd, wd = gu.to_dev(x, w)
+    want = oracle.linear_fast(x, w)
+    nwords = (rg.rg_device_cu_count() + 31) // 32
+    done = 0
+    for mask in ([0x55555555] * nwords, [0xFFFFFFFF] * (nwords // 2) + [0] * (nwords - nwords // 2),
+                 [0xFFFFFFFF, 0x1F] + [0] * (nwords - 2)):
+        try:
+            s = rg.rg_stream_create_cu_mask(mask)
+        except rg.RgError:
+            continue                                  # the runtime may refuse a mask
+        try:
+            ext = torch.cuda.ExternalStream(s)
+            y = torch.full((M, N), 7.0, dtype=torch.float32, device=gu.dev())
+            torch.cuda.synchronize()
+            gu.run(xd, wd, stream=ext, out=y)
+            ext.synchronize()
+            gu.assert_bitwise(y.cpu().numpy(), want, f"({M},{N},{K}) mask {mask[0]:x}")
+            done += 1
+        finally:
+            torch.cuda.synchronize()
+            rg.rg_stream_destroy(s)
+    assert done >= 1, "no CU mask could be exercised"
 
 
 @pytest.mark.parametrize("K", [255, 270, 264])
