@@ -456,7 +456,50 @@ bool is_default(const rg_launch_t& o) {
     return o.kernel <= 0 && o.waves_per_wg == 0 && o.grid_wgs == 0 && o.depth == 0 && o.tile_n == 0 && o.slice_m == 0;
 }
 
-// rg::wtile_choose, remembered for the shapes a thread has used last (a serving loop launches the same few).
+// Rows of 16 < M <= 64 that the skinny kernel runs where the wave tiles do not: fewer than 448 tiles of 64 W rows (every
+// ktile workgroup re-reads all of x) and x of two segment groups fits (K <= 16384).
+bool skinny_mid(int64_t M, int64_t N, int64_t J) {
+    return M > kSkinnyMaxM && M <= kDecodeMaxM && ceil_div(N, 64) < 448 && ceil_div(J, 4) <= 16;
+}
+
+// A wave tile's time, us, from its estimate (which is high by about this much: 1600 shapes of random size).
+double wave_tile_us(const rg::WtileChoice& c) { return 0.87 * (c.us + 2.5); }
+
+// Narrow layers of M > 8 rows whose one-, two- or four-row slices put the skinny kernel's workgroups on the chip in
+// few rounds: a wave tile walks all of K alone there (16 segments at a time at most, a round of them 10 us), the
+// skinny kernel's slices have a workgroup each.  The skinny kernel's time, us, fitted over 838 shapes of 9 to 64 rows
+// (within 0.84 to 1.16 of the measured for 9 of 10): rounds of the fullest XCD's row groups, each about 5.1 us for
+// four segments per wave and 0.7 us more per further row of x, and the waves that share a CU.  Measured, skinny
+// against wave tile, us: 9 x 300 x 28672 24 against 73, 64 x 256 x 7056 12.7 against 22.2, 16 x 1024 x 1024 5.7
+// against 7.4; below four segments the wave tiles are level or ahead.
+bool skinny_leads(int64_t M, int64_t N, int64_t K, const rg::WtileChoice& c) {
+    const int64_t J = ceil_div(K, rg::kChunk);
+    if (J < 4 || !(M <= kSkinnyMaxM || skinny_mid(M, N, J)) || !skinny_shape_ok(M, K)) return false;
+    Plan p;
+    const rg_launch_t none = {};
+    if (!skinny_schedule(M, N, K, none, &p) || p.mt > 4) return false;
+    const int64_t S = p.mslices, G = p.groups, RG = ceil_div(N, 16);
+    const int64_t lds = (int64_t)rg::skinny_lds_bytes(p.mt, p.nw, p.depth, p.jp);
+    int64_t percu = kLdsBytes / lds < 8 / p.nw ? kLdsBytes / lds : 8 / p.nw;
+    if (percu < 1) percu = 1;
+    const int64_t xcd_rows = ceil_div(G, 8) * (RG / G) + ceil_div(RG % G, 8);   // row groups of the fullest XCD
+    int64_t rounds = ceil_div(xcd_rows * S, 32 * percu);
+    if (rounds < ceil_div(RG, G)) rounds = ceil_div(RG, G);
+    const double waves = (double)(ceil_div(G, 8) * S * p.nw) / 32.0;            // per CU of that XCD
+    const double us = 1.4 + (double)(rounds * p.spw) * (5.1 + 0.73 * (p.mt - 1)) + 0.35 * waves;
+    return us < wave_tile_us(c);
+}
+
+// The wave tile a shape runs on by default, if it is the better kernel for it.
+rg::WtileChoice wave_tile_choice(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
+    rg::WtileChoice c = rg::wtile_choose(M, N, K, f32, aligned);
+    if (!c.ok) return c;
+    if (!aligned) return c;
+    if (M <= kDecodeMaxM && !f32) c.ok = !skinny_leads(M, N, K, c);
+    return c;
+}
+
+// wave_tile_choice, remembered for the shapes a thread has used last (a serving loop launches the same few).
 rg::WtileChoice wave_tile(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
     struct Entry {
         int64_t M = 0, N = 0, K = 0;
@@ -467,7 +510,7 @@ rg::WtileChoice wave_tile(int64_t M, int64_t N, int64_t K, bool f32, bool aligne
     static thread_local Entry seen[kEntries];
     Entry& e = seen[((uint64_t)M * 31 + (uint64_t)N * 7 + (uint64_t)K / 8) % kEntries];
     if (e.M != M || e.N != N || e.K != K || e.f32 != f32 || e.aligned != aligned) {
-        e.c = rg::wtile_choose(M, N, K, f32, aligned);
+        e.c = wave_tile_choice(M, N, K, f32, aligned);
         e.M = M;
         e.N = N;
         e.K = K;
@@ -528,14 +571,11 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
     const bool skinny_ok = fast_ok && skinny_shape_ok(M, K);
     // M == 1 too: the one-row skinny build measured 2 % faster than the GEMV on the
     // 28672 x 4096, 4096 x 14336 and 128256 x 4096 layers
-    // 16 < M <= 64: skinny where ktile's tiles are narrow (fewer than 448 of 64 W rows: every
-    // ktile workgroup re-reads all of x) and x of two segment groups fits (K <= 16384).
+    // 16 < M <= 64: skinny where ktile's tiles are narrow.
     // Measured, interleaved A/B: QKV 6144 x 4096 at M = 32 / 48 / 64 40.6 / 83.3 / 73.8 against
     // 71.7 / 86.7 / 89.8 us, O 4096 x 4096 at M = 24 / 32 / 64 33.2 / 29.6 / 51.5 against
     // 36.3 / 39.4 / 65.5, down 4096 x 14336 at M = 32 113 against 133 (level at M = 64);
     // ktile stays faster on gate+up 28672 x 4096 and the 70B down 8192 x 28672
-    const bool skinny_mid = skinny_ok && M > kSkinnyMaxM && M <= kDecodeMaxM && ceil_div(N, 64) < 448 &&
-                            ceil_div(J, 4) <= 16;
     // 32 < M <= 64 on wide layers with at most 1024 tiles of 64 W rows: the wave-tile kernel
     // (interleaved A/B against ktile: gate+up 28672 x 4096 at M = 40 / 64 219 / 225 against
     // 250 / 252 us, 70B gate+up 57344 x 8192 at M = 64 858 against 944; level on the
@@ -549,7 +589,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, bool fast_ok, const rg_launch_t& 
     // against 11.3 / 13.6 / 37.0 at 6144 / 8192 / 28672)
     const bool gemv_short = gemv_ok && ceil_div(K, rg::kChunk) == 16 && N <= 4096;
     if (gemv_short) want = RG_KERNEL_GEMV;
-    else if (skinny_ok && (M <= kSkinnyMaxM || skinny_mid)) want = RG_KERNEL_SKINNY;
+    else if (skinny_ok && (M <= kSkinnyMaxM || skinny_mid(M, N, J))) want = RG_KERNEL_SKINNY;
     else if (wtile_pref) want = RG_KERNEL_WTILE;
     else if (gemv_ok && ceil_div(K, rg::kChunk) == 16) want = RG_KERNEL_GEMV;
     else if (ktile_ok && ktile_pref) want = RG_KERNEL_KTILE;

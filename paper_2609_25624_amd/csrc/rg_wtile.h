@@ -94,6 +94,7 @@ inline int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
 struct WtileChoice {
     bool ok = false;
     int build = 0, waves = 0;      // index into wtile_builds, waves per workgroup
+    double us = 0.0;               // estimated time
 };
 
 inline WtileChoice wtile_choose(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
@@ -103,7 +104,6 @@ inline WtileChoice wtile_choose(int64_t M, int64_t N, int64_t K, bool f32, bool 
     const int64_t J = (K + kChunk - 1) / kChunk;
     const double last_len = (double)(K - (J - 1) * kChunk);
     const double hbm = (double)N * (double)K * (f32 ? 4 : 2) / 6.2e6;
-    double best = 0.0;
     for (int i = 0; i < nb; ++i) {
         const WtileBuild& b = bs[i];
         const double tiles = (double)((M + b.bm - 1) / b.bm) * (double)((N + b.bn - 1) / b.bn);
@@ -128,8 +128,8 @@ inline WtileChoice wtile_choose(int64_t M, int64_t N, int64_t K, bool f32, bool 
             double us = batches * (1.0 + (double)rounds * (0.3 + 1.7 / nw * (tile / 4096.0)) +
                                    path * share * tile / (b.rate * 125.0));
             if (us < hbm) us = hbm + 0.05 * us;
-            if (!c.ok || us < best) {
-                best = us;
+            if (!c.ok || us < c.us) {
+                c.us = us;
                 c.ok = true;
                 c.build = i;
                 c.waves = nw;
@@ -141,7 +141,7 @@ inline WtileChoice wtile_choose(int64_t M, int64_t N, int64_t K, bool f32, bool 
         const double t128 = (double)((M + 127) / 128) * (double)((N + 127) / 128);
         if (t128 >= 512.0) {
             const double rounds = (double)(((int64_t)t128 + 511) / 512);
-            if (rounds * 2.0 * 128.0 * 128.0 * (double)K / 175000.0 < 0.9 * best) c.ok = false;
+            if (rounds * 2.0 * 128.0 * 128.0 * (double)K / 175000.0 < 0.9 * c.us) c.ok = false;
         }
     }
     return c;

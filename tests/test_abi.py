@@ -171,6 +171,24 @@ def test_mid_batch_kernel_choice():
         rg.rg_linear_set_launch(None)
 
 
+def test_default_kernel_where_the_wave_tiles_are_behind():
+    # Shapes measured slower on a wave tile than on the kernel they ran on before it, and
+    # neighbours that stay on the wave tile.
+    bf16 = (((9, 300, 28672), "skinny"), ((13, 64, 32168), "skinny"), ((16, 16, 4096), "skinny"), ((64, 256, 7056), "skinny"),
+            ((16, 1024, 1024), "skinny"), ((31, 64, 12840), "skinny"), ((14, 1920, 7664), "skinny"), ((16, 6144, 4096), "wtile"),
+            ((16, 4096, 14336), "wtile"), ((64, 256, 512), "wtile"),
+            ((333, 28672, 4096), "wtile"), ((333, 6144, 4096), "wtile"), ((333, 4096, 14336), "wtile"),
+            ((333, 4096, 4096), "wtile"), ((64, 6144, 4096), "wtile"), ((64, 28672, 4096), "wtile"), ((100, 300, 1000), "wtile"),
+            ((5, 2999, 1003), "wtile"),
+            ((1, 31, 263), "wtile"))
+    fp32 = (((333, 28672, 4096), "wtile"),
+            ((16, 16, 4096), "wtile"), ((1, 187328, 21), "wtile"))
+    for shape, kernel in bf16:
+        assert rg.rg_plan(*shape)["kernel_name"] == kernel, (shape, rg.rg_plan(*shape))
+    for shape, kernel in fp32:
+        assert rg.rg_plan_f32w(*shape)["kernel_name"] == kernel, (shape, rg.rg_plan_f32w(*shape))
+
+
 def test_tiled_128_build_choice():
     # three waves per SIMD only where its rounds of 768 resident tiles are clearly fuller than
     # the two-wave build's rounds of 512; other tiles report depth 0 (forced: where the default runs the

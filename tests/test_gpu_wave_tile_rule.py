@@ -82,6 +82,17 @@ def test_odd_k_builds(M, N, K, f32):
     _check(M, N, K, f32=f32)
 
 
+@pytest.mark.parametrize("M,N,K,f32,kernel", [
+    (9, 300, 28672, False, "skinny"), (16, 1024, 1024, False, "skinny"), (64, 250, 7056, False, "skinny"),
+    (33, 40, 2056, False, "skinny"), (13, 64, 32168, False, "skinny"),
+])
+def test_defaults_that_other_kernels_lead(M, N, K, f32, kernel):
+    import paper_2609_25624_amd as rg
+    rg.rg_linear_set_launch(None)
+    assert (rg.rg_plan_f32w if f32 else rg.rg_plan)(M, N, K)["kernel_name"] == kernel
+    _check(M, N, K, f32=f32)
+
+
 @pytest.mark.parametrize("M,N,K,shift", [(5, 100, 1003, 0), (12, 300, 512, 1), (70, 500, 264, 3), (2, 40, 256, 1)])
 def test_bias_and_shifted_pointers(M, N, K, shift):
     _check(M, N, K, bias=True, shift=shift)
