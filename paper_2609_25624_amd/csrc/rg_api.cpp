@@ -490,12 +490,45 @@ bool skinny_leads(int64_t M, int64_t N, int64_t K, const rg::WtileChoice& c) {
     return us < wave_tile_us(c);
 }
 
+// Many rows of a short K: the register tiles (whole K per workgroup, no partials) where their own time is less than
+// the wave tiles'.  Theirs, us, over 520 shapes each of 64 x 128 and 128 x 128 tiles (within 0.9 to 1.1 for 9 of 10):
+// a fixed part, one per tile of a CU and the FMAs at 175 / 189 (FP32 weights 169 / 179) per ns and CU.  The wave tiles'
+// estimate is high by a fifth there, less with one or three waves per workgroup, and with two whose workgroups
+// fill the second or third round to the last few (0.8 of the estimate becomes 1.1 there).  Measured, register against wave tiles, us: 1906 x 4288 x 360 81 against 109, 1483 x 4770 x 736 145 against
+// 211, 2048 x 3072 x 1536 249 against 298; FP32 102 x 32768 x 1096 129 against 167; 333 x 28672 x 4096 stays (1118
+// against 931).
+bool register_tiles_lead(int64_t M, int64_t N, int64_t K, bool f32, const rg::WtileChoice& c) {
+    Plan p;
+    const rg_launch_t none = {};
+    if (M <= kDecodeMaxM || K > (f32 ? 2560 : 1792)) return false;   // (from there on within a tenth, either way)
+    if (tiled_schedule(M, N, none, &p) != RG_OK || p.tile_n < 128) return false;
+    const int64_t percu = ceil_div((int64_t)p.grid, kNominalCUs);
+    if (percu < 2) return false;
+    const bool big = p.tile_m == 128;
+    const double rate = big ? (f32 ? 179.0 : 189.0) : (f32 ? 169.0 : 175.0);
+    const double us = (big ? (f32 ? 3.3 : 0.5) : (f32 ? 3.8 : 4.7)) +
+                      (double)percu * ((big ? 5.5 : 1.6) + (double)p.tile_m * p.tile_n * (double)K / (rate * 1000.0));
+    int nb = 0;
+    const rg::WtileBuild& b = rg::wtile_builds(f32, true, &nb)[c.build];
+    const double rounds = (double)(ceil_div(M, b.bm) * ceil_div(N, b.bn) * c.waves) / (8.0 * kNominalCUs);
+    const double part = rounds - (double)(int64_t)rounds;
+    double high = f32 ? 0.76 : 0.8;
+    if (c.waves == 1) high *= rounds > 1.0 ? (f32 ? 1.06 : 1.18) : (f32 ? 0.9 : 0.95);
+    if (c.waves == 2 && rounds > 1.0) {
+        if (b.bm <= 16) high *= 1.15;
+        else if (rounds <= 3.0 && (part == 0.0 || part > 0.955)) high *= f32 ? 1.16 : 1.35;
+    }
+    if (!f32 && (c.waves == 3 || c.waves == 5) && rounds > 1.0) high *= 1.2;
+    return us < high * (c.us + 2.5);
+}
+
 // The wave tile a shape runs on by default, if it is the better kernel for it.
 rg::WtileChoice wave_tile_choice(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
     rg::WtileChoice c = rg::wtile_choose(M, N, K, f32, aligned);
     if (!c.ok) return c;
     if (!aligned) return c;
-    if (M <= kDecodeMaxM && !f32) c.ok = !skinny_leads(M, N, K, c);
+    if (M > kDecodeMaxM) c.ok = !register_tiles_lead(M, N, K, f32, c);
+    else if (!f32) c.ok = !skinny_leads(M, N, K, c);
     return c;
 }
 

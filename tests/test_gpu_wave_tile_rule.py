@@ -85,6 +85,8 @@ def test_odd_k_builds(M, N, K, f32):
 @pytest.mark.parametrize("M,N,K,f32,kernel", [
     (9, 300, 28672, False, "skinny"), (16, 1024, 1024, False, "skinny"), (64, 250, 7056, False, "skinny"),
     (33, 40, 2056, False, "skinny"), (13, 64, 32168, False, "skinny"),
+    (1906, 4288, 360, False, "tiled"), (2000, 4096, 1032, False, "tiled"), (249, 27072, 304, False, "tiled"),
+    (142, 28835, 320, True, "tiled"), (2000, 4096, 1036, True, "tiled"), (487, 11335, 388, True, "tiled"),
 ])
 def test_defaults_that_other_kernels_lead(M, N, K, f32, kernel):
     import paper_2609_25624_amd as rg
