@@ -522,12 +522,20 @@ bool register_tiles_lead(int64_t M, int64_t N, int64_t K, bool f32, const rg::Wt
     return us < high * (c.us + 2.5);
 }
 
+// Unaligned calls of a few k: one thread per output has nothing to stage.  Measured, generic against wave tile, us
+// (BF16): 51 x 231036 x 1 23.0 against 29.2, 8 x 52136 x 5 3.6 against 5.0, 1 x 187328 x 21 5.6 against 7.4; behind
+// beyond (94 x 157301 x 3 35 against 27.5).
+bool generic_leads(int64_t M, int64_t N, int64_t K, bool f32) {
+    return (K < 4 && M <= 64) || (K < 6 && M * N < (f32 ? 700000 : 1500000)) || (K < 8 && M * N < (f32 ? 300000 : 700000)) ||
+           (!f32 && M <= 2 && K < 24 && N < 300000);
+}
+
 // The wave tile a shape runs on by default, if it is the better kernel for it.
 rg::WtileChoice wave_tile_choice(int64_t M, int64_t N, int64_t K, bool f32, bool aligned) {
     rg::WtileChoice c = rg::wtile_choose(M, N, K, f32, aligned);
     if (!c.ok) return c;
-    if (!aligned) return c;
-    if (M > kDecodeMaxM) c.ok = !register_tiles_lead(M, N, K, f32, c);
+    if (!aligned) c.ok = !generic_leads(M, N, K, f32);
+    else if (M > kDecodeMaxM) c.ok = !register_tiles_lead(M, N, K, f32, c);
     else if (!f32) c.ok = !skinny_leads(M, N, K, c);
     return c;
 }
