@@ -30,6 +30,7 @@
 
 #include <type_traits>
 
+#include "rg_attn_rule.h"
 #include "rg_kernels.h"
 
 namespace rg {
@@ -878,7 +879,7 @@ __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
 
 // The whole call for one (sequence, kv head) in one workgroup of eight waves, with barriers in place of launches.
 template <int GP, int D, int CS>
-__global__ void __launch_bounds__(512, 2) attn_fused_kernel(AttnArgs a) {
+__global__ void __launch_bounds__(kAttnFusedThreads, 2) attn_fused_kernel(AttnArgs a) {
     using KS = KeySteps<GP, D>;
     using VS = ValueSteps<GP, D, CS>;
     constexpr int RING = KS::RING > VS::RING ? KS::RING : VS::RING;
@@ -947,36 +948,23 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
     return hipGetLastError();
 }
 
-// Fixed head dims (64, 128, 256).
-//
-// Fused (one launch) where the cache holds at most two segments per sequence, so that launches and their gaps are most of
-// the time, or eight with the lightest heads; one launch per pass otherwise: a workgroup per (sequence, kv head)
-// takes as long as its longest sequence, which the passes spread over the device.  Whole calls, us, fused
-// against one launch per pass (4 sequences, 2 kv heads, 400 positions): D = 128, 1 / 2 / 4 heads per kv head 12.6 / 16.9 /
-// 22.6 against 16.2 / 20.5 / 24.5 and their two gaps, 8 heads level; D = 256, 1 / 2 / 4 heads 18.0 / 25.0 / 36.7
-// against 26 / 27 / 34.7; D = 64, 1 / 2 / 4 / 8 heads 10.7 / 13.8 / 17.7 / 24.4 against 15 / 17 / 19 / 24.
+// Fixed head dims (64, 128, 256), by attn_route.
 //
 // Scores: 64-column key steps (32 KB tiles, four workgroups per CU); with eight query heads per kv head the
 // two-positions-per-thread kernel (32-column steps, 128 threads, about 20 KB of LDS; measured 111 -> 90 us
 // for the scores of a 32 x 64-head, 4096-position batch, and 0-22 % slower than the 64-column kernel with six or fewer heads).
-//
-// Partials: one wave per segment, or two with half its value columns each where there are at most four segments per CU
-// (64 of D = 64 fill a wave as they are; the heaviest waves, D = 256 with more than four heads, are always split).
-// Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
-// 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
-// 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0 (a workgroup per segment before; that
-// kernel stays for four and more heads and at most 1.25 segments per CU: eight heads 11.8 against 15.9, four heads 11.2
-// against 12.0).
 template <int G, int D>
 hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
-    constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
+    constexpr int GP = attn_lanes(G);
+    const AttnRoute route = attn_route(a.B, a.Hkv, a.Lmax, D, G, cus);
     // (more in flight per wave costs waves: slower but for the heaviest rows)
     constexpr int RING1 = GP == 8 ? 12288 : 8192, RING2 = GP == 8 || D == 256 ? 12288 : 8192;
     const int64_t items = a.B * a.Hkv * a.J;
     if constexpr (D * GP <= 512) {
-        if (a.J <= 2 || (D * GP == 64 && a.J <= 8)) {
+        if (route.fused) {
             constexpr int CS = D == 64 ? 1 : 2;
-            hipLaunchKernelGGL((attn_fused_kernel<GP, D, CS>), dim3((unsigned)(a.B * a.Hkv)), dim3(512), 0, stream, a);
+            hipLaunchKernelGGL((attn_fused_kernel<GP, D, CS>), dim3((unsigned)(a.B * a.Hkv)), dim3(kAttnFusedThreads), 0,
+                               stream, a);
             return hipGetLastError();
         }
     }
@@ -991,7 +979,7 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (D == 64 && G >= 4 && 4 * items <= 5 * (int64_t)cus) {
+    if (route.group) {
         constexpr int RS = 16384 / 64;
         hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 255) / 256)), dim3(256), 0, stream, a);
         e = hipGetLastError();
@@ -999,13 +987,12 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
         if constexpr (D == 64 && G >= 4)
             hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
-        const bool split = D > 64 && ((D == 256 && GP == 8) || items <= 4 * (int64_t)cus);
-        const int64_t units = items * (split ? 2 : 1);
+        const int64_t units = items * (route.split ? 2 : 1);
         const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
         if constexpr (D > 64) {
-            if (split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RING2>), grid, dim3(64), 0, stream, a);
+            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RING2>), grid, dim3(64), 0, stream, a);
         }
-        if (!split) {
+        if (!route.split) {
             if constexpr (!(D == 256 && GP == 8))
                 hipLaunchKernelGGL((attn_values_kernel<GP, D, 1, RING1>), grid, dim3(64), 0, stream, a);
         }

@@ -8,6 +8,7 @@
 
 #include "../../include/rg.h"
 #include "../../include/rg_attn.h"
+#include "../../paper_2609_25624_amd/csrc/rg_attn_rule.h"
 #include "../../paper_2609_25624_amd/csrc/rg_kernels.h"
 #include "../../paper_2609_25624_amd/csrc/rg_wtile.h"
 
@@ -183,6 +184,18 @@ int main() {
                         printf("entry %d (%ld,%ld,%ld): status %d, launched %d\n", entry, (long)M, (long)(MN / M), (long)K,
                                st, seen.kernel);
                         return 6;
+                    }
+                }
+    // attention: the one-launch kernel only where its threads fit a launch
+    for (int64_t pairs : {(int64_t)1, (int64_t)1 << 22, ((int64_t)1 << 23) - 1, (int64_t)1 << 23, (int64_t)1 << 24, (int64_t)1 << 28})
+        for (int D : {64, 128, 256})
+            for (int G = 1; G <= 8; ++G)
+                for (int64_t L : {1, 256, 512, 2048}) {
+                    if (pairs * ((L + 255) / 256) > 0x3fffffff) continue;
+                    const rg::AttnRoute r = rg::attn_route(pairs, 1, L, D, G, 256);
+                    if (r.fused && pairs * rg::kAttnFusedThreads > 0xffffffffLL) {
+                        printf("fused: %ld pairs D %d G %d L %ld\n", (long)pairs, D, G, (long)L);
+                        return 8;
                     }
                 }
     // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel

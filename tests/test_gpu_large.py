@@ -92,3 +92,21 @@ def test_attention_caches_beyond_4_gib():
     # the first sequence (its positions lie in the first block) against the oracle
     want0 = oracle.attn_decode(q[:1], kb[:1], vb[:1], lens[:1], scale)
     assert np.array_equal(gu.bits(got[:1]), gu.bits(want0)), "first sequence vs oracle"
+
+
+def test_attention_of_more_pairs_than_the_one_launch_kernel_holds():
+    """2^23 (sequence, kv head) pairs of one position each: the one-launch kernel's 512 threads per pair would be
+    2^32, so the passes run.  One position: e = 1, the output is its value."""
+    import torch
+    import paper_2609_25624_amd as rg
+    B, H, D = 1 << 20, 8, 64
+    g = torch.Generator(device=gu.dev())
+    g.manual_seed(5)
+    q = torch.empty((B, H, D), dtype=torch.float32, device=gu.dev()).normal_(generator=g)
+    k = torch.empty((B, H, 1, D), dtype=torch.bfloat16, device=gu.dev()).normal_(generator=g)
+    v = torch.empty((B, H, 1, D), dtype=torch.bfloat16, device=gu.dev()).normal_(generator=g)
+    out = torch.full((B, H, D), 7.0, dtype=torch.float32, device=gu.dev())
+    gu.log(f"attention pairs: {B * H}")
+    rg.rg_attn_decode(q, k, v, torch.ones(B, dtype=torch.int32, device=gu.dev()), out, 0.125)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), v.view(B, H, D).float().view(torch.int32))
