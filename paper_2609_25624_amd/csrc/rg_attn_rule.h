@@ -16,12 +16,19 @@ constexpr int attn_lanes(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 
 
 constexpr int kAttnFusedThreads = 512;
 
-// Fused (one launch) where the cache holds at most two segments per sequence, so that launches and their gaps are most of
-// the time, or eight with the lightest heads; one launch per pass otherwise: a workgroup per (sequence, kv head)
-// takes as long as its longest sequence, which the passes spread over the device.  Whole calls, us, fused
-// against one launch per pass (4 sequences, 2 kv heads, 400 positions): D = 128, 1 / 2 / 4 heads per kv head 12.6 / 16.9 /
-// 22.6 against 16.2 / 20.5 / 24.5 and their two gaps, 8 heads level; D = 256, 1 / 2 / 4 heads 18.0 / 25.0 / 36.7
-// against 26 / 27 / 34.7; D = 64, 1 / 2 / 4 / 8 heads 10.7 / 13.8 / 17.7 / 24.4 against 15 / 17 / 19 / 24.
+// Fused (one launch) for short caches, where launches and their gaps are most of the time; one launch per pass otherwise.
+// A CU holds one of its workgroups (115 to 147 KB of LDS), each as slow as its longest sequence and with half its waves
+// idle at two segments, so it leads only while the pairs run in one round of the CUs.  Whole calls, us, fused against one
+// launch per pass (ragged batches, pairs of sequence and kv head x longest length; D and query heads per kv head):
+//   one or two heads, at most two segments      D = 64, 1: 256 x 512 11.7 / 16.3, 512 x 512 21.0 / 18.6, 2048 x 256 64 / 26;
+//                                               D = 128, 2: 256 x 512 18.5 / 23, 512 x 256 28 / 22; D = 256, 1: 256 x 512
+//                                               23.3 / 26.9; D = 256, 2, two segments: 64 x 512 29.7 / 26.1 (one only)
+//   one head, D = 64, up to eight segments      256 x 2048 20 / 31; above a round of the CUs 512 x 1024 25.8 / 27.0,
+//                                               2048 x 1024 99 / 82, 2048 x 2048 145 / 171
+//   one head, at most 128 positions             two rounds too: D = 128, 512 x 128 16.0 / 16.4
+//   three or four heads, one segment            D = 64: 64 x 256 17.4 / 17.8 (the group kernel), 128 x 128 12.0 / 15.7;
+//   or two on more than half the CUs            D = 128: 64 x 256 21.1 / 21.9, 64 x 512 24.1 / 22.6, 256 x 512 24.7 / 27.1
+//   five to eight heads, D = 64                 64 x 128 16.6 / 21.1, 64 x 256 24 / 21 (at most 128 positions)
 // Its launch must hold its threads (a launch has at most 2^32 - 1).
 //
 // Partials: one wave per segment, or two with half its value columns each where there are at most four segments per CU
@@ -35,7 +42,14 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     const int GP = attn_lanes(G);
     const int64_t J = (Lmax + 255) / 256, pairs = B * Hkv, items = pairs * J;
     AttnRoute r = {};
-    r.fused = D * GP <= 512 && (J <= 2 || (D * GP == 64 && J <= 8)) && pairs <= 0xffffffffLL / kAttnFusedThreads;
+    const bool round = pairs <= cus;
+    if (D * GP > 512) r.fused = false;
+    else if (GP == 8) r.fused = round && Lmax <= 128;
+    else if (GP == 4) r.fused = round && (J == 1 || (J == 2 && 2 * pairs > cus));
+    else if (GP == 2) r.fused = round && J <= (D == 256 ? 1 : 2);
+    else if (D == 64 && J > 2) r.fused = J <= 8 && (round || J >= 7 || (J >= 4 && pairs <= 2 * cus));
+    else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
+    if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
     r.group = !r.fused && D == 64 && G >= 4 && 4 * items <= 5 * cus;
     r.split = D > 64 && ((D == 256 && GP == 8) || items <= 4 * cus);
     return r;

@@ -198,6 +198,19 @@ int main() {
                         return 8;
                     }
                 }
+    // and only where it was measured ahead of one launch per pass: a round of the CUs, short caches of heavy groups
+    const struct { int64_t pairs, L; int D, G; bool fused; } short_caches[] = {
+        {8, 512, 64, 1, true}, {256, 512, 64, 1, true}, {512, 512, 64, 1, false}, {2048, 64, 64, 1, false},
+        {8192, 256, 64, 1, false}, {256, 2048, 64, 1, true}, {2048, 1024, 64, 1, false}, {2048, 2048, 64, 1, true},
+        {512, 1100, 64, 1, true}, {256, 512, 128, 2, true}, {512, 128, 128, 2, false}, {512, 128, 128, 1, true},
+        {512, 128, 256, 1, false}, {64, 200, 256, 2, true}, {64, 400, 256, 2, false}, {8, 256, 64, 4, true},
+        {8, 300, 64, 4, false}, {200, 300, 64, 4, true}, {257, 64, 128, 4, false}, {64, 128, 64, 8, true},
+        {64, 129, 64, 5, false}, {4, 100, 128, 8, false}};
+    for (const auto& c : short_caches)
+        if (rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256).fused != c.fused) {
+            printf("fused %d: %ld pairs x %ld, D %d, G %d\n", !c.fused, (long)c.pairs, (long)c.L, c.D, c.G);
+            return 9;
+        }
     // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel
     rg_linear_set_launch(nullptr);
     for (hipError_t err : {hipErrorInvalidValue, hipErrorInvalidConfiguration, hipErrorOutOfMemory})
