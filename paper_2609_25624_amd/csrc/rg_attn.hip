@@ -984,7 +984,7 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
         hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 255) / 256)), dim3(256), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if constexpr (D == 64 && G >= 4)
+        if constexpr (D == 64 && G >= 3)
             hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
         const int64_t units = items * (route.split ? 2 : 1);
