@@ -679,15 +679,15 @@ __device__ __forceinline__ float key_pass(const AttnArgs& a, int b, int g, int G
 // Segment partials of units first, first + stride, ... below Jb * CS (segment unit / CS, value columns part unit % CS) of
 // kv head g of sequence b.  The value stream starts, then row_max(m) brings the group's row maxima;
 // the wave turns t into e (LDS, [position][head], EC positions at a time) and lane p runs the numerator chains of its
-// columns for all heads.  Lanes < G sum e.
-template <int GP, int D, int CS, int RINGB, typename F>
+// columns for GH heads (the group's G where the kernel is built for them, else GP).  Lanes < G sum e.
+template <int GH, int GP, int D, int CS, int RINGB, typename F>
 __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int G, int L, int Jb, int first, int stride,
                                            uint8_t* ring, float* es, F row_max) {
     using VS = ValueSteps<GP, D, CS, RINGB>;
     constexpr int DH = VS::DH, RS = VS::RS, EC = VS::EC, NS = VS::RING / 4096, NI = 4;
     constexpr int SEG = kAttnSeg / RS;                // steps of a whole segment
     constexpr int SVC = EC / RS;                      // steps per chunk of e
-    constexpr int NT = EC * GP / 64;                  // scores per lane per chunk
+    constexpr int NT = EC * GH / 64;                  // scores per lane per chunk
     constexpr int PPL = DH >= 128 ? DH / 128 : 0;     // value pairs per lane (0: one column)
     constexpr int NC = PPL > 0 ? PPL : 1;
     static_assert(EC % RS == 0 && kAttnSeg % EC == 0, "value step");
@@ -715,26 +715,26 @@ __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int 
             attn_dma16(sb, (uint32_t)(min(row, rmax) * (D * 2) + 16 * pc), slot + 1024u * i);
         }
     };
-    float tr[NT];                                     // score (position lane + 64 i, head h) at GP i + h
+    float tr[NT];                                     // score (position lane + 64 i, head h) at GH i + h
     auto tload = [&](int s) {                         // the chunk that begins at step s
         const int u = s / SEG, r = s - u * SEG;
         const int l0 = (first + stride * u) / CS * kAttnSeg + r * RS;
 #pragma unroll
         for (int i = 0; i < EC / 64; ++i)
 #pragma unroll
-            for (int h = 0; h < GP; ++h) {
+            for (int h = 0; h < GH; ++h) {
                 // (past L the last score again: its e is never used)
                 const int l = min(l0 + lane + 64 * i, L - 1);
-                tr[GP * i + h] = tb[(int64_t)(h < G ? h : G - 1) * a.Lmax + l];
+                tr[GH * i + h] = tb[(int64_t)(h < G ? h : G - 1) * a.Lmax + l];
             }
     };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
         if (s < S) issue(s);
-    float m[GP];
+    float m[GH];
     row_max(m);
     if (S > 0) tload(0);
-    float n0[NC][GP], n1[NC][GP], ssum = 0.0f;
+    float n0[NC][GH], n1[NC][GH], ssum = 0.0f;
 #pragma unroll 1
     for (int s = 0; s < S; ++s) {
         const int u = s / SEG, r = s - u * SEG;
@@ -746,7 +746,7 @@ __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int 
 #pragma unroll
             for (int i = 0; i < EC / 64; ++i)
 #pragma unroll
-                for (int h = 0; h < GP; ++h) es[(lane + 64 * i) * GP + h] = exp1_select(tr[GP * i + h] - m[h]);
+                for (int h = 0; h < GH; ++h) es[(lane + 64 * i) * GP + h] = exp1_select(tr[GH * i + h] - m[h]);
             // the next chunk's scores: of this unit if it has more rows, else of the next unit
             const int next = (r + SVC) * RS < rows ? s + SVC : (u + 1) * SEG;
             if (next < S) tload(next);
@@ -754,7 +754,7 @@ __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int 
 #pragma unroll
                 for (int k = 0; k < NC; ++k)
 #pragma unroll
-                    for (int h = 0; h < GP; ++h) n0[k][h] = n1[k][h] = 0.0f;
+                    for (int h = 0; h < GH; ++h) n0[k][h] = n1[k][h] = 0.0f;
                 ssum = 0.0f;
             }
         }
@@ -764,22 +764,22 @@ __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int 
         if (s + NS - 1 < S) issue(s + NS - 1);
         const uint16_t* vw = reinterpret_cast<const uint16_t*>(ring + s % NS * 4096);
         const float* er = es + (r % SVC) * (RS * GP);
-        const float* eo = er + (lane < GP ? lane : 0);
+        const float* eo = er + (lane < GH ? lane : 0);
         auto row_step = [&](int l) {
-            float ev[GP];
+            float ev[GH];
 #pragma unroll
-            for (int h = 0; h < GP; ++h) ev[h] = er[l * GP + h];
+            for (int h = 0; h < GH; ++h) ev[h] = er[l * GP + h];
             if constexpr (PPL == 0) {
                 const float v1 = __uint_as_float((uint32_t)vw[l * DH + lane] << 16);
 #pragma unroll
-                for (int h = 0; h < GP; ++h) n0[0][h] = __builtin_fmaf(ev[h], v1, n0[0][h]);
+                for (int h = 0; h < GH; ++h) n0[0][h] = __builtin_fmaf(ev[h], v1, n0[0][h]);
             } else {
 #pragma unroll
                 for (int k = 0; k < PPL; ++k) {
                     const uint32_t v2 = *reinterpret_cast<const uint32_t*>(vw + l * DH + 128 * k + 2 * lane);
                     const float vlo = __uint_as_float(v2 << 16), vhi = __uint_as_float(v2 & 0xffff0000u);
 #pragma unroll
-                    for (int h = 0; h < GP; ++h) {
+                    for (int h = 0; h < GH; ++h) {
                         n0[k][h] = __builtin_fmaf(ev[h], vlo, n0[k][h]);
                         n1[k][h] = __builtin_fmaf(ev[h], vhi, n1[k][h]);
                     }
@@ -796,7 +796,7 @@ __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int 
         }
         if (r * RS + RS >= rows) {                    // the unit's last step
 #pragma unroll
-            for (int h = 0; h < GP; ++h) {
+            for (int h = 0; h < GH; ++h) {
                 if (h >= G) break;
                 float* nb = a.npart + ((h0 + h) * a.J + j) * D + part * DH;
                 if constexpr (PPL == 0) {
@@ -848,8 +848,9 @@ __device__ __forceinline__ void fold_out(const AttnArgs& a, int64_t bh, int d, i
 // segment maxima itself (exact, so no launch of the maximum kernel).  One unit per workgroup (more only beyond the
 // largest grid): the waves of a CU are then at different points of their units, and a short sequence's
 // waves leave at once.
-template <int GP, int D, int CS, int RINGB>
+template <int GH, int D, int CS, int RINGB>
 __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
+    constexpr int GP = attn_lanes(GH);
     __shared__ __attribute__((aligned(16))) uint8_t ring[RINGB];
     __shared__ __attribute__((aligned(16))) float es[ValueSteps<GP, D, CS>::EC * GP];
     const int lane = threadIdx.x;
@@ -861,17 +862,17 @@ __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
         const int b = __builtin_amdgcn_readfirstlane(w.b), g = __builtin_amdgcn_readfirstlane(w.g);
         const int j = __builtin_amdgcn_readfirstlane(w.j), L = __builtin_amdgcn_readfirstlane(w.L);
         const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
-        value_pass<GP, D, CS, RINGB>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GP]) {
+        value_pass<GH, GP, D, CS, RINGB>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GH]) {
             const float* sm = a.segmax + ((int64_t)b * a.H + (int64_t)g * G) * a.J;
 #pragma unroll
-            for (int h = 0; h < GP; ++h) m[h] = -__builtin_inff();
+            for (int h = 0; h < GH; ++h) m[h] = -__builtin_inff();
             for (int j0 = lane; j0 < Jb; j0 += 64)
 #pragma unroll
-                for (int h = 0; h < GP; ++h) m[h] = __builtin_fmaxf(m[h], sm[(int64_t)(h < G ? h : G - 1) * a.J + j0]);
+                for (int h = 0; h < GH; ++h) m[h] = __builtin_fmaxf(m[h], sm[(int64_t)(h < G ? h : G - 1) * a.J + j0]);
 #pragma unroll
             for (int sh = 32; sh > 0; sh >>= 1)
 #pragma unroll
-                for (int h = 0; h < GP; ++h) m[h] = __builtin_fmaxf(m[h], __shfl_xor(m[h], sh, 64));
+                for (int h = 0; h < GH; ++h) m[h] = __builtin_fmaxf(m[h], __shfl_xor(m[h], sh, 64));
         });
         attn_lds_wait();                              // before the next unit's rows arrive
     }
@@ -894,7 +895,7 @@ __global__ void __launch_bounds__(kAttnFusedThreads, 2) attn_fused_kernel(AttnAr
     const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
     const int nunits = (L + KS::UNIT - 1) / KS::UNIT;
     float mymax = key_pass<GP, D>(a, b, g, G, L, wave, 8, wave < nunits ? (nunits - 1 - wave) / 8 + 1 : 0, ring[wave]);
-    value_pass<GP, D, CS, VS::RING>(a, b, g, G, L, Jb, wave, 8, ring[wave], es[wave], [&](float (&m)[GP]) {
+    value_pass<GP, GP, D, CS, VS::RING>(a, b, g, G, L, Jb, wave, 8, ring[wave], es[wave], [&](float (&m)[GP]) {
         // the maxima over the lanes of each head, then over the waves (through the e region, free until then)
         float v = mymax;
 #pragma unroll
@@ -955,7 +956,9 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
 // for the scores of a 32 x 64-head, 4096-position batch, and 0-22 % slower than the 64-column kernel with six or fewer heads).
 template <int G, int D>
 hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
-    constexpr int GP = attn_lanes(G);
+    // heads of a values wave: five and six their own number, three and seven the next power of two (their e are then
+    // read as whole vectors: 32 x 8 pairs of 4096 positions at D = 64 with three heads 58 us, 62 with chains for three)
+    constexpr int GP = attn_lanes(G), GH = G == 5 || G == 6 ? G : GP;
     const AttnRoute route = attn_route(a.B, a.Hkv, a.Lmax, D, G, cus);
     // (more in flight per wave costs waves: slower but for the heaviest rows)
     constexpr int RING1 = GP == 8 ? 12288 : 8192, RING2 = GP == 8 || D == 256 ? 12288 : 8192;
@@ -990,11 +993,11 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
         const int64_t units = items * (route.split ? 2 : 1);
         const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
         if constexpr (D > 64) {
-            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GP, D, 2, RING2>), grid, dim3(64), 0, stream, a);
+            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GH, D, 2, RING2>), grid, dim3(64), 0, stream, a);
         }
         if (!route.split) {
             if constexpr (!(D == 256 && GP == 8))
-                hipLaunchKernelGGL((attn_values_kernel<GP, D, 1, RING1>), grid, dim3(64), 0, stream, a);
+                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, RING1>), grid, dim3(64), 0, stream, a);
         }
     }
     e = hipGetLastError();
