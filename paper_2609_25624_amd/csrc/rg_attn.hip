@@ -554,11 +554,11 @@ struct KeySteps {
     static constexpr int NS = RING / STEP;                      // steps in the ring
     static constexpr int UNIT = 128;                            // positions per unit
 };
-template <int GP, int D, int CS, int RINGB = 12288>
+template <int GP, int D, int CS, int RINGB = 12288, int ECP = GP >= 4 ? 128 : 256>
 struct ValueSteps {
     static constexpr int DH = D / CS;                           // value columns of a unit
     static constexpr int RS = 4096 / (DH * 2);                  // value rows per 4 KB step
-    static constexpr int EC = GP >= 4 ? 128 : 256;              // positions whose e are in LDS at a time
+    static constexpr int EC = ECP;                              // positions whose e are in LDS at a time
     static constexpr int RING = RINGB;
 };
 
@@ -680,10 +680,9 @@ __device__ __forceinline__ float key_pass(const AttnArgs& a, int b, int g, int G
 // kv head g of sequence b.  The value stream starts, then row_max(m) brings the group's row maxima;
 // the wave turns t into e (LDS, [position][head], EC positions at a time) and lane p runs the numerator chains of its
 // columns for GH heads (the group's G where the kernel is built for them, else GP).  Lanes < G sum e.
-template <int GH, int GP, int D, int CS, int RINGB, typename F>
+template <int GH, typename VS, int GP, int D, int CS, typename F>
 __device__ __forceinline__ void value_pass(const AttnArgs& a, int b, int g, int G, int L, int Jb, int first, int stride,
                                            uint8_t* ring, float* es, F row_max) {
-    using VS = ValueSteps<GP, D, CS, RINGB>;
     constexpr int DH = VS::DH, RS = VS::RS, EC = VS::EC, NS = VS::RING / 4096, NI = 4;
     constexpr int SEG = kAttnSeg / RS;                // steps of a whole segment
     constexpr int SVC = EC / RS;                      // steps per chunk of e
@@ -848,11 +847,11 @@ __device__ __forceinline__ void fold_out(const AttnArgs& a, int64_t bh, int d, i
 // segment maxima itself (exact, so no launch of the maximum kernel).  One unit per workgroup (more only beyond the
 // largest grid): the waves of a CU are then at different points of their units, and a short sequence's
 // waves leave at once.
-template <int GH, int D, int CS, int RINGB>
+template <int GH, int D, int CS, int RINGB, int EC>
 __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
     constexpr int GP = attn_lanes(GH);
     __shared__ __attribute__((aligned(16))) uint8_t ring[RINGB];
-    __shared__ __attribute__((aligned(16))) float es[ValueSteps<GP, D, CS>::EC * GP];
+    __shared__ __attribute__((aligned(16))) float es[EC * GP];
     const int lane = threadIdx.x;
     const int G = (int)(a.H / a.Hkv);
     const uint32_t units = (uint32_t)(a.B * a.Hkv * a.J) * CS;
@@ -862,7 +861,7 @@ __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
         const int b = __builtin_amdgcn_readfirstlane(w.b), g = __builtin_amdgcn_readfirstlane(w.g);
         const int j = __builtin_amdgcn_readfirstlane(w.j), L = __builtin_amdgcn_readfirstlane(w.L);
         const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
-        value_pass<GH, GP, D, CS, RINGB>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GH]) {
+        value_pass<GH, ValueSteps<GP, D, CS, RINGB, EC>, GP, D, CS>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GH]) {
             const float* sm = a.segmax + ((int64_t)b * a.H + (int64_t)g * G) * a.J;
 #pragma unroll
             for (int h = 0; h < GH; ++h) m[h] = -__builtin_inff();
@@ -895,7 +894,7 @@ __global__ void __launch_bounds__(kAttnFusedThreads, 2) attn_fused_kernel(AttnAr
     const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
     const int nunits = (L + KS::UNIT - 1) / KS::UNIT;
     float mymax = key_pass<GP, D>(a, b, g, G, L, wave, 8, wave < nunits ? (nunits - 1 - wave) / 8 + 1 : 0, ring[wave]);
-    value_pass<GP, GP, D, CS, VS::RING>(a, b, g, G, L, Jb, wave, 8, ring[wave], es[wave], [&](float (&m)[GP]) {
+    value_pass<GP, VS, GP, D, CS>(a, b, g, G, L, Jb, wave, 8, ring[wave], es[wave], [&](float (&m)[GP]) {
         // the maxima over the lanes of each head, then over the waves (through the e region, free until then)
         float v = mymax;
 #pragma unroll
@@ -960,8 +959,10 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     // read as whole vectors: 32 x 8 pairs of 4096 positions at D = 64 with three heads 58 us, 62 with chains for three)
     constexpr int GP = attn_lanes(G), GH = G == 5 || G == 6 ? G : GP;
     const AttnRoute route = attn_route(a.B, a.Hkv, a.Lmax, D, G, cus);
-    // (more in flight per wave costs waves: slower but for the heaviest rows)
-    constexpr int RING1 = GP == 8 ? 12288 : 8192, RING2 = GP == 8 || D == 256 ? 12288 : 8192;
+    // bytes in flight of a whole-row wave and of one with half the columns, and positions whose e it holds (more per wave
+    // costs waves: slower but for the heaviest rows)
+    constexpr int RING1 = GP == 8 ? 12288 : 8192, RING2 = GP == 8 || (D == 256 && GP < 4) ? 12288 : 8192;
+    constexpr int EC = GP >= 4 ? 128 : 256;
     const int64_t items = a.B * a.Hkv * a.J;
     if constexpr (D * GP <= 512) {
         if (route.fused) {
@@ -993,11 +994,14 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
         const int64_t units = items * (route.split ? 2 : 1);
         const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
         if constexpr (D > 64) {
-            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GH, D, 2, RING2>), grid, dim3(64), 0, stream, a);
+            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GH, D, 2, RING2, EC>), grid, dim3(64), 0, stream, a);
         }
-        if (!route.split) {
+        if constexpr (D > 64 && GP == 8) {
+            if (route.light) hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, 8192, 64>), grid, dim3(64), 0, stream, a);
+        }
+        if (!route.split && !route.light) {
             if constexpr (!(D == 256 && GP == 8))
-                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, RING1>), grid, dim3(64), 0, stream, a);
+                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, RING1, EC>), grid, dim3(64), 0, stream, a);
         }
     }
     e = hipGetLastError();

@@ -9,6 +9,7 @@ struct AttnRoute {
     bool fused;    // one launch: a workgroup of eight waves per (sequence, kv head)
     bool group;    // partials by a workgroup per segment (D = 64), after the maximum kernel
     bool split;    // partials by two waves per segment, half the value columns each; one wave otherwise
+    bool light;    // ... by one wave with less LDS (five to eight heads), so that a CU holds sixteen
 };
 
 // Lanes (of a position) that a group of G query heads takes: the power of two it fits.
@@ -31,8 +32,14 @@ constexpr int kAttnFusedThreads = 512;
 //   five to eight heads, D = 64                 64 x 128 16.6 / 21.1, 64 x 256 24 / 21 (at most 128 positions)
 // Its launch must hold its threads (a launch has at most 2^32 - 1).
 //
-// Partials: one wave per segment, or two with half its value columns each where there are at most four segments per CU
-// (64 of D = 64 fill a wave as they are; the heaviest waves, D = 256 with more than four heads, are always split).
+// Partials: one wave per segment, or two with half its value columns each where there are few segments (64 of D = 64 fill a
+// wave as they are): at most four per CU, three at D = 128 with two and more heads (32 x 8 pairs of 1000 positions, 1024
+// segments: four heads 38.1 split, 35.2 whole; one head 27.8 / 29.6; D = 256, eight heads 79.9 / 89.4).  With five to
+// eight heads many segments want waves more than bytes in flight per wave (8 KB of rows and the e of 64 positions in
+// place of 12 KB and 128): from eight segments per CU at D = 128, from five at D = 256, where both halves of a split
+// segment compute all its e.  Whole calls, us, heavy / light: D = 128, eight heads 256 x 8 pairs of 384 positions 138 / 126, 64 x 8
+// of 2048 155 / 144; 64 x 8 of 384 (1024 segments) 55 / 59; D = 256, eight heads (split / light) 256 x 8 of 384 250 / 218, 64 x 8 of
+// 1024 150 / 146, of 384 (1024 segments) 80 / 88; seven heads 28 x 8 of 1156 (1120 segments) 76 / 84.
 // Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
 // 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
 // 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0.
@@ -56,7 +63,8 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
     if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
     r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && items <= 3 * cus;
-    r.split = D > 64 && ((D == 256 && GP == 8) || items <= 4 * cus);
+    r.split = D > 64 && items <= (D == 256 && GP == 8 ? 5 : D == 128 && GP > 1 ? 3 : 4) * cus;
+    r.light = D > 64 && GP == 8 && items > (D == 128 ? 8 : 5) * cus;
     return r;
 }
 

@@ -220,6 +220,19 @@ int main() {
             printf("group %d: %ld pairs x %ld, G %d\n", !c.group, (long)c.pairs, (long)c.L, c.G);
             return 10;
         }
+    // value waves: split, whole or light
+    const struct { int64_t pairs, L; int D, G, split, light; } waves[] = {
+        {16, 1024, 128, 4, 1, 0}, {192, 1024, 128, 4, 1, 0}, {256, 1024, 128, 4, 0, 0}, {256, 1024, 128, 1, 1, 0},
+        {257, 1024, 128, 1, 0, 0}, {256, 1024, 128, 8, 0, 0}, {512, 1024, 128, 8, 0, 0}, {513, 1024, 128, 5, 0, 1},
+        {2048, 1024, 128, 4, 0, 0}, {320, 1024, 256, 8, 1, 0}, {321, 1024, 256, 5, 0, 1}, {257, 1024, 256, 4, 0, 0},
+        {256, 1024, 256, 1, 1, 0}, {16, 1024, 64, 8, 0, 0}, {2048, 1024, 64, 8, 0, 0}};
+    for (const auto& c : waves) {
+        const rg::AttnRoute r = rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256);
+        if (r.fused || r.split != (c.split != 0) || r.light != (c.light != 0)) {
+            printf("split %d light %d: %ld pairs x %ld, D %d, G %d\n", r.split, r.light, (long)c.pairs, (long)c.L, c.D, c.G);
+            return 11;
+        }
+    }
     // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel
     rg_linear_set_launch(nullptr);
     for (hipError_t err : {hipErrorInvalidValue, hipErrorInvalidConfiguration, hipErrorOutOfMemory})
