@@ -44,11 +44,11 @@ constexpr int kAttnFusedThreads = 512;
 // 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
 // 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0.
 //
-// D = 64 with three and more heads: a workgroup per segment while a CU holds them all (three of 40 to 45 KB) and the segments
-// are more than half full; its four waves share the heads that one wave would run alone.  Whole calls, us, group against
+// D = 64 with three and more heads: a workgroup per segment while a CU holds them all (three of 40 to 45 KB; three and four
+// heads, whose waves run fewer chains, 2.5 per CU) and the segments are more than half full; its four waves share the heads that one wave would run alone.  Whole calls, us, group against
 // wave partials (pairs x longest length): eight heads 8 x 1024 22.7 / 27.6, 256 x 512 25.8 / 30.7, 192 x 1024 (768
 // segments) 31.3 / 34.0, 256 x 1024 (1024 segments) 39.9 / 37.6; five heads 64 x 1024 20.0 / 25.3; four heads 64 x 2048
-// 22.8 / 23.1, 256 x 512 20.6 / 21.3, 128 x 2048 (1024 segments) 29.2 / 25.9; three heads 8 x 1024 18.5 / 19.4;
+// 22.8 / 23.1, 256 x 512 20.6 / 21.3, 128 x 1536 (768 segments, all full) 26.0 / 23.9; three heads 8 x 1024 18.5 / 19.4;
 // eight heads 512 x 64 25.2 / 22.2.
 inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, int64_t cus) {
     const int GP = attn_lanes(G);
@@ -62,7 +62,7 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     else if (D == 64 && J > 2) r.fused = J <= 8 && (round || J >= 7 || (J >= 4 && pairs <= 2 * cus));
     else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
     if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
-    r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && items <= 3 * cus;
+    r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && 2 * items <= (G <= 4 ? 5 : 6) * cus;
     r.split = D > 64 && items <= (D == 256 && GP == 8 ? 5 : D == 128 && GP > 1 ? 3 : 4) * cus;
     r.light = D > 64 && GP == 8 && items > (D == 128 ? 8 : 5) * cus;
     return r;

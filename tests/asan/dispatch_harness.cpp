@@ -214,7 +214,7 @@ int main() {
     // workgroup partials: D = 64, three and more heads, at most three segments per CU
     const struct { int64_t pairs, L; int G; bool group; } groups[] = {
         {8, 1024, 8, true}, {192, 1024, 8, true}, {256, 1024, 8, false}, {64, 1024, 5, true}, {8, 1024, 3, true},
-        {64, 2048, 4, true}, {512, 64, 8, false}, {8, 1024, 2, false}, {257, 300, 6, true}};
+        {64, 2048, 4, true}, {128, 1536, 4, false}, {512, 64, 8, false}, {8, 1024, 2, false}, {257, 300, 6, true}};
     for (const auto& c : groups)
         if (rg::attn_route(c.pairs, 1, c.L, 64, c.G, 256).group != c.group) {
             printf("group %d: %ld pairs x %ld, G %d\n", !c.group, (long)c.pairs, (long)c.L, c.G);
