@@ -9,6 +9,7 @@ struct AttnRoute {
     bool fused;    // one launch: a workgroup of eight waves per (sequence, kv head)
     bool group;    // partials by a workgroup per segment (D = 64), after the maximum kernel
     bool split;    // partials by two waves per segment, half the value columns each; one wave otherwise
+    bool maxima;   // the wave partials' row maxima from a launch of their own
     bool light;    // ... by one wave with less LDS (five to eight heads), so that a CU holds sixteen
 };
 
@@ -50,6 +51,12 @@ constexpr int kAttnFusedThreads = 512;
 // segments) 31.3 / 34.0, 256 x 1024 (1024 segments) 39.9 / 37.6; five heads 64 x 1024 20.0 / 25.3; four heads 64 x 2048
 // 22.8 / 23.1, 256 x 512 20.6 / 21.3, 128 x 1536 (768 segments, all full) 26.0 / 23.9; three heads 8 x 1024 18.5 / 19.4;
 // eight heads 512 x 64 25.2 / 22.2.
+//
+// Row maxima of the wave partials: each wave reduces the segment maxima of its whole sequence, work that grows with the
+// square of the length; from the lines below on (waves x segments / 64) a launch of 2 us takes it over.  Whole calls,
+// us, in the waves / by the launch: eight heads, D = 128, 1 x 8 pairs of 262144 positions 332 / 316, of 1048576 1501 / 1216
+// (1346 with the maximum kernel of one thread per row); 1 x 1 of 262144 76 / 76; D = 64, one head, 1 x 8 of 524288 244 / 227,
+// of 262144 114 / 113; D = 128, four heads, 1 x 8 of 524288 456 / 441, of 131072 113 / 116.
 inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, int64_t cus) {
     const int GP = attn_lanes(G);
     const int64_t J = (Lmax + 255) / 256, pairs = B * Hkv, items = pairs * J;
@@ -65,6 +72,8 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && 2 * items <= (G <= 4 ? 5 : 6) * cus;
     r.split = D > 64 && items <= (D == 256 && GP == 8 ? 5 : D == 128 && GP > 1 ? 3 : 4) * cus;
     r.light = D > 64 && GP == 8 && items > (D == 128 ? 8 : 5) * cus;
+    const int64_t waves = items * (r.split ? 2 : 1);
+    r.maxima = !r.fused && !r.group && waves * ((J + 63) / 64) >= (GP == 8 ? 32768 : 393216);
     return r;
 }
 

@@ -233,6 +233,16 @@ int main() {
             return 11;
         }
     }
+    // row maxima by a launch of their own: long caches
+    const struct { int64_t pairs, L; int D, G; bool maxima; } rows[] = {
+        {1, 32768, 128, 4, false}, {8, 65536, 128, 8, false}, {8, 131072, 128, 8, true}, {8, 1 << 20, 128, 8, true},
+        {8, 262144, 128, 4, false}, {8, 524288, 64, 1, true}, {1, 1 << 20, 64, 4, false}, {1, 262144, 256, 8, true},
+        {16, 4096, 128, 4, false}, {2048, 1024, 64, 8, false}};
+    for (const auto& c : rows)
+        if (rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256).maxima != c.maxima) {
+            printf("maxima %d: %ld pairs x %ld, D %d, G %d\n", !c.maxima, (long)c.pairs, (long)c.L, c.D, c.G);
+            return 12;
+        }
     // a launch that the runtime refuses, with whatever code, is reported and not tried on another kernel
     rg_linear_set_launch(nullptr);
     for (hipError_t err : {hipErrorInvalidValue, hipErrorInvalidConfiguration, hipErrorOutOfMemory})

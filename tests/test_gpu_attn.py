@@ -240,3 +240,33 @@ def test_fused_and_wave_partials(B, H, Hkv, L, D):
     nan = np.isnan(want)
     assert np.array_equal(nan, np.isnan(got))
     gu.assert_bitwise(np.where(nan, 0.0, got), np.where(nan, 0.0, want), f"attn ({B},{H},{Hkv},{L},{D})")
+
+
+# Long caches take their row maxima from the maximum kernel (one wave per row); the sequences in them may be short or empty.
+@pytest.mark.parametrize("H,Hkv,L,D,lens", [
+    (8, 1, 384001, 64, [384001]), (5, 1, 230400, 64, [230400, 0, 70000]), (1, 1, 1300000, 64, [5000]),
+    (12, 2, 150000, 128, [150000, 129, 3, 40001]), (8, 1, 220100, 256, [1000, 220100, 20])])
+def test_row_maxima_of_long_caches(H, Hkv, L, D, lens):
+    import torch
+    import oracle
+    import paper_2609_25624_amd as rg
+    B = len(lens)
+    rng = np.random.default_rng(L + H)
+    q = rng.standard_normal((B, H, D), dtype=np.float32)
+    kc, vc = (np.zeros((B, Hkv, L, D), dtype=np.uint16) for _ in range(2))
+    for b, n in enumerate(lens):
+        for c in (kc, vc):
+            c[b, :, :n] = rng.standard_normal((Hkv, n, D), dtype=np.float32).view(np.uint32) >> 16
+    lens = np.array(lens, dtype=np.int32)
+    scale = 1.0 / np.sqrt(D)
+    gu.log(f"attn long B={B} H={H} Hkv={Hkv} L={L} D={D}")
+    want = oracle.attn_decode(q, kc, vc, lens, scale)
+    dev = gu.dev()
+    out = torch.full((B, H, D), 7.0, dtype=torch.float32, device=dev)
+    rg.rg_attn_decode(torch.from_numpy(q).to(dev), torch.from_numpy(kc.view(np.int16)).to(dev),
+                      torch.from_numpy(vc.view(np.int16)).to(dev), torch.from_numpy(lens).to(dev), out, scale)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    nan = np.isnan(want)
+    assert np.array_equal(nan, np.isnan(got))
+    gu.assert_bitwise(np.where(nan, 0.0, got), np.where(nan, 0.0, want), f"attn long ({B},{H},{Hkv},{L},{D})")
