@@ -30,17 +30,19 @@ constexpr int kAttnFusedThreads = 512;
 //   one head, at most 128 positions             two rounds too: D = 128, 512 x 128 16.0 / 16.4
 //   three or four heads, one segment            D = 64: 64 x 256 17.4 / 17.8 (the group kernel), 128 x 128 12.0 / 15.7;
 //   or two on more than half the CUs            D = 128: 64 x 256 21.1 / 21.9, 64 x 512 24.1 / 22.6, 256 x 512 24.7 / 27.1
-//   five to eight heads, D = 64                 64 x 128 16.6 / 21.1, 64 x 256 24 / 21 (at most 128 positions)
+//   five to eight heads, D = 64                 64 x 128 16.6 / 21.1, 64 x 256 24 / 21; eight 64 x 131 18.5 / 21.6
+//                                               (at most 128 positions, eight heads 176)
 // Its launch must hold its threads (a launch has at most 2^32 - 1).
 //
 // Partials: one wave per segment, or two with half its value columns each where there are few segments (64 of D = 64 fill a
-// wave as they are): at most four per CU, three at D = 128 with two and more heads (32 x 8 pairs of 1000 positions, 1024
+// wave as they are): at most four per CU, three (with five to eight heads 3.5) at D = 128 with two and more heads (32 x 8 pairs of 1000 positions, 1024
 // segments: four heads 38.1 split, 35.2 whole; one head 27.8 / 29.6; D = 256, eight heads 79.9 / 89.4).  With five to
 // eight heads many segments want waves more than bytes in flight per wave (8 KB of rows and the e of 64 positions in
-// place of 12 KB and 128): from eight segments per CU at D = 128, from five at D = 256, where both halves of a split
+// place of 12 KB and 128): from eight segments per CU at D = 128, from five (seven and eight heads six) at D = 256, where both halves of a split
 // segment compute all its e.  Whole calls, us, heavy / light: D = 128, eight heads 256 x 8 pairs of 384 positions 138 / 126, 64 x 8
 // of 2048 155 / 144; 64 x 8 of 384 (1024 segments) 55 / 59; D = 256, eight heads (split / light) 256 x 8 of 384 250 / 218, 64 x 8 of
-// 1024 150 / 146, of 384 (1024 segments) 80 / 88; seven heads 28 x 8 of 1156 (1120 segments) 76 / 84.
+// 1024 150 / 146, of 384 (1024 segments) 80 / 88; 65 x 4 of 1188 (1300 segments) 93 / 100;
+// seven heads 28 x 8 of 1156 (1120 segments) 76 / 84.
 // Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
 // 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
 // 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0.
@@ -63,15 +65,16 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     AttnRoute r = {};
     const bool round = pairs <= cus;
     if (D * GP > 512) r.fused = false;
-    else if (GP == 8) r.fused = round && Lmax <= 128;
+    else if (GP == 8) r.fused = round && Lmax <= (G == 8 ? 176 : 128);
     else if (GP == 4) r.fused = round && (J == 1 || (J == 2 && 2 * pairs > cus));
     else if (GP == 2) r.fused = round && J <= (D == 256 ? 1 : 2);
     else if (D == 64 && J > 2) r.fused = J <= 8 && (round || J >= 7 || (J >= 4 && pairs <= 2 * cus));
     else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
     if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
     r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && 2 * items <= (G <= 4 ? 5 : 6) * cus;
-    r.split = D > 64 && items <= (D == 256 && GP == 8 ? 5 : D == 128 && GP > 1 ? 3 : 4) * cus;
-    r.light = D > 64 && GP == 8 && items > (D == 128 ? 8 : 5) * cus;
+    const int64_t heavy = G >= 7 ? 12 : 10;              // D = 256, five to eight heads: half segments per CU
+    r.split = D > 64 && 2 * items <= (D == 256 ? (GP == 8 ? heavy : 8) : GP == 8 ? 7 : GP == 1 ? 8 : 6) * cus;
+    r.light = D > 64 && GP == 8 && 2 * items > (D == 256 ? heavy : 16) * cus;
     const int64_t waves = items * (r.split ? 2 : 1);
     r.maxima = !r.fused && !r.group && waves * ((J + 63) / 64) >= (GP == 8 ? 32768 : 393216);
     return r;

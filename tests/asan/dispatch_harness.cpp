@@ -204,7 +204,7 @@ int main() {
         {8192, 256, 64, 1, false}, {256, 2048, 64, 1, true}, {2048, 1024, 64, 1, false}, {2048, 2048, 64, 1, true},
         {512, 1100, 64, 1, true}, {256, 512, 128, 2, true}, {512, 128, 128, 2, false}, {512, 128, 128, 1, true},
         {512, 128, 256, 1, false}, {64, 200, 256, 2, true}, {64, 400, 256, 2, false}, {8, 256, 64, 4, true},
-        {8, 300, 64, 4, false}, {200, 300, 64, 4, true}, {257, 64, 128, 4, false}, {64, 128, 64, 8, true},
+        {8, 300, 64, 4, false}, {200, 300, 64, 4, true}, {257, 64, 128, 4, false}, {64, 128, 64, 8, true}, {64, 150, 64, 8, true}, {64, 200, 64, 8, false},
         {64, 129, 64, 5, false}, {4, 100, 128, 8, false}};
     for (const auto& c : short_caches)
         if (rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256).fused != c.fused) {
@@ -224,7 +224,8 @@ int main() {
     const struct { int64_t pairs, L; int D, G, split, light; } waves[] = {
         {16, 1024, 128, 4, 1, 0}, {192, 1024, 128, 4, 1, 0}, {256, 1024, 128, 4, 0, 0}, {256, 1024, 128, 1, 1, 0},
         {257, 1024, 128, 1, 0, 0}, {256, 1024, 128, 8, 0, 0}, {512, 1024, 128, 8, 0, 0}, {513, 1024, 128, 5, 0, 1},
-        {2048, 1024, 128, 4, 0, 0}, {320, 1024, 256, 8, 1, 0}, {321, 1024, 256, 5, 0, 1}, {257, 1024, 256, 4, 0, 0},
+        {2048, 1024, 128, 4, 0, 0}, {320, 1024, 256, 5, 1, 0}, {321, 1024, 256, 5, 0, 1}, {384, 1024, 256, 8, 1, 0}, {385, 1024, 256, 8, 0, 1},
+        {224, 1024, 128, 8, 1, 0}, {225, 1024, 128, 8, 0, 0}, {257, 1024, 256, 4, 0, 0},
         {256, 1024, 256, 1, 1, 0}, {16, 1024, 64, 8, 0, 0}, {2048, 1024, 64, 8, 0, 0}};
     for (const auto& c : waves) {
         const rg::AttnRoute r = rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256);
