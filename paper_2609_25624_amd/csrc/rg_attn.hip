@@ -370,10 +370,31 @@ __global__ void __launch_bounds__(128) attn_scores2_kernel(AttnArgs a) {
     }
 }
 
-// 2. m[b][h] = the largest segment maximum (exact).  One wave per (b, h), its lanes over the segments: with one thread
-// a row of 512 segments is a chain of 64 batches of loads (D = 64, eight heads, one sequence of 131072 positions:
-// the call 42.4 -> 39 us).
+// 2. m[b][h] = the largest segment maximum (exact).  One thread per (b, h) for up to
+// kMaxThreadSegs segments.
 __global__ void __launch_bounds__(256) attn_max_kernel(AttnArgs a) {
+    const int64_t bh = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (bh >= a.B * a.H) return;
+    const int L = clamp_len(a.lens, bh / a.H, a.Lmax);
+    const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
+    const float* sm = a.segmax + bh * a.J;
+    float m = -__builtin_inff();
+    int jj = 0;
+    for (; jj + 8 <= Jb; jj += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = sm[jj + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = __builtin_fmaxf(m, v[i]);
+    }
+    for (; jj < Jb; ++jj) m = __builtin_fmaxf(m, sm[jj]);
+    a.mmax[bh] = m;
+}
+
+// The same with one wave per (b, h), its lanes over the segments: with one thread a row of 512 segments is a chain of 64
+// batches of loads (D = 64, eight heads, one sequence of 131072 positions: the call 42.0 -> 35.4 us; a short row's wave
+// takes 0.7 us more than its thread).
+__global__ void __launch_bounds__(256) attn_max_rows_kernel(AttnArgs a) {
     const int64_t bh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (bh >= a.B * a.H) return;
     const int L = clamp_len(a.lens, bh / a.H, a.Lmax);
@@ -384,6 +405,17 @@ __global__ void __launch_bounds__(256) attn_max_kernel(AttnArgs a) {
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, sh, 64));
     if ((threadIdx.x & 63) == 0) a.mmax[bh] = m;
+}
+
+constexpr int64_t kMaxThreadSegs = 16;
+
+hipError_t launch_max(const AttnArgs& a, hipStream_t stream) {
+    const int64_t rows = a.B * a.H;
+    if (a.J <= kMaxThreadSegs)
+        hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL(attn_max_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 // 3. exponentials and the segment partials S_j and n_j[d].  Work item = segment;
@@ -840,11 +872,12 @@ __device__ __forceinline__ void fold_out(const AttnArgs& a, int64_t bh, int d, i
 }
 
 // 3'. the same partials with one wave per (segment, value columns part); each takes the group's row maxima from the
-// segment maxima itself (exact, so no launch of the maximum kernel), or from that kernel (`maxima`).  One unit per workgroup (more only beyond the
+// segment maxima itself (exact, so no launch of the maximum kernel), or from that kernel (MAXIMA: a
+// build of its own; as an argument it cost the other one 0.5 us of 23).  One unit per workgroup (more only beyond the
 // largest grid): the waves of a CU are then at different points of their units, and a short sequence's
 // waves leave at once.
-template <int GH, int D, int CS, int RINGB, int EC>
-__global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a, int maxima) {
+template <int GH, int D, int CS, int RINGB, int EC, bool MAXIMA>
+__global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a) {
     constexpr int GP = attn_lanes(GH);
     __shared__ __attribute__((aligned(16))) uint8_t ring[RINGB];
     __shared__ __attribute__((aligned(16))) float es[EC * GP];
@@ -858,22 +891,22 @@ __global__ void __launch_bounds__(64) attn_values_kernel(AttnArgs a, int maxima)
         const int j = __builtin_amdgcn_readfirstlane(w.j), L = __builtin_amdgcn_readfirstlane(w.L);
         const int Jb = (L + kAttnSeg - 1) / kAttnSeg;
         value_pass<GH, ValueSteps<GP, D, CS, RINGB, EC>, GP, D, CS>(a, b, g, G, L, Jb, j * CS + (int)(it % CS), Jb * CS, ring, es, [&](float (&m)[GH]) {
-            const int64_t h0 = (int64_t)b * a.H + (int64_t)g * G;
-            if (maxima) {
+            if constexpr (MAXIMA) {
 #pragma unroll
-                for (int h = 0; h < GH; ++h) m[h] = a.mmax[h0 + (h < G ? h : G - 1)];
-                return;
+                for (int h = 0; h < GH; ++h) m[h] = a.mmax[(int64_t)b * a.H + (int64_t)g * G + (h < G ? h : G - 1)];
+            } else {
+                const float* sm = a.segmax + ((int64_t)b * a.H + (int64_t)g * G) * a.J;
+#pragma unroll
+                for (int h = 0; h < GH; ++h) m[h] = -__builtin_inff();
+                for (int j0 = lane; j0 < Jb; j0 += 64)
+#pragma unroll
+                    for (int h = 0; h < GH; ++h)
+                        m[h] = __builtin_fmaxf(m[h], sm[(int64_t)(h < G ? h : G - 1) * a.J + j0]);
+#pragma unroll
+                for (int sh = 32; sh > 0; sh >>= 1)
+#pragma unroll
+                    for (int h = 0; h < GH; ++h) m[h] = __builtin_fmaxf(m[h], __shfl_xor(m[h], sh, 64));
             }
-            const float* sm = a.segmax + h0 * a.J;
-#pragma unroll
-            for (int h = 0; h < GH; ++h) m[h] = -__builtin_inff();
-            for (int j0 = lane; j0 < Jb; j0 += 64)
-#pragma unroll
-                for (int h = 0; h < GH; ++h) m[h] = __builtin_fmaxf(m[h], sm[(int64_t)(h < G ? h : G - 1) * a.J + j0]);
-#pragma unroll
-            for (int sh = 32; sh > 0; sh >>= 1)
-#pragma unroll
-                for (int h = 0; h < GH; ++h) m[h] = __builtin_fmaxf(m[h], __shfl_xor(m[h], sh, 64));
         });
         attn_lds_wait();                              // before the next unit's rows arrive
     }
@@ -940,8 +973,7 @@ hipError_t launch_pair(K1 k1, int64_t lds1, K3 k3, int64_t lds3, const AttnArgs&
     hipLaunchKernelGGL(k1, dim3((unsigned)g1), dim3(256), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 3) / 4)), dim3(256), 0, stream, a);
-    e = hipGetLastError();
+    e = launch_max(a, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k3, dim3((unsigned)g3), dim3(256), 0, stream, a);
     e = hipGetLastError();
@@ -987,28 +1019,35 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (route.group) {
         constexpr int RS = 16384 / 64;
-        hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 3) / 4)), dim3(256), 0, stream, a);
-        e = hipGetLastError();
+        e = launch_max(a, stream);
         if (e != hipSuccess) return e;
         if constexpr (D == 64 && G >= 3)
             hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
         if (route.maxima) {
-            hipLaunchKernelGGL(attn_max_kernel, dim3((unsigned)((a.B * a.H + 3) / 4)), dim3(256), 0, stream, a);
-            e = hipGetLastError();
+            e = launch_max(a, stream);
             if (e != hipSuccess) return e;
         }
         const int64_t units = items * (route.split ? 2 : 1);
         const dim3 grid((unsigned)(units < (1 << 24) ? units : (1 << 24)));
         if constexpr (D > 64) {
-            if (route.split) hipLaunchKernelGGL((attn_values_kernel<GH, D, 2, RING2, EC>), grid, dim3(64), 0, stream, a, (int)route.maxima);
+            if (route.split)
+                hipLaunchKernelGGL((attn_values_kernel<GH, D, 2, RING2, EC, false>), grid, dim3(64), 0, stream, a);
         }
+        auto whole = [&](auto ring, auto ec) {
+            if (route.maxima)
+                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, decltype(ring)::value, decltype(ec)::value, true>), grid,
+                                   dim3(64), 0, stream, a);
+            else
+                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, decltype(ring)::value, decltype(ec)::value, false>), grid,
+                                   dim3(64), 0, stream, a);
+        };
         if constexpr (D > 64 && GP == 8) {
-            if (route.light) hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, 8192, 64>), grid, dim3(64), 0, stream, a, (int)route.maxima);
+            if (route.light) whole(std::integral_constant<int, 8192>{}, std::integral_constant<int, 64>{});
         }
         if (!route.split && !route.light) {
             if constexpr (!(D == 256 && GP == 8))
-                hipLaunchKernelGGL((attn_values_kernel<GH, D, 1, RING1, EC>), grid, dim3(64), 0, stream, a, (int)route.maxima);
+                whole(std::integral_constant<int, RING1>{}, std::integral_constant<int, EC>{});
         }
     }
     e = hipGetLastError();

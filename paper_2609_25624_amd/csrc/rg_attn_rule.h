@@ -9,7 +9,7 @@ struct AttnRoute {
     bool fused;    // one launch: a workgroup of eight waves per (sequence, kv head)
     bool group;    // partials by a workgroup per segment (D = 64), after the maximum kernel
     bool split;    // partials by two waves per segment, half the value columns each; one wave otherwise
-    bool maxima;   // the wave partials' row maxima from a launch of their own
+    bool maxima;   // the whole-row wave partials' row maxima from a launch of their own
     bool light;    // ... by one wave with less LDS (five to eight heads), so that a CU holds sixteen
 };
 
@@ -35,30 +35,31 @@ constexpr int kAttnFusedThreads = 512;
 // Its launch must hold its threads (a launch has at most 2^32 - 1).
 //
 // Partials: one wave per segment, or two with half its value columns each where there are few segments (64 of D = 64 fill a
-// wave as they are): at most four per CU, three (with five to eight heads 3.5) at D = 128 with two and more heads (32 x 8 pairs of 1000 positions, 1024
-// segments: four heads 38.1 split, 35.2 whole; one head 27.8 / 29.6; D = 256, eight heads 79.9 / 89.4).  With five to
+// wave as they are): at most four per CU (1024 segments, us, split / whole: D = 128, four heads 1 x 8 pairs of 32768
+// positions 38.7 / 40.1 with the cache's rows in the memory-side cache, 40.0 / 39.8 without, 32 x 8 of 1000 38 / 35 and
+// 40 / 38; one head 28 / 30; five heads 44.5 / 39.9, eight 55.9 / 54.4, hence 3.5 from five heads on).  With five to
 // eight heads many segments want waves more than bytes in flight per wave (8 KB of rows and the e of 64 positions in
-// place of 12 KB and 128): from eight segments per CU at D = 128, from five (seven and eight heads six) at D = 256, where both halves of a split
-// segment compute all its e.  Whole calls, us, heavy / light: D = 128, eight heads 256 x 8 pairs of 384 positions 138 / 126, 64 x 8
-// of 2048 155 / 144; 64 x 8 of 384 (1024 segments) 55 / 59; D = 256, eight heads (split / light) 256 x 8 of 384 250 / 218, 64 x 8 of
-// 1024 150 / 146, of 384 (1024 segments) 80 / 88; 65 x 4 of 1188 (1300 segments) 93 / 100;
-// seven heads 28 x 8 of 1156 (1120 segments) 76 / 84.
+// place of 12 KB and 128): from eight segments per CU at D = 128, from five (seven and eight heads six) at D = 256, where
+// both halves of a split segment compute all its e.  Whole calls, us, heavy / light: D = 128, eight heads, 256 x 8 pairs of
+// 384 positions 138 / 126, 64 x 8 of 2048 155 / 144, of 384 (1024 segments) 55 / 59; D = 256, eight heads (split / light),
+// 256 x 8 of 384 250 / 218, 64 x 8 of 1024 150 / 146, of 384 (1024 segments) 80 / 88, 65 x 4 of 1188 (1300 segments)
+// 93 / 100; seven heads 28 x 8 of 1156 (1120 segments) 76 / 84.
 // Against the persistent wave kernel they replaced, with the maximum kernel where it was launched, us: 64 x 32 heads,
 // 2048 positions 51.4 -> 46.3; 32 x 64 heads 72.9 -> 63.7; 16 x 32 heads, 4096 positions 27.2 -> 27.0; 4 x 32 heads,
 // 2000 positions 14.0 -> 12.3; D = 64, 60 x 32 heads, 3000 positions 74.3 -> 39.0.
 //
-// D = 64 with three and more heads: a workgroup per segment while a CU holds them all (three of 40 to 45 KB; three and four
-// heads, whose waves run fewer chains, 2.5 per CU) and the segments are more than half full; its four waves share the heads that one wave would run alone.  Whole calls, us, group against
-// wave partials (pairs x longest length): eight heads 8 x 1024 22.7 / 27.6, 256 x 512 25.8 / 30.7, 192 x 1024 (768
-// segments) 31.3 / 34.0, 256 x 1024 (1024 segments) 39.9 / 37.6; five heads 64 x 1024 20.0 / 25.3; four heads 64 x 2048
-// 22.8 / 23.1, 256 x 512 20.6 / 21.3, 128 x 1536 (768 segments, all full) 26.0 / 23.9; three heads 8 x 1024 18.5 / 19.4;
-// eight heads 512 x 64 25.2 / 22.2.
+// D = 64 with three and more heads: a workgroup per segment while a CU holds them all (three of 40 to 45 KB; with three and
+// four heads, whose waves run fewer chains, two per CU) and the segments are more than half full; its four waves share the
+// heads that one wave would run alone.  Whole calls, us, group against wave partials (pairs x longest length): eight heads
+// 8 x 1024 22.7 / 27.6, 256 x 512 25.8 / 30.7, 192 x 1024 (768 segments) 31.3 / 34.0, 256 x 1024 (1024 segments) 39.9 /
+// 37.6; five heads 64 x 1024 20.0 / 25.3; four heads 64 x 2048 22.8 / 23.1, 256 x 512 20.6 / 21.3, 144 x 840 (all full)
+// 26.1 / 24.7; three heads 8 x 1024 18.5 / 19.4; eight heads 512 x 64 25.2 / 22.2.
 //
 // Row maxima of the wave partials: each wave reduces the segment maxima of its whole sequence, work that grows with the
-// square of the length; from the lines below on (waves x segments / 64) a launch of 2 us takes it over.  Whole calls,
-// us, in the waves / by the launch: eight heads, D = 128, 1 x 8 pairs of 262144 positions 332 / 316, of 1048576 1501 / 1216
-// (1346 with the maximum kernel of one thread per row); 1 x 1 of 262144 76 / 76; D = 64, one head, 1 x 8 of 524288 244 / 227,
-// of 262144 114 / 113; D = 128, four heads, 1 x 8 of 524288 456 / 441, of 131072 113 / 116.
+// square of the length; from the line below on (segments x segments / 64; split segments never get there) a launch of
+// 2 us takes it over.  Whole calls, us, in the waves / by the launch: eight heads, D = 128, 1 x 8 pairs of 262144 positions
+// 332 / 316, of 1048576 1501 / 1216 (1346 with the maximum kernel of one thread per row); D = 64, one head, 1 x 8 of 524288
+// 244 / 227, of 262144 114 / 113; D = 128, four heads, 1 x 8 of 524288 456 / 441, of 131072 113 / 116.
 inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, int64_t cus) {
     const int GP = attn_lanes(G);
     const int64_t J = (Lmax + 255) / 256, pairs = B * Hkv, items = pairs * J;
@@ -71,12 +72,11 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     else if (D == 64 && J > 2) r.fused = J <= 8 && (round || J >= 7 || (J >= 4 && pairs <= 2 * cus));
     else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
     if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
-    r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && 2 * items <= (G <= 4 ? 5 : 6) * cus;
+    r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && items <= (G <= 4 ? 2 : 3) * cus;
     const int64_t heavy = G >= 7 ? 12 : 10;              // D = 256, five to eight heads: half segments per CU
-    r.split = D > 64 && 2 * items <= (D == 256 ? (GP == 8 ? heavy : 8) : GP == 8 ? 7 : GP == 1 ? 8 : 6) * cus;
+    r.split = D > 64 && 2 * items <= (GP < 8 ? 8 : D == 256 ? heavy : 7) * cus;
     r.light = D > 64 && GP == 8 && 2 * items > (D == 256 ? heavy : 16) * cus;
-    const int64_t waves = items * (r.split ? 2 : 1);
-    r.maxima = !r.fused && !r.group && waves * ((J + 63) / 64) >= (GP == 8 ? 32768 : 393216);
+    r.maxima = !r.fused && !r.group && !r.split && items * ((J + 63) / 64) >= (GP == 8 ? 32768 : 393216);
     return r;
 }
 

@@ -214,7 +214,7 @@ int main() {
     // workgroup partials: D = 64, three and more heads, at most three segments per CU
     const struct { int64_t pairs, L; int G; bool group; } groups[] = {
         {8, 1024, 8, true}, {192, 1024, 8, true}, {256, 1024, 8, false}, {64, 1024, 5, true}, {8, 1024, 3, true},
-        {64, 2048, 4, true}, {128, 1536, 4, false}, {512, 64, 8, false}, {8, 1024, 2, false}, {257, 300, 6, true}};
+        {64, 2048, 4, true}, {128, 1024, 4, true}, {129, 1024, 4, false}, {512, 64, 8, false}, {8, 1024, 2, false}, {257, 300, 6, true}};
     for (const auto& c : groups)
         if (rg::attn_route(c.pairs, 1, c.L, 64, c.G, 256).group != c.group) {
             printf("group %d: %ld pairs x %ld, G %d\n", !c.group, (long)c.pairs, (long)c.L, c.G);
@@ -222,7 +222,7 @@ int main() {
         }
     // value waves: split, whole or light
     const struct { int64_t pairs, L; int D, G, split, light; } waves[] = {
-        {16, 1024, 128, 4, 1, 0}, {192, 1024, 128, 4, 1, 0}, {256, 1024, 128, 4, 0, 0}, {256, 1024, 128, 1, 1, 0},
+        {16, 1024, 128, 4, 1, 0}, {256, 1024, 128, 4, 1, 0}, {257, 1024, 128, 4, 0, 0}, {256, 1024, 128, 1, 1, 0},
         {257, 1024, 128, 1, 0, 0}, {256, 1024, 128, 8, 0, 0}, {512, 1024, 128, 8, 0, 0}, {513, 1024, 128, 5, 0, 1},
         {2048, 1024, 128, 4, 0, 0}, {320, 1024, 256, 5, 1, 0}, {321, 1024, 256, 5, 0, 1}, {384, 1024, 256, 8, 1, 0}, {385, 1024, 256, 8, 0, 1},
         {224, 1024, 128, 8, 1, 0}, {225, 1024, 128, 8, 0, 0}, {257, 1024, 256, 4, 0, 0},
@@ -237,7 +237,7 @@ int main() {
     // row maxima by a launch of their own: long caches
     const struct { int64_t pairs, L; int D, G; bool maxima; } rows[] = {
         {1, 32768, 128, 4, false}, {8, 65536, 128, 8, false}, {8, 131072, 128, 8, true}, {8, 1 << 20, 128, 8, true},
-        {8, 262144, 128, 4, false}, {8, 524288, 64, 1, true}, {1, 1 << 20, 64, 4, false}, {1, 262144, 256, 8, true},
+        {8, 262144, 128, 4, false}, {8, 524288, 64, 1, true}, {1, 1 << 20, 64, 4, false}, {1, 262144, 256, 8, false}, {1, 524288, 256, 8, true},
         {16, 4096, 128, 4, false}, {2048, 1024, 64, 8, false}};
     for (const auto& c : rows)
         if (rg::attn_route(c.pairs, 1, c.L, c.D, c.G, 256).maxima != c.maxima) {
