@@ -1,7 +1,8 @@
 // Fixed-order decode attention kernels for gfx950 (MI355X): the order
 // RG-ATTN-1 and its exponential EXP1, both defined in include/rg_attn.h.
 //
-// One launch for short caches, three (four for other head dims) otherwise, each
+// One launch for short caches, three otherwise, or four where the maximum is a launch of its own
+// (attn_route in rg_attn_rule.h; head dims other than 64, 128 and 256 always four), each
 // deterministic by construction (no order that depends on the grid):
 //   1. scores:   work item (b, g, j) = segment j (positions [256j, 256j + 256))
 //                of kv head g of sequence b; its keys are staged in LDS and
@@ -18,10 +19,10 @@
 //   4. fold:     workgroup (b, h) folds the S_j and n_j[d] in ascending j and
 //                divides.
 // The fused kernel runs 1 to 4 in one workgroup per (b, g).
-// Kernels 1, and 3 for other head dims, are persistent: a workgroup walks work items it,
-// it + grid, ... in steps of one 32 KB tile, fetching the next step into registers while it
-// computes the current one from LDS.  Kernel 3 for head dims 64, 128 and 256 and the fused kernel
-// stream rows wave by wave through LDS rings by DMA.
+// Kernel 1, and kernel 3 for other head dims, are persistent: a workgroup walks work items it,
+// it + grid, ... (kernel 1 in steps of one 32 KB tile), fetching the next step into registers while it
+// computes the current one from LDS.  Kernel 3 for head dims 64, 128 and 256 (but where a workgroup per
+// segment leads at 64) and the fused kernel stream rows wave by wave through LDS rings by DMA.
 // Arithmetic: binary32 fmaf / add / multiply / correctly rounded divide,
 // denormals kept, no contraction (the build uses -ffp-contract=off).
 
@@ -418,20 +419,18 @@ hipError_t launch_max(const AttnArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// 3. exponentials and the segment partials S_j and n_j[d].  Work item = segment;
-// its NS steps take positions [l0 + s RS, l0 + s RS + RS) in turn (RS = 16384 / D
-// rows for the fixed head dims, else all 256 in one step), so every chain below
-// continues across the steps in ascending l.  e for the segment is computed at
-// its first step into LDS ([head][position], -0 past the sequence).  Unit u =
+// 3. exponentials and the segment partials S_j and n_j[d] (head dim 64, and the head dims without wave
+// passes).  Work item = segment, all its 256 value rows staged at once.  e for the segment is computed
+// into LDS ([head][position], -0 past the sequence).  Unit u =
 // (head, pair of adjacent d): two fmaf chains over the positions; threads tid < G
 // also run the segment sum of head tid (an addition chain).  Chains run over all
 // 256 positions of the segment: past the sequence e = -0 and the values are +0,
 // so a padded step is fmaf(-0, +0, n) = -0 + n = n and s + (-0) = s for every n and
 // s, including a numerator that is -0 (a negative product e * v that underflows).
 // (A +0 pad would turn such a -0 numerator into +0.)
-template <int G, int DM, int RS, bool EXACT>
+template <int G, int DM, bool EXACT>
 __global__ void __launch_bounds__(256) attn_partials_kernel(AttnArgs a) {
-    constexpr int NS = kAttnSeg / RS;                 // steps per item
+    constexpr int RS = kAttnSeg;                      // value rows staged
     constexpr int VPR = EXACT ? DM / 8 : 0;
     constexpr int NV = RS * DM / 8 / 256;             // vectors per thread
     constexpr int UPT = (G * DM / 2 + 255) / 256;     // units per thread
@@ -442,63 +441,45 @@ __global__ void __launch_bounds__(256) attn_partials_kernel(AttnArgs a) {
     const int items = (int)(a.B * a.Hkv * a.J);
     Tile<NV, VPR> tile;
     float tr[G], mr[G];
-    auto fetch = [&](const Item& w, int s) {
-        const int r0 = s * RS;
-        const int rows = w.rows - r0 < RS ? w.rows - r0 : RS;
-        tile.fetch(a.v + (((int64_t)w.b * a.Hkv + w.g) * a.Lmax + w.l0 + r0) * D, D, rows, vpr, a.vmagic);
-        if (s == 0) {
-            const int64_t h0 = (int64_t)w.g * G;
+    auto fetch = [&](const Item& w) {
+        tile.fetch(a.v + (((int64_t)w.b * a.Hkv + w.g) * a.Lmax + w.l0) * D, D, w.rows < RS ? w.rows : RS, vpr, a.vmagic);
+        const int64_t h0 = (int64_t)w.g * G;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                tr[i] = tid < w.rows ? a.t[((int64_t)w.b * a.H + h0 + i) * a.Lmax + w.l0 + tid] : 0.0f;
-                mr[i] = a.mmax[(int64_t)w.b * a.H + h0 + i];
-            }
+        for (int i = 0; i < G; ++i) {
+            tr[i] = tid < w.rows ? a.t[((int64_t)w.b * a.H + h0 + i) * a.Lmax + w.l0 + tid] : 0.0f;
+            mr[i] = a.mmax[(int64_t)w.b * a.H + h0 + i];
         }
     };
     int it = next_item(a, (int)blockIdx.x, items);
     Item w;
-    int st = 0;
     if (it < items) {
         w = item_of(a, it);
-        fetch(w, 0);
+        fetch(w);
     }
     const int npd = D / 2;
     const int nunits = G * npd;
-    float n0[UPT], n1[UPT], ssum = 0.0f;
     while (it < items) {
         __syncthreads();
         tile.store(vs, RS, vpr, a.vmagic);
-        if (st == 0) {
 #pragma unroll
-            for (int i = 0; i < G; ++i) es[i * kAttnSeg + tid] = tid < w.rows ? exp1(tr[i] - mr[i]) : -0.0f;
-        }
+        for (int i = 0; i < G; ++i) es[i * kAttnSeg + tid] = tid < w.rows ? exp1(tr[i] - mr[i]) : -0.0f;
         __syncthreads();
         const Item cur = w;
-        const int ss = st;
-        if (st + 1 < NS) {
-            ++st;
-        } else {
-            st = 0;
-            it = next_item(a, it + (int)gridDim.x, items);
-            if (it < items) w = item_of(a, it);
+        it = next_item(a, it + (int)gridDim.x, items);
+        if (it < items) {
+            w = item_of(a, it);
+            fetch(w);                                 // in flight during this item's chains
         }
-        if (it < items) fetch(w, st);                 // in flight during this step's chains
-        if (ss == 0) {
-#pragma unroll
-            for (int k = 0; k < UPT; ++k) n0[k] = n1[k] = 0.0f;
-            ssum = 0.0f;
-        }
-        const int lb = ss * RS;                        // first position of this step in the segment
 #pragma unroll
         for (int k = 0; k < UPT; ++k) {
             const int u = tid + 256 * k;
             if (u < nunits) {
                 const int hh = u / npd, d = 2 * (u - hh * npd);
                 const bool sums = k == 0 && tid < G;
-                const float* ep = es + hh * kAttnSeg + lb;
-                const float* sp = es + (tid < G ? tid : 0) * kAttnSeg + lb;
+                const float* ep = es + hh * kAttnSeg;
+                const float* sp = es + (tid < G ? tid : 0) * kAttnSeg;
                 const uint16_t* vp = vs + d;
-                float x0 = n0[k], x1 = n1[k], sm = ssum;
+                float x0 = 0.0f, x1 = 0.0f, sm = 0.0f;
 #pragma unroll 2
                 for (int l = 0; l < RS; l += 8) {
                     const float4 e0 = *reinterpret_cast<const float4*>(ep + l);
@@ -519,15 +500,10 @@ __global__ void __launch_bounds__(256) attn_partials_kernel(AttnArgs a) {
                         sm = sm + s1.x; sm = sm + s1.y; sm = sm + s1.z; sm = sm + s1.w;
                     }
                 }
-                n0[k] = x0;
-                n1[k] = x1;
-                if (sums) ssum = sm;
-                if (ss == NS - 1) {
-                    float* np = a.npart + (((int64_t)cur.b * a.H + cur.g * G + hh) * a.J + cur.j) * D + d;
-                    np[0] = x0;
-                    np[1] = x1;
-                    if (sums) a.spart[((int64_t)cur.b * a.H + cur.g * G + tid) * a.J + cur.j] = sm;
-                }
+                float* np = a.npart + (((int64_t)cur.b * a.H + cur.g * G + hh) * a.J + cur.j) * D + d;
+                np[0] = x0;
+                np[1] = x1;
+                if (sums) a.spart[((int64_t)cur.b * a.H + cur.g * G + tid) * a.J + cur.j] = sm;
             }
         }
     }
@@ -1018,11 +994,10 @@ hipError_t launch_fixed(const AttnArgs& a, int cus, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (route.group) {
-        constexpr int RS = 16384 / 64;
         e = launch_max(a, stream);
         if (e != hipSuccess) return e;
         if constexpr (D == 64 && G >= 3)
-            hipLaunchKernelGGL((attn_partials_kernel<G, D, RS, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
+            hipLaunchKernelGGL((attn_partials_kernel<G, D, true>), dim3((unsigned)items), dim3(256), 0, stream, a);
     } else {
         if (route.maxima) {
             e = launch_max(a, stream);
@@ -1060,7 +1035,7 @@ template <int G, int DM>
 hipError_t launch_any(const AttnArgs& a, int cus, hipStream_t stream) {
     const int64_t lds1 = (int64_t)kAttnSeg * (DM + 8) * 2 + 16 * G;
     const int64_t lds3 = (int64_t)G * kAttnSeg * 4 + (int64_t)kAttnSeg * (DM + 8) * 2;
-    return launch_pair(attn_scores_kernel<G, DM, 1, false>, lds1, attn_partials_kernel<G, DM, kAttnSeg, false>, lds3,
+    return launch_pair(attn_scores_kernel<G, DM, 1, false>, lds1, attn_partials_kernel<G, DM, false>, lds3,
                        a, cus, stream);
 }
 

@@ -168,10 +168,9 @@ def test_argument_errors():
         rg.rg_attn_decode(q2, kc, kc.clone(), lens, torch.empty_like(q2), 1.0, workspace=ws)
 
 
-def test_both_row_maximum_paths():
-    """More work items than the partials kernel has waves (16 per CU, so B x 8 kv heads x 32
-    segments with B = CUs / 16 + 1): the row maxima come from the maximum kernel; the same
-    sequences in a smaller batch take them inside the partials kernel.  Both equal the oracle."""
+def test_large_batch_and_its_first_sequences():
+    """More than sixteen segments per CU (B x 8 kv heads x 32 segments with B = CUs / 16 + 1), one wave
+    each; the first three sequences alone run two waves per segment.  Both equal the oracle."""
     import paper_2609_25624_amd as rg
     B = rg.rg_device_cu_count() // 16 + 1
     H, Hkv, Lmax, D = 32, 8, 8192, 128
@@ -200,17 +199,16 @@ def test_whole_and_split_value_columns(D):
 
 @pytest.mark.parametrize("H,L", [(4, 33000), (3, 44000), (7, 19000)])
 def test_in_kernel_maximum_beyond_512_segment_maxima(H, L):
-    """One sequence long enough that its G x Jb segment maxima exceed the 512 a wave loads with
-    its first step (G = 4, 3, 7 query heads per kv head), so the partials wave folds the rest
-    in its tail loop.  One kv head: few work items, so the in-kernel maximum path is taken."""
+    """One sequence of more segments than a wave has lanes (G = 4, 3, 7 query heads per kv head): each
+    wave of the partials reduces the segment maxima of its heads in several rounds."""
     assert H * (-(-L // 256)) > 512
     _check(1, H, 1, L, 128, [L], seed=H * 7 + L)
 
 
-# The one-launch kernel (at most two segments per sequence; eight with one query head per kv head and D = 64) and
-# the wave-per-unit partials: group sizes that fill the lanes and that repeat heads, lengths around the
-# 128-position units, the 256-position segments and the value steps, empty and over-long sequences, segments on
-# either side of the column split (four segments per CU) and of the kept workgroup partials (one per CU).
+# The one-launch kernel (short caches of one or two query heads per kv head, one segment of more; eight segments with one
+# head and D = 64), the wave partials and the workgroup partials (D = 64, three and more heads): group sizes that fill the
+# lanes and that repeat heads, lengths around the 128-position units, the 256-position segments and the value steps, empty
+# and over-long sequences.
 @pytest.mark.parametrize("B,H,Hkv,L,D", [
     (3, 2, 2, 512, 64), (3, 4, 2, 300, 64), (3, 9, 3, 512, 64), (3, 14, 2, 129, 64), (2, 3, 3, 2048, 64),
     (3, 2, 2, 512, 128), (3, 4, 2, 257, 128), (3, 6, 2, 512, 128), (3, 8, 2, 127, 128),
@@ -240,6 +238,21 @@ def test_fused_and_wave_partials(B, H, Hkv, L, D):
     nan = np.isnan(want)
     assert np.array_equal(nan, np.isnan(got))
     gu.assert_bitwise(np.where(nan, 0.0, got), np.where(nan, 0.0, want), f"attn ({B},{H},{Hkv},{L},{D})")
+
+
+# Either side of the lines between the attention kernels (256 CUs): the one-launch kernel of four and eight lanes per
+# position, of pairs for more than half the CUs and of two rounds, the passes just beyond; workgroup partials of three to eight
+# heads; value waves of five and six chains, whole, split and with 10 KB of LDS.
+@pytest.mark.parametrize("B,H,Hkv,L,D", [
+    (3, 8, 2, 255, 64), (33, 16, 4, 300, 64), (3, 16, 2, 128, 64), (3, 10, 2, 100, 64), (2, 8, 1, 176, 64), (2, 8, 1, 177, 64),
+    (33, 16, 4, 300, 128), (32, 16, 4, 300, 128), (3, 4, 2, 200, 256), (3, 4, 2, 257, 256), (40, 7, 7, 120, 64),
+    (40, 7, 7, 129, 128), (65, 4, 4, 300, 64), (65, 8, 4, 300, 128), (257, 4, 1, 130, 128),
+    (3, 6, 2, 129, 64), (30, 40, 8, 700, 64), (5, 16, 2, 1024, 64), (64, 24, 8, 500, 64), (65, 24, 8, 500, 64),
+    (70, 40, 8, 300, 64), (70, 48, 8, 300, 64), (65, 40, 8, 500, 128), (9, 48, 8, 900, 128), (129, 40, 8, 257, 128),
+    (129, 48, 8, 257, 128), (129, 64, 8, 300, 128), (81, 40, 8, 300, 256), (81, 48, 8, 300, 256), (97, 56, 8, 300, 256),
+    (97, 64, 8, 290, 256), (20, 40, 8, 400, 256), (20, 48, 8, 400, 256)])
+def test_kernels_on_either_side_of_their_lines(B, H, Hkv, L, D):
+    test_fused_and_wave_partials(B, H, Hkv, L, D)
 
 
 # Long caches take their row maxima from the maximum kernel (one wave per row); the sequences in them may be short or empty.
