@@ -27,7 +27,8 @@ constexpr int kAttnFusedThreads = 512;
 //                                               23.3 / 26.9; D = 256, 2, two segments: 64 x 512 29.7 / 26.1 (one only)
 //   one head, D = 64, up to eight segments      256 x 2048 20 / 31; above a round of the CUs 512 x 1024 25.8 / 27.0,
 //                                               2048 x 1024 99 / 82, 2048 x 2048 145 / 171
-//   one head, at most 128 positions             two rounds too: D = 128, 512 x 128 16.0 / 16.4
+//   one head, at most 128 positions             two rounds too: D = 128, 512 x 128 16.0 / 16.4; D = 64, 288 x 164
+//                                               12.3 / 13.8, 384 x 256 15.9 / 15.9 (one segment, 1.5 rounds)
 //   three or four heads, one segment            D = 64: 64 x 256 17.4 / 17.8 (the group kernel), 128 x 128 12.0 / 15.7;
 //   or two on more than half the CUs            D = 128: 64 x 256 21.1 / 21.9, 64 x 512 24.1 / 22.6, 256 x 512 24.7 / 27.1
 //   five to eight heads, D = 64                 64 x 128 16.6 / 21.1, 64 x 256 24 / 21; eight 64 x 131 18.5 / 21.6
@@ -70,7 +71,8 @@ inline AttnRoute attn_route(int64_t B, int64_t Hkv, int64_t Lmax, int D, int G, 
     else if (GP == 4) r.fused = round && (J == 1 || (J == 2 && 2 * pairs > cus));
     else if (GP == 2) r.fused = round && J <= (D == 256 ? 1 : 2);
     else if (D == 64 && J > 2) r.fused = J <= 8 && (round || J >= 7 || (J >= 4 && pairs <= 2 * cus));
-    else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus));
+    else r.fused = J <= 2 && (round || (Lmax <= 128 && D < 256 && pairs <= 2 * cus) ||
+                              (D == 64 && J == 1 && 2 * pairs <= 3 * cus));
     if (pairs > 0xffffffffLL / kAttnFusedThreads) r.fused = false;
     r.group = !r.fused && D == 64 && G >= 3 && Lmax > 128 && items <= (G <= 4 ? 2 : 3) * cus;
     const int64_t heavy = G >= 7 ? 12 : 10;              // D = 256, five to eight heads: half segments per CU

@@ -201,7 +201,7 @@ int main() {
     // and only where it was measured ahead of one launch per pass: a round of the CUs, short caches of heavy groups
     const struct { int64_t pairs, L; int D, G; bool fused; } short_caches[] = {
         {8, 512, 64, 1, true}, {256, 512, 64, 1, true}, {512, 512, 64, 1, false}, {2048, 64, 64, 1, false},
-        {8192, 256, 64, 1, false}, {256, 2048, 64, 1, true}, {2048, 1024, 64, 1, false}, {2048, 2048, 64, 1, true},
+        {8192, 256, 64, 1, false}, {300, 200, 64, 1, true}, {400, 200, 64, 1, false}, {256, 2048, 64, 1, true}, {2048, 1024, 64, 1, false}, {2048, 2048, 64, 1, true},
         {512, 1100, 64, 1, true}, {256, 512, 128, 2, true}, {512, 128, 128, 2, false}, {512, 128, 128, 1, true},
         {512, 128, 256, 1, false}, {64, 200, 256, 2, true}, {64, 400, 256, 2, false}, {8, 256, 64, 4, true},
         {8, 300, 64, 4, false}, {200, 300, 64, 4, true}, {257, 64, 128, 4, false}, {64, 128, 64, 8, true}, {64, 150, 64, 8, true}, {64, 200, 64, 8, false},
