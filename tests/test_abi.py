@@ -467,3 +467,20 @@ def test_probe_library_exports_and_host_checks():
     assert L.rg_probe_fma(0, 12, 0x1000, 1, 1, None) == 1               # 8 or 16 chains
     assert L.rg_probe_fma(0, 8, 0x1000, 0, 1, None) == 1
     assert L.rg_probe_fma(0, 8, 0x1000, 1, 0, None) == 1
+
+
+def test_wave_tile_tests_reach_every_build():
+    # The shapes of test_gpu_wave_tile_rule.py are chosen so that each makes the rule take another build; the builds are
+    # read from the lists the kernels are made from.
+    from tests import test_gpu_wave_tile_rule as t
+    src = open(os.path.join(os.path.dirname(rg.__file__), "csrc", "rg_wtile.h")).read()
+    rg.rg_linear_set_launch(None)
+    for name, plan, shapes in (("BF16", rg.rg_plan, t.ALIGNED), ("F32", rg.rg_plan_f32w, t.ALIGNED_F32),
+                               ("ANY", rg.rg_plan, t.ANY), ("ANY", rg.rg_plan_f32w, t.ANY)):
+        text = re.search(rf"#define RG_WTILE_{name}\(B\)(.*?)\n(?=#define|\n|struct)", src, re.S).group(1)
+        builds = {(int(lm) * int(tm), 64 // int(lm) * int(tn))
+                  for lm, tm, tn in re.findall(r"B\((\d+), (\d+), (\d+),", text)}
+        assert len(builds) == text.count("B(")
+        plans = [plan(*s) for s in shapes]
+        reached = {(p["tile_m"], p["tile_n"]) for p in plans if p["kernel_name"] == "wtile"}
+        assert reached == builds, (name, sorted(builds - reached))

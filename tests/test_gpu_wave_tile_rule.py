@@ -1,7 +1,7 @@
 """The wave-tile builds that default launches choose among (rg_linear for M > 8, FP32 weights at
 M > 4, and any K or alignment the 16-byte kernels do not take) against the oracle, bit for bit.
 
-Every shape below makes the rule choose another build: the tiles from 8 x 16 to 64 x 64, with
+Every shape below makes the rule choose another build (tests/test_abi.py holds that all are reached): the tiles from 8 x 16 to 64 x 64, with
 ragged last tiles in M and N, a short last segment and slab, one and several rounds of
 segments, K below one slab, odd K (rows of x and W at every alignment), the bias and pointers off
 their 16-byte alignment.  No tolerance: the order fixes every bit.
