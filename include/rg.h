@@ -71,13 +71,15 @@ typedef enum {
 
 /* Kernel ids reported by rg_plan (scheduling only; the order is the same).  Default launches (no
  * override) run GEMV or SKINNY for M <= 8 (FP32 weights: STREAM for M <= 4) and WTILE for larger M and for every
- * K or alignment those do not take, but for the shapes TILED's 128 x 128 tiles are better at; the others run
- * when forced, in launches with overrides, or where K is beyond what these take. */
+ * K or alignment those do not take, but for the shapes another kernel is faster at: SKINNY for narrow BF16
+ * layers of up to 64 rows, TILED's 64 x 128 and 128 x 128 tiles for many rows of a short K, GENERIC for a few k
+ * that are not aligned.  The others run when forced, in launches with overrides, or where K is beyond what
+ * these take. */
 typedef enum {
     RG_KERNEL_GENERIC = 0,   /* one thread per output; any K, any alignment */
     RG_KERNEL_DECODE = 1,    /* M <= 64: streaming skinny GEMM, x in registers, slices of at most 4 rows */
     RG_KERNEL_TILED = 2,     /* register-tiled kernel, whole K per workgroup (the default for many
-                                128 x 128 tiles of a short K) */
+                                64 x 128 or 128 x 128 tiles of a short K) */
     RG_KERNEL_DECODE_XS = 3, /* M == 1 (when forced, or where the skinny kernel's x does not fit its
                                 registers): streaming GEMV with x streamed through LDS beside W */
     RG_KERNEL_GEMV = 4,      /* M == 1, K % 256 == 0, K >= 4096 (the default for K == 4096 with
@@ -178,8 +180,8 @@ int rg_linear_bias(const float* x, const uint16_t* w_bf16, const float* bias, fl
  *   w_f32  device pointer, float32 [N][K], 4-byte aligned
  *   y      device pointer, float32 [M][N], 4-byte aligned, must not overlap x or W
  * Kernels: RG_KERNEL_STREAM for M <= 4 with 16-byte aligned x and W and K % 4 == 0, the
- * wave-tile kernel otherwise, but for many 128 x 128 tiles of a short K (tiled); ktile, tiled,
- * wtile and generic when forced.  Errors, streams and ownership as rg_linear; the same
+ * wave-tile kernel otherwise, but for many 64 x 128 or 128 x 128 tiles of a short K (tiled) and a few
+ * unaligned k (generic); ktile, tiled, wtile and generic when forced.  Errors, streams and ownership as rg_linear; the same
  * rg_linear_set_launch overrides apply (decode, decode_xs, gemv and skinny cannot be
  * forced here: RG_ERR_RANGE).
  */

@@ -494,9 +494,9 @@ bool skinny_leads(int64_t M, int64_t N, int64_t K, const rg::WtileChoice& c) {
 // the wave tiles'.  Theirs, us, over 520 shapes each of 64 x 128 and 128 x 128 tiles (within 0.9 to 1.1 for 9 of 10):
 // a fixed part, one per tile of a CU and the FMAs at 175 / 189 (FP32 weights 169 / 179) per ns and CU.  The wave tiles'
 // estimate is high by a fifth there, less with one or three waves per workgroup, and with two whose workgroups
-// fill the second or third round to the last few (0.8 of the estimate becomes 1.1 there).  Measured, register against wave tiles, us: 1906 x 4288 x 360 81 against 109, 1483 x 4770 x 736 145 against
-// 211, 2048 x 3072 x 1536 249 against 298; FP32 102 x 32768 x 1096 129 against 167; 333 x 28672 x 4096 stays (1118
-// against 931).
+// fill the second or third round to the last few (0.8 of the estimate becomes 1.1 there).  Measured, register against
+// wave tiles, us: 1906 x 4288 x 360 81 against 109, 1483 x 4770 x 736 145 against 211, 2048 x 3072 x 1536 249 against
+// 298; FP32 102 x 32768 x 1096 129 against 167; 333 x 28672 x 4096 stays (1118 against 931).
 bool register_tiles_lead(int64_t M, int64_t N, int64_t K, bool f32, const rg::WtileChoice& c) {
     Plan p;
     const rg_launch_t none = {};
@@ -568,9 +568,9 @@ rg::WtileChoice wave_tile(int64_t M, int64_t N, int64_t K, bool f32, bool aligne
 //                    down 4096 x 14336: 60.6 / 168 / 219 -> 46 / 85 / 109; at M = 8 the skinny
 //                    kernel stays (QKV 17.4 against 16.9, gate+up 50.8 against 57)
 //   ktile, wtile     gate+up 28672 x 4096 at M = 24 / 64: 143 / 220 -> 91 / 183
-//   tiled            gate+up at M = 333: 1118 -> 1036; 8192 x 28672 at M = 2048: 10650 -> 10280
+//   tiled            gate+up at M = 333: 1118 -> 931; 8192 x 28672 at M = 2048: 10650 -> 10280
 //   generic          one thread per output, a serial chain of 2-byte loads each: 2999 x 1003
-//                    at M = 5: 255 -> 12
+//                    at M = 5: 255 -> 8.6
 bool wave_tile_plan(int64_t M, int64_t N, int64_t K, bool f32, bool fast_ok, int64_t own_max_m, const rg_launch_t& o,
                     Plan* p) {
     if (!is_default(o) || K > rg::kWtileMaxK || (fast_ok && M <= own_max_m)) return false;

@@ -1,6 +1,7 @@
 // Wave-tile kernel for the fused-upcast linear layer (gfx950): the default for M > 8, for FP32
-// weights at M > 4 (both except where many 128 x 128 tiles of a short K lead, wtile_choose), and
-// for every K or alignment the 16-byte kernels do not take.
+// weights at M > 4 and for every K or alignment the 16-byte kernels do not take, but for the shapes
+// where the planner finds another kernel ahead: narrow BF16 layers of up to 64 rows (skinny), register
+// tiles of a short K (tiled), a few unaligned k (generic).
 //
 // Same order as every kernel of the library (include/rg.h, RG-ORDER-1; paper: Design,
 // eq. 2 and rules R1-R4): 256-wide K segments, each a chain of fmaf from +0 in ascending
@@ -26,12 +27,13 @@
 // outputs in ascending segment order to the running total (LDS); the last round stores
 // y (+ b).  No atomics, no workspace, no second launch.
 //
-// What bounds it.  A SIMD issues one FMA per 2 cycles over two waves (one wave: one per 4), LDS
-// returns 128 bytes per cycle to a CU, so a tile of TM x TN chains per lane is bound by the
-// FMAs (and TN widenings per k) from 8 x 8 down to about 8 x 4, and by its LDS reads
-// (4 / TN + 2 / TM bytes per FMA) below that.  With two waves per SIMD an FMA whose three
-// operands lie in registers of the same parity holds up the other wave, so W is
-// widened into register pairs such that x and W never share a parity (widen2).
+// What bounds it.  A SIMD issues one FMA per 2 cycles over two waves (one wave: one per 4).  A lane's
+// TM x TN chains read 4 / TN + 2 / TM bytes of LDS per FMA (FP32 weights 4 / TN + 4 / TM) and widen TN values of W
+// per k, so the fewer chains the slower a multiply-add (the builds' rates in rg_wtile.h).  The counters give 0.60 of the FMA
+// issue limit to 64 x 56 tiles at M = 64 and 0.36 to 16 x 64 at M = 16, with no bank conflict and nearly every wave
+// slot taken at M = 64 (7.2 of 8; 5.7 at M = 16); what the rest waits for, the counters taken do not show.
+// W is widened into register pairs such that an FMA's x and W never share a register parity (widen2): these kernels
+// run faster so; why is not measured apart.
 // 28672 x 4096 at M = 64: 183 us (82 TFLOP/s) against 223 with the transposing wave tile this
 // replaced; 4096 x 14336: 109 against 219; 6144 x 4096: 47 against 74.
 //
@@ -115,8 +117,8 @@ __device__ __forceinline__ void wg_barrier() {
 // The two bfloat16 of a packed dword (even k in the low half), widened exactly.  The odd k's value is
 // placed in the even register of a pair and the even k's in the odd one: x arrives by 16-byte LDS reads,
 // whose k-th register has the parity of k, so an FMA's x and W never share a register
-// parity (two waves per SIMD then issue at the full rate: 64 x 56 tiles 185 -> 180 us at M = 64
-// on 28672 x 4096, 64 x 64 tiles 10.77 -> 10.28 ms on 8192 x 28672 at M = 2048).
+// parity (64 x 56 tiles 185 -> 180 us at M = 64 on 28672 x 4096, 64 x 64 tiles
+// 10.77 -> 10.28 ms on 8192 x 28672 at M = 2048).
 __device__ __forceinline__ void widen2(uint32_t d, float& even_k, float& odd_k) {
     uint64_t pair = ((uint64_t)(d << 16) << 32) | (d & 0xffff0000u);
     asm("" : "+v"(pair));
