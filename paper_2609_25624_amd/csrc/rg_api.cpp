@@ -522,12 +522,24 @@ bool register_tiles_lead(int64_t M, int64_t N, int64_t K, bool f32, const rg::Wt
     return us < high * (c.us + 2.5);
 }
 
-// Unaligned calls of a few k: one thread per output has nothing to stage.  Measured, generic against wave tile, us
-// (BF16): 51 x 231036 x 1 23.0 against 29.2, 8 x 52136 x 5 3.6 against 5.0, 1 x 187328 x 21 5.6 against 7.4; behind
-// beyond (94 x 157301 x 3 35 against 27.5).
+// Unaligned calls of a few k: one thread per output has nothing to stage, until its loads, a cache line per lane of
+// every row, are more than the wave tiles' whole lines (the more k and the more outputs, the sooner).  The lines lie
+// where both met over 2400 shapes.  Measured, generic against wave tile, us: BF16 51 x 231036 x 1 23.0 / 29.2,
+// 98 x 66560 x 1 14.3 / 18.1, 10 x 150592 x 5 6.9 / 9.3, 8 x 52136 x 5 3.6 / 5.0, 3 x 64891 x 11 3.8 / 5.1,
+// 2 x 296744 x 9 5.8 / 9.6, 1 x 155712 x 27 6.8 / 10.0 and, behind the lines, 94 x 157301 x 3 35 / 27.5,
+// 2 x 176000 x 23 14.0 / 7.6; FP32 2 x 349683 x 7 6.1 / 9.3, 1 x 324871 x 11 6.5 / 8.7, 1 x 58557 x 23 3.6 / 5.0 and,
+// behind, 3 x 130359 x 13 9.9 / 5.1.
 bool generic_leads(int64_t M, int64_t N, int64_t K, bool f32) {
-    return (K < 4 && M <= 64) || (K < 6 && M * N < (f32 ? 700000 : 1500000)) || (K < 8 && M * N < (f32 ? 300000 : 700000)) ||
-           (!f32 && M <= 2 && K < 24 && N < 300000);
+    const int64_t outs = M * N;
+    if (K >= 28) return false;
+    if (K < 4 && (M <= 64 || outs < (K < 2 ? 15000000 : 1200000))) return true;
+    if (f32)
+        return (K < 6 && outs < (M <= 4 ? 1000000 : 700000)) || (K < 8 && outs < (M <= 2 ? 5000000 / K : 300000)) ||
+               (K < 12 && M <= 2 && outs < (M == 1 ? 5000000 : 3000000) / K) || (K < 26 && M <= 2 && outs < 1800000 / K);
+    return (K < 6 && outs < (M <= 16 ? 3000000 : 1500000)) || (K < 8 && outs < 700000) ||
+           (K < 12 && outs < (M <= 2 ? 8000000 : M <= 4 ? 5200000 : 3500000) / K) ||
+           (K < 14 && M <= 4 && outs < 2500000 / K) || (K < 16 && M <= 2 && outs < 5500000 / K) ||
+           (K < 20 && M == 2 && outs < 3000000 / K) || (M == 1 && outs < 6800000 / K);
 }
 
 // The wave tile a shape runs on by default, if it is the better kernel for it.

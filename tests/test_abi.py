@@ -181,9 +181,11 @@ def test_default_kernel_where_the_wave_tiles_are_behind():
             ((333, 28672, 4096), "wtile"), ((333, 6144, 4096), "wtile"), ((333, 4096, 14336), "wtile"),
             ((333, 4096, 4096), "wtile"), ((64, 6144, 4096), "wtile"), ((64, 28672, 4096), "wtile"), ((100, 300, 1000), "wtile"),
             ((51, 231036, 1), "generic"), ((8, 52136, 5), "generic"), ((1, 187328, 21), "generic"), ((5, 2999, 1003), "wtile"),
+            ((2, 176000, 23), "wtile"), ((3, 64891, 11), "generic"), ((2, 296744, 9), "generic"), ((206, 22390, 1), "generic"), ((98, 66560, 1), "generic"),
             ((1, 31, 263), "wtile"))
     fp32 = (((102, 32768, 1096), "tiled"), ((487, 11335, 384), "tiled"), ((400, 8192, 2304), "tiled"), ((333, 28672, 4096), "wtile"),
-            ((16, 16, 4096), "wtile"), ((51, 231036, 1), "generic"), ((1, 187328, 21), "wtile"))
+            ((16, 16, 4096), "wtile"), ((51, 231036, 1), "generic"), ((1, 187328, 21), "wtile"),
+            ((2, 349683, 7), "generic"), ((1, 58557, 23), "generic"), ((3, 130359, 13), "wtile"))
     for shape, kernel in bf16:
         assert rg.rg_plan(*shape)["kernel_name"] == kernel, (shape, rg.rg_plan(*shape))
     for shape, kernel in fp32:

@@ -87,7 +87,8 @@ def test_odd_k_builds(M, N, K, f32):
     (33, 40, 2056, False, "skinny"), (13, 64, 32168, False, "skinny"),
     (1906, 4288, 360, False, "tiled"), (2000, 4096, 1032, False, "tiled"), (249, 27072, 304, False, "tiled"),
     (142, 28835, 320, True, "tiled"), (2000, 4096, 1036, True, "tiled"), (487, 11335, 388, True, "tiled"),
-    (51, 2310, 1, False, "generic"), (2, 3001, 21, False, "generic"), (7, 555, 7, True, "generic")])
+    (51, 2310, 1, False, "generic"), (1, 3001, 21, False, "generic"), (7, 555, 7, True, "generic"),
+    (3, 901, 11, False, "generic"), (2, 501, 23, True, "generic"), (206, 390, 1, False, "generic")])
 def test_defaults_that_other_kernels_lead(M, N, K, f32, kernel):
     import paper_2609_25624_amd as rg
     rg.rg_linear_set_launch(None)
