@@ -29,9 +29,9 @@
 //
 // What bounds it.  A SIMD issues one FMA per 2 cycles over two waves (one wave: one per 4).  A lane's
 // TM x TN chains read 4 / TN + 2 / TM bytes of LDS per FMA (FP32 weights 4 / TN + 4 / TM) and widen TN values of W
-// per k, so the fewer chains the slower a multiply-add (the builds' rates in rg_wtile.h).  The counters give 0.60 of the FMA
-// issue limit to 64 x 56 tiles at M = 64 and 0.36 to 16 x 64 at M = 16, with no bank conflict and nearly every wave
-// slot taken at M = 64 (7.2 of 8; 5.7 at M = 16); what the rest waits for, the counters taken do not show.
+// per k, so the fewer chains the slower a multiply-add (the builds' rates in rg_wtile.h).  Counters on 28672 x 4096 give
+// about 0.6 of the FMA issue limit to 64 x 56 tiles at M = 64 and 0.35 to 16 x 64 at M = 16, with no bank conflict and
+// nearly every wave slot taken at M = 64 (about 7 of 8; 6 at M = 16); what the rest waits for, they do not show.
 // W is widened into register pairs such that an FMA's x and W never share a register parity (widen2): these kernels
 // run faster so; why is not measured apart.
 // 28672 x 4096 at M = 64: 183 us (82 TFLOP/s) against 223 with the transposing wave tile this
