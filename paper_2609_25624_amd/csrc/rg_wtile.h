@@ -84,7 +84,7 @@ inline int64_t wtile_lds(const WtileBuild& b, int64_t J, int nw) {
 // segments, a short last segment alone in its round counted as short), plus 1 us for its first slabs and
 // per round 0.3 us and the fold, which its threads share; a CU works off ceil(tiles / 256) tiles, as many
 // at a time as its eight wave slots and LDS hold (builds of sixteen waves share the slots), and never
-// faster than W streams (6.2 GB per ms: a constant of this model; the fastest reads measured reach 6.7).  So 1536 = 6 segments run on 2 waves, four workgroups per
+// faster than W streams (6.2 GB per ms: a constant of this model; the fastest reads measured reach 6.8).  So 1536 = 6 segments run on 2 waves, four workgroups per
 // CU, not on 6 waves with two slots empty (2048 x 16384 x 1536 1472 -> 1116 us).
 //
 // Not ok where no build's tiles fit a launch, and where the 128 x 128 register tiles are the better ones: at
